@@ -75,9 +75,39 @@ std::vector<int32_t> build_tiles(int32_t rows, const int32_t* rp, int32_t tn, in
     return t;
 }
 
+// Structure of a Sell matrix (see lp_device.h): slice offsets and the row of every lane.
+struct SellHost {
+    std::vector<int32_t> ptr, row;
+    int64_t slots() const { return ptr.empty() ? 0 : ptr.back(); }
+};
+
+// Rows go to slices longest first (a stable counting sort), or in order when `sorted` is
+// false. False when a row is longer than one thread sums.
+bool build_sell(int32_t rows, const int32_t* rp, bool sorted, SellHost* S) {
+    const int32_t slices = (rows + 63) / 64;
+    S->ptr.assign(static_cast<size_t>(slices) + 1, 0);
+    S->row.assign(static_cast<size_t>(slices) * 64, rows);
+    int32_t first[kSoloMaxRow + 2] = {0};
+    for (int32_t r = 0; r < rows; ++r) {
+        const int32_t len = rp[r + 1] - rp[r];
+        if (len > kSoloMaxRow) return false;
+        first[kSoloMaxRow - len + 1]++;
+    }
+    for (int32_t k = 1; k <= kSoloMaxRow + 1; ++k) first[k] += first[k - 1];
+    for (int32_t r = 0; r < rows; ++r) S->row[sorted ? first[kSoloMaxRow - (rp[r + 1] - rp[r])]++ : r] = r;
+    for (int32_t s = 0; s < slices; ++s) {
+        int32_t longest = 0;
+        for (int32_t l = s * 64; l < std::min(rows, s * 64 + 64); ++l)
+            longest = std::max(longest, rp[S->row[l] + 1] - rp[S->row[l]]);
+        S->ptr[s + 1] = S->ptr[s] + 64 * ((longest + 1) / 2);
+    }
+    return true;
+}
+
 // Host-side integer structure of an LP, built once at lp_create.
 struct Prep {
     std::vector<int32_t> rpT, ciT, perm, tA, tAT;
+    SellHost sA, sAT;  // empty: the LP has no one-workgroup form
     PanelLayoutHost LA, LAT;
     int shape = 1;  // row-tile shape
     bool panels = false;
@@ -103,6 +133,7 @@ struct Offsets {
     size_t fr[6];  // residual restarts: z - T(z) of the last iterate (x, y, A~x parts), then of the anchor
     size_t f32[15] = {0};
     size_t pA[7] = {0}, pAT[7] = {0}, pA32 = 0, pAT32 = 0;
+    size_t sA[5] = {0}, sAT[5] = {0};  // Sell: slice offsets, rows, columns, values, FP32 values
     size_t part, sc, tr, job;
 };
 
@@ -217,6 +248,7 @@ struct lp_handle {
     int64_t samples = 0;
     std::shared_ptr<Prep> prep;     // shared with the server's per-request clones
     std::shared_ptr<HostData> raw;
+    std::vector<int32_t> sell_a, sell_at;  // slice offsets of the Sell matrices (empty: none)
     bool has_x0 = false, has_y0 = false;
     bool deferred = false;
     bool on_device = false;
@@ -380,6 +412,9 @@ BatchJob make_job(lp_handle* h, const lp_options* bo) {
     // the time limit becomes a device-clock deadline, checked at every evaluation on the device
     J.limit_ticks = 0;
     J.t0 = nullptr;
+    J.variant = SOLO_NONE;
+    J.eval_blocks = 1;
+    J.a_slices = J.a_slots = J.at_slices = J.at_slots = J.plain_stop = 0;
     int khz = 0;
     if (o.time_limit_s > 0.0 && hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, h->device) == hipSuccess &&
         khz > 0) {
@@ -387,6 +422,45 @@ BatchJob make_job(lp_handle* h, const lp_options* bo) {
         J.limit_ticks = ticks >= 9.0e18 ? static_cast<long long>(9.0e18) : std::max(1LL, static_cast<long long>(ticks));
     }
     return J;
+}
+
+// How the one-workgroup solver runs an LP: its instance, the slices of A and A^T staged in
+// LDS, and the LDS it needs. `whole`: all of the LP's arrays there fit the budget.
+struct SoloPlan {
+    int variant = SOLO_NONE, a_slices = 0, at_slices = 0, a_slots = 0, at_slots = 0, lds = 0;
+    bool whole = false;
+    void apply(BatchJob* J) const {
+        J->variant = variant;
+        J->a_slices = a_slices;
+        J->a_slots = a_slots;
+        J->at_slices = at_slices;
+        J->at_slots = at_slots;
+    }
+};
+
+// An LP with at most one row and one column per thread takes the fewest threads that give it
+// that (fewer waves meet at each barrier, and several such workgroups share a CU) when all of
+// it fits the LDS budget; the wider ones stage the slices that fit, those of A (the longer
+// rows of the two in most LPs, summed by fewer threads) first. Operands that no longer fit the
+// registers of 1024 threads stay in global memory.
+SoloPlan solo_plan(const lp_handle* h, int budget) {
+    SoloPlan S;
+    if (h->sell_a.empty()) return S;
+    const int m = h->m, n = h->n, fp32 = h->opt.precision == LP_PREC_FP32_REFINED;
+    const int na = static_cast<int>(h->sell_a.size()) - 1, nat = static_cast<int>(h->sell_at.size()) - 1;
+    auto bytes = [&](int a, int at) { return solo_lds_bytes(m, n, fp32, h->sell_a[a], h->sell_at[at]); };
+    while (S.a_slices < na && bytes(S.a_slices + 1, 0) <= budget) S.a_slices++;
+    while (S.at_slices < nat && bytes(S.a_slices, S.at_slices + 1) <= budget) S.at_slices++;
+    S.a_slots = h->sell_a[S.a_slices];
+    S.at_slots = h->sell_at[S.at_slices];
+    S.lds = bytes(S.a_slices, S.at_slices);
+    S.whole = S.a_slices == na && S.at_slices == nat;
+    const int mx = std::max(m, n);
+    if (S.whole && mx <= 512) S.variant = mx <= 256 ? SOLO_256 : SOLO_512;
+    else if (solo_sorted(m, n)) S.variant = SOLO_1024;
+    else if (n <= 4096 && m <= 2048) S.variant = SOLO_WIDE;
+    else S.variant = solo_register_dims(m, n, fp32) ? SOLO_WIDE32 : SOLO_GLOBAL;
+    return S;
 }
 
 int32_t finish_batch(const std::vector<lp_handle*>& hs, hipStream_t s) {
@@ -585,23 +659,71 @@ void run_round(DevMaps& D, hipStream_t s, int capture_after) {
     D.stable_rounds++;
 }
 
-// LPs solved one per workgroup in a single persistent launch, started on its own stream
-// so that it runs beside the block-diagonal launches of the larger LPs. The host arrays
+// LPs solved one per workgroup in persistent launches, started on streams of their own so
+// that they run beside the block-diagonal launches of the larger LPs. The host arrays
 // stay alive until finish_persistent. The runtime spreads streams over a few hardware queues
 // in creation order, and two launches whose streams share a queue run one after the other,
-// so the block-diagonal launches get the third of three streams created together (s[2])
+// so the block-diagonal launches get the last of four streams created together (s[3])
 // rather than an older stream that may share a queue with a persistent launch.
 struct PersistentRun {
     std::vector<BatchJob> jobs;
     std::vector<int32_t> order;
     char* buf = nullptr;
-    hipStream_t s[3] = {nullptr, nullptr, nullptr};
+    hipStream_t s[4] = {nullptr, nullptr, nullptr, nullptr};
 };
 
-// Two persistent launches at most, each on a stream of its own: the LPs whose iteration
-// arrays fit in the small-LP LDS budget (one workgroup per CU, each LP solved from LDS) and
-// the others (batch_wg_per_cu workgroups per CU, from global memory). Each launch takes its
-// LPs largest first.
+// The launches of a persistent batch: LPs of one kernel, their dynamic LDS.
+enum BatchGroup { BG_SOLO_1024 = 0, BG_SOLO_512, BG_SOLO_256, BG_TILES_LDS, BG_TILES, BG_COUNT };
+static_assert(BG_COUNT <= kBatchCounters, "one work counter per launch");
+
+struct BatchGroups {
+    int first[BG_COUNT] = {0}, count[BG_COUNT] = {0}, lds[BG_COUNT] = {0};
+};
+
+// Assigns every LP its launch: the one-workgroup solver for those that have its form, else the
+// row tiles (staged in LDS when the LP fits the budget). order[] lists the LPs launch by
+// launch, in each largest first (ties by position: a strict order, so the sort needs no
+// buffer).
+void group_batch(lp_handle* const* hs, int count, int budget, int32_t* order, uint8_t* group, BatchGroups* G) {
+    *G = BatchGroups{};
+    for (int32_t i = 0; i < count; ++i) {
+        const SoloPlan plan = solo_plan(hs[i], budget);
+        int g, lds = plan.lds;
+        if (plan.variant != SOLO_NONE) {
+            const int threads = solo_threads(plan.variant);
+            g = threads == 256 ? BG_SOLO_256 : threads == 512 ? BG_SOLO_512 : BG_SOLO_1024;
+        } else {
+            const size_t need = small_lp_lds_bytes(hs[i]->P);
+            const bool fits = budget > 0 && need <= static_cast<size_t>(budget);
+            g = fits ? BG_TILES_LDS : BG_TILES;
+            lds = fits ? static_cast<int>((need + 16383) / 16384 * 16384) : 0;
+        }
+        group[i] = static_cast<uint8_t>(g);
+        order[i] = i;
+        G->count[g]++;
+        G->lds[g] = std::max(G->lds[g], lds);
+    }
+    for (int g = 1; g < BG_COUNT; ++g) G->first[g] = G->first[g - 1] + G->count[g - 1];
+    std::sort(order, order + count, [&](int32_t a, int32_t b) {
+        if (group[a] != group[b]) return group[a] < group[b];
+        return hs[a]->nnz != hs[b]->nnz ? hs[a]->nnz > hs[b]->nnz : a < b;
+    });
+}
+
+// Launches group g with its own counter; enough workgroups to fill the device at most.
+void launch_group(const BatchGroups& G, int g, const BatchJob* jobs, const int32_t* order, int32_t* counters, int cus,
+                  int wpc, hipStream_t s) {
+    const int count = G.count[g];
+    if (count == 0) return;
+    const int threads = g == BG_SOLO_1024 ? 1024 : g == BG_SOLO_512 ? 512 : 256;
+    if (g <= BG_SOLO_256)
+        launch_solo(threads, jobs, order + G.first[g], count, counters + g, std::min(cus * (1024 / threads), count),
+                    G.lds[g], s);
+    else
+        launch_batch(jobs, order + G.first[g], count, counters + g, std::min(g == BG_TILES ? cus * wpc : cus, count), s,
+                     G.lds[g]);
+}
+
 int32_t start_persistent(const std::vector<lp_handle*>& hs, const lp_options* bo, PersistentRun& R) {
     const int count = static_cast<int>(hs.size());
     lp_handle* h0 = hs[0];
@@ -610,54 +732,38 @@ int32_t start_persistent(const std::vector<lp_handle*>& hs, const lp_options* bo
     const int budget = bo ? bo->small_lp_lds : h0->opt.small_lp_lds;
     R.jobs.resize(static_cast<size_t>(count));
     R.order.resize(static_cast<size_t>(count));
-    std::vector<size_t> need(static_cast<size_t>(count));
-    size_t cap = 0;
-    int n_lds = 0;
     for (int i = 0; i < count; ++i) {
         R.jobs[i] = make_job(hs[i], bo);
-        R.order[i] = i;
-        need[i] = small_lp_lds_bytes(R.jobs[i].P);
-        if (budget > 0 && need[i] <= static_cast<size_t>(budget)) {
-            cap = std::max(cap, need[i]);
-            ++n_lds;
-        }
+        solo_plan(hs[i], budget).apply(&R.jobs[i]);
     }
-    auto in_lds = [&](int32_t i) { return budget > 0 && need[i] <= static_cast<size_t>(budget); };
-    // LDS LPs first, then the others; each part largest first
-    std::stable_sort(R.order.begin(), R.order.end(), [&](int32_t a, int32_t b) {
-        if (in_lds(a) != in_lds(b)) return in_lds(a);
-        return hs[a]->nnz > hs[b]->nnz;
-    });
-    const int lds_cap = n_lds ? static_cast<int>((cap + 16383) / 16384 * 16384) : 0;
+    std::vector<uint8_t> group(static_cast<size_t>(count));
+    BatchGroups G;
+    group_batch(hs.data(), count, budget, R.order.data(), group.data(), &G);
     int cus = 256;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h0->device) != hipSuccess || cus < 1)
         cus = 256;
     const int wpc = (bo && bo->batch_wg_per_cu > 0) ? bo->batch_wg_per_cu : 3;
     const size_t bj = sizeof(BatchJob) * static_cast<size_t>(count), bo_ = sizeof(int32_t) * static_cast<size_t>(count);
     const size_t oc = (bj + bo_ + 255) / 256 * 256;
-    HIP_TRY(h0, hipMalloc(reinterpret_cast<void**>(&R.buf), oc + 512));
+    HIP_TRY(h0, hipMalloc(reinterpret_cast<void**>(&R.buf), oc + 256));
     BatchJob* djobs = reinterpret_cast<BatchJob*>(R.buf);
     int32_t* dorder = reinterpret_cast<int32_t*>(R.buf + bj);
-    int32_t* dcounter = reinterpret_cast<int32_t*>(R.buf + oc);  // one counter per launch, 256 bytes apart
+    int32_t* dcounters = reinterpret_cast<int32_t*>(R.buf + oc);
     long long* dt0 = reinterpret_cast<long long*>(R.buf + oc + 128);  // device clock at the start of the call
     for (BatchJob& J : R.jobs) J.t0 = dt0;
     hipError_t e = hipSuccess;
-    for (int l = 0; l < 3 && e == hipSuccess; ++l)
-        e = hipStreamCreateWithFlags(&R.s[l], hipStreamNonBlocking);
+    for (hipStream_t& st : R.s)
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipMemcpyAsync(djobs, R.jobs.data(), bj, hipMemcpyHostToDevice, R.s[0]);
     if (e == hipSuccess) e = hipMemcpyAsync(dorder, R.order.data(), bo_, hipMemcpyHostToDevice, R.s[0]);
-    if (e == hipSuccess) e = hipMemsetAsync(dcounter, 0, 512, R.s[0]);
     if (e == hipSuccess) {
-        launch_batch_start(dcounter, dt0, R.s[0]);
+        launch_batch_start(dcounters, dt0, R.s[0]);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(R.s[0]);
-    if (e == hipSuccess && n_lds > 0) {
-        launch_batch(djobs, dorder, n_lds, dcounter, std::min(cus, n_lds), R.s[1], lds_cap);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess && count > n_lds) {
-        launch_batch(djobs, dorder + n_lds, count - n_lds, dcounter + 64, std::min(cus * wpc, count - n_lds), R.s[0]);
+    static constexpr int kStreamOf[BG_COUNT] = {0, 1, 2, 1, 2};
+    for (int g = 0; g < BG_COUNT && e == hipSuccess; ++g) {
+        launch_group(G, g, djobs, dorder, dcounters, cus, wpc, R.s[kStreamOf[g]]);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return fail(h0, LP_ERR_DEVICE, std::string("batched solve: ") + hipGetErrorString(e));
@@ -787,6 +893,19 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
     h->tile_shape = Q.shape;
     Q.tA = build_tiles(m, rp, tile_nnz_of(Q.shape), &dummy_long);
     Q.tAT = build_tiles(n, Q.rpT.data(), tile_nnz_of(Q.shape), &dummy_long);
+    // One-workgroup form: 16-bit columns, LDS for the gathered vectors, short rows, and padding
+    // (slices as wide as their longest row) that stays within four times the entries. Rows
+    // are sorted where a thread keeps its rows' operands in registers; elsewhere the operands
+    // are read at every iteration, or the row number is not worth a register, and the rows keep
+    // their order.
+    const bool sorted = solo_sorted(m, n);
+    const bool admits = m >= 1 && m <= kSoloMaxDim && n <= kSoloMaxDim && nnz <= kSoloMaxNnz &&
+                        solo_lds_bytes(m, n, o.precision == LP_PREC_FP32_REFINED, 0, 0) <= kSoloLdsMax &&
+                        build_sell(m, rp, sorted, &Q.sA) && build_sell(n, Q.rpT.data(), sorted, &Q.sAT) &&
+                        Q.sA.slots() + Q.sAT.slots() <= 4 * nnz + 16384;
+    if (!admits) Q.sA = Q.sAT = SellHost{};
+    h->sell_a = Q.sA.ptr;
+    h->sell_at = Q.sAT.ptr;
     int cus = 256;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus < 1)
         cus = 256;
@@ -885,6 +1004,18 @@ size_t arena_layout(const lp_handle* h, Offsets* O) {
             O->pA32 = L.add(sizeof(float) * Q.LA.packed.size());
             O->pAT32 = L.add(sizeof(float) * Q.LAT.packed.size());
         }
+    }
+    auto add_sell = [&](const SellHost& S, size_t* off) {
+        const size_t slots = static_cast<size_t>(S.slots());
+        off[0] = L.add(sizeof(int32_t) * S.ptr.size());
+        off[1] = L.add(sizeof(int32_t) * S.row.size());
+        off[2] = L.add(sizeof(uint32_t) * slots);
+        off[3] = L.add(2 * sizeof(double) * slots);
+        off[4] = fp32 ? L.add(2 * sizeof(float) * slots) : 0;
+    };
+    if (!Q.sA.ptr.empty()) {
+        add_sell(Q.sA, O->sA);
+        add_sell(Q.sAT, O->sAT);
     }
     O->part = L.add(sizeof(double) * kNT * kMaxRedBlocks);
     O->sc = L.add(sizeof(Scalars));
@@ -1012,6 +1143,15 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
             P.AT.pan.v32 = F(O.pAT32);
         }
     }
+    const bool sell = !Q.sA.ptr.empty();
+    auto bind_sell = [&](const SellHost& H, const size_t* off, Sell& S) {
+        S = Sell{static_cast<int>(H.ptr.size()) - 1, static_cast<int>(H.slots()), I(off[0]), I(off[1]),
+                 reinterpret_cast<const unsigned*>(b + off[2]), D(off[3]), fp32 ? F(off[4]) : nullptr};
+    };
+    if (sell) {
+        bind_sell(Q.sA, O.sA, P.sA);
+        bind_sell(Q.sAT, O.sAT, P.sAT);
+    }
     P.c = D(O.c);
     P.xl = D(O.xl);
     P.xu = D(O.xu);
@@ -1088,6 +1228,12 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
         HIP_TRY(h, upload_layout(Q.LA, O.pA));
         HIP_TRY(h, upload_layout(Q.LAT, O.pAT));
     }
+    if (sell) {
+        HIP_TRY(h, H2D(I(O.sA[0]), Q.sA.ptr.data(), sizeof(int32_t) * Q.sA.ptr.size()));
+        HIP_TRY(h, H2D(I(O.sA[1]), Q.sA.row.data(), sizeof(int32_t) * Q.sA.row.size()));
+        HIP_TRY(h, H2D(I(O.sAT[0]), Q.sAT.ptr.data(), sizeof(int32_t) * Q.sAT.ptr.size()));
+        HIP_TRY(h, H2D(I(O.sAT[1]), Q.sAT.row.data(), sizeof(int32_t) * Q.sAT.row.size()));
+    }
     if (h->has_x0) HIP_TRY(h, H2D(h->d_x0, x0, sn));
     if (h->has_y0 && m > 0) HIP_TRY(h, H2D(h->d_y0, y0, sm));
     HIP_TRY(h, hipMemsetAsync(P.sc, 0, sizeof(Scalars), s));
@@ -1112,6 +1258,12 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
             launch_to_float(D(O.pA[3]), F(O.pA32), Q.LA.nnz_packed, s);
             launch_to_float(D(O.pAT[3]), F(O.pAT32), Q.LAT.nnz_packed, s);
         }
+    }
+    if (sell) {
+        launch_fill_sell(P.A.csr, P.sA, reinterpret_cast<unsigned*>(b + O.sA[2]), D(O.sA[3]),
+                         fp32 ? F(O.sA[4]) : nullptr, s);
+        launch_fill_sell(P.AT.csr, P.sAT, reinterpret_cast<unsigned*>(b + O.sAT[2]), D(O.sAT[3]),
+                         fp32 ? F(O.sAT[4]) : nullptr, s);
     }
     launch_prepare(P, D(O.c), D(O.bl), D(O.bu), D(O.xl), D(O.xu), D(O.R), D(O.C), D(O.Ri), D(O.Ci), h->d_x0,
                    h->d_y0, s);
@@ -1182,6 +1334,8 @@ lp_handle* clone_for_request(const lp_handle* t) {
     h->arena_bytes = t->arena_bytes;
     h->prep = t->prep;
     h->raw = t->raw;
+    h->sell_a = t->sell_a;
+    h->sell_at = t->sell_at;
     h->has_x0 = t->has_x0;
     h->has_y0 = t->has_y0;
     h->deferred = true;
@@ -1791,12 +1945,16 @@ namespace {
 // 0), stopping on E_rel (term_mode 0) or on one residual alone (1 primal, 2 dual: the
 // polishing solves), with the set-up primal weight or omega0 > 0.
 // lp_solve of an LP whose iteration arrays fit the small-LP LDS budget: one workgroup runs
-// the whole loop from LDS (the persistent batched path with a batch of one), bit-identical to
-// the kernel-per-phase loop with the same row tiles; the time limit is its device deadline.
-int32_t solve_one_workgroup(lp_handle* h, size_t lds_need) {
+// the whole loop from LDS (a batch of one), bit-identical to the kernel-per-phase loop with
+// the same row tiles; the time limit is its device deadline. Without a plan of the
+// one-workgroup solver it is the row tiles staged in lds_need bytes.
+int32_t solve_one_workgroup(lp_handle* h, size_t lds_need, const SoloPlan& plan, int eval_blocks) {
     hipStream_t s = h->stream;
     const auto t0 = std::chrono::steady_clock::now();
     BatchJob J = make_job(h, nullptr);
+    plan.apply(&J);
+    J.eval_blocks = eval_blocks;
+    J.plain_stop = 1;
     char* b = h->d_job;
     BatchJob* dj = reinterpret_cast<BatchJob*>(b);
     int32_t* dorder = reinterpret_cast<int32_t*>(b + kSoloJobAligned);
@@ -1808,8 +1966,12 @@ int32_t solve_one_workgroup(lp_handle* h, size_t lds_need) {
     HIP_TRY(h, hipMemcpyAsync(dorder, &first, sizeof(first), hipMemcpyHostToDevice, s));
     HIP_TRY(h, hipStreamSynchronize(s));  // J and `first` are on this stack frame
     launch_batch_start(dcounter, dt0, s);
-    const int lds_cap = static_cast<int>((lds_need + 16383) / 16384 * 16384);
-    launch_batch(dj, dorder, 1, dcounter, 1, s, lds_cap);
+    if (plan.variant != SOLO_NONE) {
+        launch_solo(solo_threads(plan.variant), dj, dorder, 1, dcounter, 1, plan.lds, s);
+    } else {
+        const int lds_cap = static_cast<int>((lds_need + 16383) / 16384 * 16384);
+        launch_batch(dj, dorder, 1, dcounter, 1, s, lds_cap);
+    }
     if (int32_t rc = check_launch(h, "one-workgroup solve")) return rc;
     HIP_TRY(h, hipMemcpyAsync(h->h_sc, h->P.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
@@ -1831,8 +1993,13 @@ int32_t solve_from(lp_handle* h, const double* x0s, const double* y0s, int term_
     if (term_mode == 0 && omega0 == 0.0 && pause_k == 0 && x0s == h->d_x0 && y0s == h->d_y0 && !h->timing &&
         h->opt.small_lp_lds > 0) {
         const size_t need = small_lp_lds_bytes(P);
-        if (need <= static_cast<size_t>(h->opt.small_lp_lds) && need <= static_cast<size_t>(kSmallLpLdsMax))
-            return solve_one_workgroup(h, need);
+        const bool tiles = need <= static_cast<size_t>(h->opt.small_lp_lds) && need <= static_cast<size_t>(kSmallLpLdsMax);
+        // rows that the panel layout sums by a tree keep its loop
+        const bool trees = P.A.layout == 0 && P.A.nlong + P.AT.nlong > 0;
+        const SoloPlan plan = solo_plan(h, h->opt.small_lp_lds);
+        if (plan.whole && plan.variant != SOLO_GLOBAL && (tiles || !trees))
+            return solve_one_workgroup(h, 0, plan, tiles ? 1 : P.nred);
+        if (tiles) return solve_one_workgroup(h, need, SoloPlan{}, 1);
     }
     const auto t0 = std::chrono::steady_clock::now();
     launch_reset(P, h->opt.eps_rel, h->opt.eps_infeas, h->opt.max_iters, h->opt.eval_every, h->opt.restarts,
@@ -2283,7 +2450,7 @@ int32_t lp_solve_batch(lp_handle* const* hs, int32_t count, const lp_options* bo
             }
         }
         if (!big.empty()) {
-            if (int32_t rc = solve_block_diagonal(big, bo, small.empty() ? h0->stream : pr.s[2])) {
+            if (int32_t rc = solve_block_diagonal(big, bo, small.empty() ? h0->stream : pr.s[3])) {
                 if (!small.empty()) (void)finish_persistent(small, pr, false);
                 return rc;
             }
@@ -2332,12 +2499,12 @@ int32_t lp_solve_batch_static(lp_handle* const* hs, int32_t count, const lp_opti
         HIP_TRY(h0, static_batch_scratch(dev, &S));
         const auto t0 = std::chrono::steady_clock::now();
         hipStream_t s = h0->stream;
-        // largest LP first (ties by position: a strict order, so the sort needs no buffer)
+        // every LP's launch and the order inside it
         int32_t order[LP_STATIC_BATCH_MAX];
-        for (int32_t i = 0; i < count; ++i) order[i] = i;
-        std::sort(order, order + count, [&](int32_t a, int32_t b) {
-            return hs[a]->nnz != hs[b]->nnz ? hs[a]->nnz > hs[b]->nnz : a < b;
-        });
+        uint8_t group[LP_STATIC_BATCH_MAX];
+        const int budget = std::min(std::max(bo ? bo->small_lp_lds : h0->opt.small_lp_lds, 0), kSmallLpLdsMax);
+        BatchGroups G;
+        group_batch(hs, count, budget, order, group, &G);
         // job table through a small stack buffer, copied chunk by chunk on the stream
         constexpr int32_t kChunk = 16;
         BatchJob buf[kChunk];
@@ -2346,6 +2513,7 @@ int32_t lp_solve_batch_static(lp_handle* const* hs, int32_t count, const lp_opti
             for (int32_t j = 0; j < nb; ++j) {
                 buf[j] = make_job(hs[i + j], bo);
                 buf[j].t0 = S.t0;
+                solo_plan(hs[i + j], budget).apply(&buf[j]);
             }
             HIP_TRY(h0, hipMemcpyAsync(S.jobs + i, buf, sizeof(BatchJob) * nb, hipMemcpyHostToDevice, s));
             HIP_TRY(h0, hipStreamSynchronize(s));
@@ -2356,8 +2524,7 @@ int32_t lp_solve_batch_static(lp_handle* const* hs, int32_t count, const lp_opti
         int cus = 256;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
         const int wpc = (bo && bo->batch_wg_per_cu > 0) ? bo->batch_wg_per_cu : 3;
-        const int grid = std::min(cus * wpc, static_cast<int>(count));
-        launch_batch(S.jobs, S.order, count, S.counter, grid, s);
+        for (int g = 0; g < BG_COUNT; ++g) launch_group(G, g, S.jobs, S.order, S.counter, cus, wpc, s);
         if (int32_t rc = check_launch(h0, "allocation-free batched solve")) return rc;
         HIP_TRY(h0, hipStreamSynchronize(s));
         for (int32_t i = 0; i < count; ++i)

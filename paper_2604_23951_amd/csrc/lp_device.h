@@ -111,11 +111,27 @@ struct Mat {
     int layout;  // 0 panels, 1 row tiles
 };
 
+// The matrix of a one-workgroup solve: slices of 64 rows, each as wide as its longest row; a
+// slot holds two consecutive entries of one row (columns in the halves of a 32-bit word,
+// values side by side), slot p of lane l of slice s is entry ptr[s] + 64 p + l and belongs to
+// row row[64 s + l] (a permutation; lanes without a row hold the row count). Slots past a row's
+// end hold zeros whose column is the length of the gathered vector.
+struct Sell {
+    int slices;  // 0: not built (see solo_admits)
+    int slots;
+    const int* ptr;  // [slices + 1]
+    const int* row;  // [64 slices]
+    const unsigned* col;
+    const double* v;
+    const float* v32;  // FP32 storage form only
+};
+
 struct DevLP {
     int m, n;
     long long nnz;
     int nred;          // blocks of the fixed-grid reductions
     Mat A, AT;
+    Sell sA, sAT;
     // scaled problem data
     const double *c, *bl, *bu, *xl, *xu;
     const double *R, *C, *Ri, *Ci;
@@ -164,6 +180,11 @@ struct BatchJob {
     const double* y0;
     long long limit_ticks;  // time limit in device wall-clock ticks (0: none)
     const long long* t0;    // device wall clock at the start of the call (null: the LP's reset)
+    // one-workgroup solver: the SoloVariant, the reduction blocks whose order its evaluations
+    // keep, and the slices (slots) of A and A^T staged in LDS
+    int variant, eval_blocks;
+    int a_slices, a_slots, at_slices, at_slots;
+    int plain_stop;  // one-workgroup solver: statistics of a time-limit stop in plain index order
 };
 
 // Block maps of a block-diagonal batch: entry b of a map is (LP index, tile or block of it).
@@ -238,22 +259,49 @@ void launch_batch(const BatchJob* jobs, const int* order, int count, int* counte
                   int lds_cap = 0);
 size_t small_lp_lds_bytes(const DevLP& P);
 
+// One-workgroup solver over Sell matrices (lp_one_workgroup.h). Instances by threads and by
+// the rows and columns a thread keeps in registers.
+enum SoloVariant {
+    SOLO_NONE = -1,
+    SOLO_256 = 0,  // 256 threads, one row and one column each, matrices in LDS
+    SOLO_512,      // 512 threads, one each, matrices in LDS
+    SOLO_1024,     // 1024 threads, two columns and one row each
+    SOLO_WIDE,     // 1024 threads, four columns and two rows each
+    SOLO_WIDE32,   // 1024 threads, ten columns and five rows each (FP32 storage form)
+    SOLO_GLOBAL    // 1024 threads, every operand in global memory, gathered vectors in LDS
+};
+// Rows and columns whose operands the registers of 1024 threads hold.
+constexpr bool solo_register_dims(int m, int n, bool fp32) {
+    return (n <= 4096 && m <= 2048) || (fp32 && n <= 10240 && m <= 5120);
+}
+constexpr bool solo_sorted(int m, int n) { return n <= 2048 && m <= 1024; }
+constexpr int solo_threads(int variant) { return variant == SOLO_256 ? 256 : variant == SOLO_512 ? 512 : 1024; }
+constexpr int kSoloMaxDim = 14000;          // rows and columns: the gathered FP64 vector stays within LDS
+constexpr long long kSoloMaxNnz = 65536;
+constexpr int kSoloMaxRow = 128;            // entries of a row, summed by one thread
+constexpr int kSoloLdsMax = 152 * 1024;     // dynamic LDS of a workgroup at most
+void launch_fill_sell(const Csr& M, const Sell& S, unsigned* col, double* v, float* v32, hipStream_t s);
+int solo_lds_bytes(int m, int n, int fp32, int a_slots, int at_slots);  // of one LP with that many staged slots
+void launch_solo(int threads, const BatchJob* jobs, const int* order, int count, int* counter, int grid, int lds,
+                 hipStream_t s);
+
 // Allocation-free batched form: the job table, LP order and work counter of at most
 // kStaticBatchMax LPs live in a file-scope device array of the kernel source (one copy per
 // device, kept until the process ends). static_batch_scratch returns its device address on
 // `device`, which must be the current device; the address is looked up once per device.
 constexpr int kStaticBatchMax = 4096;
+constexpr int kBatchCounters = 8;  // work counters of a batched call (one per launch)
 struct StaticBatchScratch {
     BatchJob* jobs;  // kStaticBatchMax entries
     int* order;      // kStaticBatchMax entries
-    int* counter;    // one work counter
+    int* counter;    // kBatchCounters work counters
     long long* t0;   // device wall clock at the start of the call
 };
 hipError_t static_batch_scratch(int device, StaticBatchScratch* out);
 size_t static_batch_scratch_bytes();
-// Sets *counter = 0 and *t0 = the device wall clock, with a one-thread kernel (no memset
-// node if the caller captures the stream).
-void launch_batch_start(int* counter, long long* t0, hipStream_t s);
+// Clears kBatchCounters counters and sets *t0 to the device wall clock, with a kernel (no
+// memset node if the caller captures the stream).
+void launch_batch_start(int* counters, long long* t0, hipStream_t s);
 // One launch of a block-diagonal batch; it_or_mode is the iteration inside the bundle for
 // MULTI_PRIMAL / MULTI_DUAL and the evaluation mode for MULTI_PARTIALS / MULTI_DECIDE.
 void launch_multi(const MultiMaps& M, int kind, int it_or_mode, hipStream_t s);

@@ -18,6 +18,7 @@
 #include <math.h>
 
 #include <mutex>
+#include <type_traits>
 
 // Check word of the checked build (see lp_device.h); unused otherwise.
 __device__ unsigned int lp_check_word;
@@ -47,9 +48,33 @@ __device__ inline double clampd(double v, double lo, double hi) {
 
 __device__ inline bool finite_d(double v) { return __builtin_isfinite(v); }
 
+// The value N lanes up within a row of 16 lanes (DPP row shift).
+template <int N>
+__device__ inline double row_up(double v) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x100 | N, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, lo, 0x100 | N, 0xf, 0xf, true));
+}
+
+// Sum over a wave by halving (lane i adds lane i + 32, then 16, 8, 4, 2, 1), valid in lane 0.
+// The lanes are moved by permlane swaps and DPP row shifts: an LDS-permute shuffle costs ~130
+// cycles of latency at each of the six levels, and an evaluation forms up to 30 such sums (one
+// 50-row LP's evaluation on one workgroup: 24.8k cycles with shuffles).
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    {
+        const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+        v += __hiloint2double(hi[1], lo[1]);
+    }
+    {
+        const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+        v += __hiloint2double(hi[1], lo[1]);
+    }
+    v += row_up<8>(v);
+    v += row_up<4>(v);
+    v += row_up<2>(v);
+    v += row_up<1>(v);
     return v;
 }
 
@@ -505,9 +530,16 @@ struct EpiStore {
     __device__ void finish(int r, double s, const Pre&) const { out[r] = s; }
 };
 
+// The fused updates. Each epilogue splits into set_weight() (the scalars of iteration t of a restart
+// cycle, whose weight() is a division), step() (the arithmetic on one row's operands, in place, returning the value the
+// other half gathers), store() (the updated operands to memory) and record() (the residual
+// restarts' copies), so that the one-workgroup solver can keep the operands in registers
+// across iterations and run the same arithmetic.
+
 // Primal step on column j of A (row j of A^T), s = (A~^T y)_j:
 //   x_j <- clamp(x_j - tau (c~_j - s), x~lo_j, x~hi_j);  running mean of x since the restart.
 struct EpiPrimal {
+    using T = double;
     struct Pre {
         double c, lo, hi, x, xa;
     };
@@ -517,20 +549,32 @@ struct EpiPrimal {
     double *x, *xa;
     double tau, wt;
     bool first;
+    __device__ void set_weight(double step_size, double w, long long t) {
+        tau = step_size;
+        first = (t == 0);
+        wt = w;
+    }
+    __device__ static double weight(long long t) { return 1.0 / static_cast<double>(t + 1); }
     __device__ bool begin() {
         if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
-        const long long t = sc->t + it + 1;
-        tau = sc->tau;
-        first = (t == 1);
-        wt = 1.0 / static_cast<double>(t);
+        set_weight(sc->tau, weight(sc->t + it), sc->t + it);
         return true;
     }
     __device__ Pre load(int j) const { return Pre{c[j], xl[j], xu[j], x[j], xa[j]}; }
-    __device__ void finish(int j, double s, const Pre& p) const {
+    __device__ double step(Pre& p, double s) const {
         const double g = p.c - s;
         const double xn = clampd(p.x - tau * g, p.lo, p.hi);
-        x[j] = xn;
-        xa[j] = first ? xn : p.xa + wt * (xn - p.xa);
+        p.x = xn;
+        p.xa = first ? xn : p.xa + wt * (xn - p.xa);
+        return xn;
+    }
+    __device__ void store(int j, const Pre& p) const {
+        x[j] = p.x;
+        xa[j] = p.xa;
+    }
+    __device__ void finish(int j, double s, Pre p) const {
+        step(p, s);
+        store(j, p);
     }
 };
 
@@ -539,6 +583,7 @@ struct EpiPrimal {
 // (the closed-form proximal step of the row-bound term; it keeps y_i >= 0 where b_hi = +inf
 // and y_i <= 0 where b_lo = -inf), running mean of y, and A~x <- A~x+ for the next step.
 struct EpiDual {
+    using T = double;
     struct Pre {
         double y, bl, bu, ya, ax;
     };
@@ -548,24 +593,37 @@ struct EpiDual {
     double *y, *ya, *ax;
     double sigma, wt;
     bool first;
+    __device__ void set_weight(double step_size, double w, long long t) {
+        sigma = step_size;
+        first = (t == 0);
+        wt = w;
+    }
+    __device__ static double weight(long long t) { return 1.0 / static_cast<double>(t + 1); }
     __device__ bool begin() {
         if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
-        const long long t = sc->t + it + 1;
-        sigma = sc->sigma;
-        first = (t == 1);
-        wt = 1.0 / static_cast<double>(t);
+        set_weight(sc->sigma, weight(sc->t + it), sc->t + it);
         return true;
     }
     __device__ Pre load(int i) const { return Pre{y[i], bl[i], bu[i], ya[i], ax[i]}; }
-    __device__ void finish(int i, double s, const Pre& p) const {
+    __device__ double step(Pre& p, double s) const {
         const double w = 2.0 * s - p.ax;
         const double v = p.y - sigma * w;
         const double lo = v + sigma * p.bl;
         const double hi = v + sigma * p.bu;
         const double yn = (lo > 0.0 ? lo : 0.0) + (hi < 0.0 ? hi : 0.0);
-        y[i] = yn;
-        ya[i] = first ? yn : p.ya + wt * (yn - p.ya);
-        ax[i] = s;
+        p.y = yn;
+        p.ya = first ? yn : p.ya + wt * (yn - p.ya);
+        p.ax = s;
+        return yn;
+    }
+    __device__ void store(int i, const Pre& p) const {
+        y[i] = p.y;
+        ya[i] = p.ya;
+        ax[i] = p.ax;
+    }
+    __device__ void finish(int i, double s, Pre p) const {
+        step(p, s);
+        store(i, p);
     }
 };
 
@@ -575,6 +633,7 @@ struct EpiDual {
 // from the master (reduced cost, shifted bounds) are recomputed in FP64 at every restart.
 // Primal step on column j: dx_j <- clamp(dx_j - tau (d_j - (A~^T dy)_j), x~lo_j - xh_j, x~hi_j - xh_j).
 struct EpiPrimal32 {
+    using T = float;
     struct Pre {
         float d, lo, hi, x, xa;
     };
@@ -584,22 +643,34 @@ struct EpiPrimal32 {
     float *x, *xa;
     float tau, wt;
     bool first;
+    __device__ void set_weight(double step_size, double w, long long t) {
+        tau = static_cast<float>(step_size);
+        first = (t == 0);
+        wt = static_cast<float>(w);
+    }
+    __device__ static double weight(long long t) { return 1.0 / static_cast<double>(t + 1); }
     __device__ bool begin() {
         if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
-        const long long t = sc->t + it + 1;
-        tau = static_cast<float>(sc->tau);
-        first = (t == 1);
-        wt = static_cast<float>(1.0 / static_cast<double>(t));
+        set_weight(sc->tau, weight(sc->t + it), sc->t + it);
         return true;
     }
     __device__ Pre load(int j) const { return Pre{d[j], lo[j], hi[j], x[j], xa[j]}; }
-    __device__ void finish(int j, float s, const Pre& p) const {
+    __device__ float step(Pre& p, float s) const {
         const float g = p.d - s;
         float xn = p.x - tau * g;
         if (xn < p.lo) xn = p.lo;
         if (xn > p.hi) xn = p.hi;
-        x[j] = xn;
-        xa[j] = first ? xn : p.xa + wt * (xn - p.xa);
+        p.x = xn;
+        p.xa = first ? xn : p.xa + wt * (xn - p.xa);
+        return xn;
+    }
+    __device__ void store(int j, const Pre& p) const {
+        x[j] = p.x;
+        xa[j] = p.xa;
+    }
+    __device__ void finish(int j, float s, Pre p) const {
+        step(p, s);
+        store(j, p);
     }
 };
 
@@ -607,6 +678,7 @@ struct EpiPrimal32 {
 // a = v + sigma (b~lo_i - (A~xh)_i), b = v + sigma (b~hi_i - (A~xh)_i), the proximal step of
 // y = yh + dy is yh + a if yh + a > 0, yh + b if yh + b < 0, and 0 otherwise.
 struct EpiDual32 {
+    using T = float;
     struct Pre {
         float y, rl, ru, yh, ya, ax;
     };
@@ -616,16 +688,19 @@ struct EpiDual32 {
     float *y, *ya, *ax;
     float sigma, wt;
     bool first;
+    __device__ void set_weight(double step_size, double w, long long t) {
+        sigma = static_cast<float>(step_size);
+        first = (t == 0);
+        wt = static_cast<float>(w);
+    }
+    __device__ static double weight(long long t) { return 1.0 / static_cast<double>(t + 1); }
     __device__ bool begin() {
         if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
-        const long long t = sc->t + it + 1;
-        sigma = static_cast<float>(sc->sigma);
-        first = (t == 1);
-        wt = static_cast<float>(1.0 / static_cast<double>(t));
+        set_weight(sc->sigma, weight(sc->t + it), sc->t + it);
         return true;
     }
     __device__ Pre load(int i) const { return Pre{y[i], rl[i], ru[i], yh[i], ya[i], ax[i]}; }
-    __device__ void finish(int i, float s, const Pre& p) const {
+    __device__ float step(Pre& p, float s) const {
         const float w = 2.0f * s - p.ax;
         const float v = p.y - sigma * w;
         const float a = v + sigma * p.rl;
@@ -634,9 +709,19 @@ struct EpiDual32 {
         if (a > -p.yh) yn = a;
         else if (b < -p.yh) yn = b;
         else yn = -p.yh;
-        y[i] = yn;
-        ya[i] = first ? yn : p.ya + wt * (yn - p.ya);
-        ax[i] = s;
+        p.y = yn;
+        p.ya = first ? yn : p.ya + wt * (yn - p.ya);
+        p.ax = s;
+        return yn;
+    }
+    __device__ void store(int i, const Pre& p) const {
+        y[i] = p.y;
+        ya[i] = p.ya;
+        ax[i] = p.ax;
+    }
+    __device__ void finish(int i, float s, Pre p) const {
+        step(p, s);
+        store(i, p);
     }
 };
 
@@ -654,8 +739,10 @@ __device__ inline bool residual_at_last(const Scalars* sc, int it) {
 // column j, s = (A~^T y)_j: x+ = clamp(x - tau (c~ - s)), x <- w ((1 + rho) x+ - rho x) +
 // (1 - w) x0, and x+ is kept in xa for the dual half and the evaluations.
 struct EpiPrimalH {
+    using T = double;
     struct Pre {
         double c, lo, hi, x, xan;
+        double xa;  // written by step()
     };
     const Scalars* sc;
     int it;
@@ -664,25 +751,45 @@ struct EpiPrimalH {
     double *rx_c, *rx_a;  // residual restarts: x - T(z)_x of the last iterate / of the anchor (or null)
     double tau, w, wa, r1, rho;
     bool rec_c, rec_a;
-    __device__ bool begin() {
-        if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
-        const long long t = sc->t + it;
-        tau = sc->tau;
-        w = static_cast<double>(t + 1) / static_cast<double>(t + 2);
+    __device__ void set_weight(double step_size, double weight_t, long long) {
+        tau = step_size;
+        w = weight_t;
         wa = 1.0 - w;
         r1 = 1.0 + rho;
-        rec_c = rx_c != nullptr && residual_at_last(sc, it);
+    }
+    __device__ static double weight(long long t) { return static_cast<double>(t + 1) / static_cast<double>(t + 2); }
+    __device__ void set_record(bool last, long long t) {
+        rec_c = rx_c != nullptr && last;
         rec_a = rx_a != nullptr && t == 0;
+    }
+    __device__ bool begin() {
+        if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
+        set_weight(sc->tau, weight(sc->t + it), sc->t + it);
+        set_record(residual_at_last(sc, it), sc->t + it);
         return true;
     }
-    __device__ Pre load(int j) const { return Pre{c[j], xl[j], xu[j], x[j], xan[j]}; }
-    __device__ void finish(int j, double s, const Pre& p) const {
+    __device__ Pre load(int j) const { return Pre{c[j], xl[j], xu[j], x[j], xan[j], 0.0}; }
+    __device__ double step(Pre& p, double s) const {
         const double g = p.c - s;
         const double xp = clampd(p.x - tau * g, p.lo, p.hi);
-        x[j] = w * (r1 * xp - rho * p.x) + wa * p.xan;
-        xa[j] = xp;
-        if (rec_c) rx_c[j] = p.x - xp;
-        if (rec_a) rx_a[j] = p.x - xp;
+        p.x = w * (r1 * xp - rho * p.x) + wa * p.xan;
+        p.xa = xp;
+        return xp;
+    }
+    __device__ void store(int j, const Pre& p) const {
+        x[j] = p.x;
+        xa[j] = p.xa;
+    }
+    // q: the operands before the step, p: after it
+    __device__ void record(int j, const Pre& q, const Pre& p, double) const {
+        if (rec_c) rx_c[j] = q.x - p.xa;
+        if (rec_a) rx_a[j] = q.x - p.xa;
+    }
+    __device__ void finish(int j, double s, const Pre& q) const {
+        Pre p = q;
+        step(p, s);
+        store(j, p);
+        record(j, q, p, s);
     }
 };
 
@@ -690,8 +797,10 @@ struct EpiPrimalH {
 // y <- w ((1 + rho) y+ - rho y) + (1 - w) y0, ya <- y+, axa <- s, and A~x of the new Halpern
 // iterate by linearity: ax <- w ((1 + rho) s - rho ax) + (1 - w) A~x0.
 struct EpiDualH {
+    using T = double;
     struct Pre {
         double y, bl, bu, ax, yan, axan;
+        double ya, axa;  // written by step()
     };
     const Scalars* sc;
     int it;
@@ -700,44 +809,67 @@ struct EpiDualH {
     double *ry_c, *rax_c, *ry_a, *rax_a;  // residual restarts: y and A~x parts of z - T(z) (or null)
     double sigma, w, wa, r1, rho;
     bool rec_c, rec_a;
-    __device__ bool begin() {
-        if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
-        const long long t = sc->t + it;
-        sigma = sc->sigma;
-        w = static_cast<double>(t + 1) / static_cast<double>(t + 2);
+    __device__ void set_weight(double step_size, double weight_t, long long) {
+        sigma = step_size;
+        w = weight_t;
         wa = 1.0 - w;
         r1 = 1.0 + rho;
-        rec_c = ry_c != nullptr && residual_at_last(sc, it);
+    }
+    __device__ static double weight(long long t) { return static_cast<double>(t + 1) / static_cast<double>(t + 2); }
+    __device__ void set_record(bool last, long long t) {
+        rec_c = ry_c != nullptr && last;
         rec_a = ry_a != nullptr && t == 0;
+    }
+    __device__ bool begin() {
+        if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
+        set_weight(sc->sigma, weight(sc->t + it), sc->t + it);
+        set_record(residual_at_last(sc, it), sc->t + it);
         return true;
     }
-    __device__ Pre load(int i) const { return Pre{y[i], bl[i], bu[i], ax[i], yan[i], axan[i]}; }
-    __device__ void finish(int i, double s, const Pre& p) const {
+    __device__ Pre load(int i) const { return Pre{y[i], bl[i], bu[i], ax[i], yan[i], axan[i], 0.0, 0.0}; }
+    __device__ double step(Pre& p, double s) const {
         const double w2 = 2.0 * s - p.ax;
         const double v = p.y - sigma * w2;
         const double lo = v + sigma * p.bl;
         const double hi = v + sigma * p.bu;
         const double yp = (lo > 0.0 ? lo : 0.0) + (hi < 0.0 ? hi : 0.0);
-        y[i] = w * (r1 * yp - rho * p.y) + wa * p.yan;
-        ya[i] = yp;
-        axa[i] = s;
-        ax[i] = w * (r1 * s - rho * p.ax) + wa * p.axan;
+        p.y = w * (r1 * yp - rho * p.y) + wa * p.yan;
+        p.ya = yp;
+        p.axa = s;
+        p.ax = w * (r1 * s - rho * p.ax) + wa * p.axan;
+        return p.y;
+    }
+    __device__ void store(int i, const Pre& p) const {
+        y[i] = p.y;
+        ya[i] = p.ya;
+        axa[i] = p.axa;
+        ax[i] = p.ax;
+    }
+    __device__ void record(int i, const Pre& q, const Pre& p, double s) const {
         if (rec_c) {
-            ry_c[i] = p.y - yp;
-            rax_c[i] = p.ax - s;
+            ry_c[i] = q.y - p.ya;
+            rax_c[i] = q.ax - s;
         }
         if (rec_a) {
-            ry_a[i] = p.y - yp;
-            rax_a[i] = p.ax - s;
+            ry_a[i] = q.y - p.ya;
+            rax_a[i] = q.ax - s;
         }
+    }
+    __device__ void finish(int i, double s, const Pre& q) const {
+        Pre p = q;
+        step(p, s);
+        store(i, p);
+        record(i, q, p, s);
     }
 };
 
 // Halpern form in the FP32 storage form: the anchor is the FP64 master point, so in correction
 // space it is zero and the update is dz <- w ((1 + rho) T(dz) - rho dz).
 struct EpiPrimal32H {
+    using T = float;
     struct Pre {
         float d, lo, hi, x;
+        float xa;  // written by step()
     };
     const Scalars* sc;
     int it;
@@ -746,32 +878,53 @@ struct EpiPrimal32H {
     double *rx_c, *rx_a;  // residual restarts (FP64 copies of the FP32 differences, or null)
     float tau, w, r1, rho;
     bool rec_c, rec_a;
+    __device__ void set_weight(double step_size, double weight_t, long long) {
+        tau = static_cast<float>(step_size);
+        w = static_cast<float>(weight_t);
+        r1 = 1.0f + rho;
+    }
+    __device__ static double weight(long long t) { return static_cast<double>(t + 1) / static_cast<double>(t + 2); }
+    __device__ void set_record(bool last, long long t) {
+        rec_c = rx_c != nullptr && last;
+        rec_a = rx_a != nullptr && t == 0;
+    }
     __device__ bool begin() {
         if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
-        const long long t = sc->t + it;
-        tau = static_cast<float>(sc->tau);
-        w = static_cast<float>(static_cast<double>(t + 1) / static_cast<double>(t + 2));
-        r1 = 1.0f + rho;
-        rec_c = rx_c != nullptr && residual_at_last(sc, it);
-        rec_a = rx_a != nullptr && t == 0;
+        set_weight(sc->tau, weight(sc->t + it), sc->t + it);
+        set_record(residual_at_last(sc, it), sc->t + it);
         return true;
     }
-    __device__ Pre load(int j) const { return Pre{d[j], lo[j], hi[j], x[j]}; }
-    __device__ void finish(int j, float s, const Pre& p) const {
+    __device__ Pre load(int j) const { return Pre{d[j], lo[j], hi[j], x[j], 0.0f}; }
+    __device__ float step(Pre& p, float s) const {
         const float g = p.d - s;
         float xp = p.x - tau * g;
         if (xp < p.lo) xp = p.lo;
         if (xp > p.hi) xp = p.hi;
-        x[j] = w * (r1 * xp - rho * p.x);
-        xa[j] = xp;
-        if (rec_c) rx_c[j] = static_cast<double>(p.x) - static_cast<double>(xp);
-        if (rec_a) rx_a[j] = static_cast<double>(p.x) - static_cast<double>(xp);
+        p.x = w * (r1 * xp - rho * p.x);
+        p.xa = xp;
+        return xp;
+    }
+    __device__ void store(int j, const Pre& p) const {
+        x[j] = p.x;
+        xa[j] = p.xa;
+    }
+    __device__ void record(int j, const Pre& q, const Pre& p, float) const {
+        if (rec_c) rx_c[j] = static_cast<double>(q.x) - static_cast<double>(p.xa);
+        if (rec_a) rx_a[j] = static_cast<double>(q.x) - static_cast<double>(p.xa);
+    }
+    __device__ void finish(int j, float s, const Pre& q) const {
+        Pre p = q;
+        step(p, s);
+        store(j, p);
+        record(j, q, p, s);
     }
 };
 
 struct EpiDual32H {
+    using T = float;
     struct Pre {
         float y, rl, ru, yh, ax;
+        float ya;  // written by step()
     };
     const Scalars* sc;
     int it;
@@ -780,18 +933,24 @@ struct EpiDual32H {
     double *ry_c, *rax_c, *ry_a, *rax_a;  // residual restarts (FP64 copies, or null)
     float sigma, w, r1, rho;
     bool rec_c, rec_a;
+    __device__ void set_weight(double step_size, double weight_t, long long) {
+        sigma = static_cast<float>(step_size);
+        w = static_cast<float>(weight_t);
+        r1 = 1.0f + rho;
+    }
+    __device__ static double weight(long long t) { return static_cast<double>(t + 1) / static_cast<double>(t + 2); }
+    __device__ void set_record(bool last, long long t) {
+        rec_c = ry_c != nullptr && last;
+        rec_a = ry_a != nullptr && t == 0;
+    }
     __device__ bool begin() {
         if (sc->status != kRunning || sc->k + it >= sc->max_iters) return false;
-        const long long t = sc->t + it;
-        sigma = static_cast<float>(sc->sigma);
-        w = static_cast<float>(static_cast<double>(t + 1) / static_cast<double>(t + 2));
-        r1 = 1.0f + rho;
-        rec_c = ry_c != nullptr && residual_at_last(sc, it);
-        rec_a = ry_a != nullptr && t == 0;
+        set_weight(sc->sigma, weight(sc->t + it), sc->t + it);
+        set_record(residual_at_last(sc, it), sc->t + it);
         return true;
     }
-    __device__ Pre load(int i) const { return Pre{y[i], rl[i], ru[i], yh[i], ax[i]}; }
-    __device__ void finish(int i, float s, const Pre& p) const {
+    __device__ Pre load(int i) const { return Pre{y[i], rl[i], ru[i], yh[i], ax[i], 0.0f}; }
+    __device__ float step(Pre& p, float s) const {
         const float w2 = 2.0f * s - p.ax;
         const float v = p.y - sigma * w2;
         const float a = v + sigma * p.rl;
@@ -800,17 +959,31 @@ struct EpiDual32H {
         if (a > -p.yh) yp = a;
         else if (b < -p.yh) yp = b;
         else yp = -p.yh;
-        y[i] = w * (r1 * yp - rho * p.y);
-        ya[i] = yp;
-        ax[i] = w * (r1 * s - rho * p.ax);
+        p.y = w * (r1 * yp - rho * p.y);
+        p.ya = yp;
+        p.ax = w * (r1 * s - rho * p.ax);
+        return p.y;
+    }
+    __device__ void store(int i, const Pre& p) const {
+        y[i] = p.y;
+        ya[i] = p.ya;
+        ax[i] = p.ax;
+    }
+    __device__ void record(int i, const Pre& q, const Pre& p, float s) const {
         if (rec_c) {
-            ry_c[i] = static_cast<double>(p.y) - static_cast<double>(yp);
-            rax_c[i] = static_cast<double>(p.ax) - static_cast<double>(s);
+            ry_c[i] = static_cast<double>(q.y) - static_cast<double>(p.ya);
+            rax_c[i] = static_cast<double>(q.ax) - static_cast<double>(s);
         }
         if (rec_a) {
-            ry_a[i] = static_cast<double>(p.y) - static_cast<double>(yp);
-            rax_a[i] = static_cast<double>(p.ax) - static_cast<double>(s);
+            ry_a[i] = static_cast<double>(q.y) - static_cast<double>(p.ya);
+            rax_a[i] = static_cast<double>(q.ax) - static_cast<double>(s);
         }
+    }
+    __device__ void finish(int i, float s, const Pre& q) const {
+        Pre p = q;
+        step(p, s);
+        store(i, p);
+        record(i, q, p, s);
     }
 };
 
@@ -1801,6 +1974,29 @@ __global__ void to_float_kernel(const double* src, float* dst, long long n) {
 }
 
 
+// Fills a Sell matrix from the (scaled) CSR: one thread per lane of the slices.
+__global__ void fill_sell_kernel(Csr M, Sell S, unsigned* col, double* v, float* v32) {
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= S.slices * 64) return;
+    const int sl = r >> 6, lane = r & 63;
+    const int base = S.ptr[sl], width = (S.ptr[sl + 1] - base) >> 6, row = S.row[r];
+    const int e0 = row < M.rows ? M.rp[row] : 0, e1 = row < M.rows ? M.rp[row + 1] : 0;
+    const unsigned zero = static_cast<unsigned>(M.cols);
+    for (int p = 0; p < width; ++p) {
+        const long long o = base + 64LL * p + lane;
+        const int e = e0 + 2 * p;
+        const bool h0 = e < e1, h1 = e + 1 < e1;
+        col[o] = (h0 ? static_cast<unsigned>(M.ci[e]) : zero) | ((h1 ? static_cast<unsigned>(M.ci[e + 1]) : zero) << 16);
+        const double a0 = h0 ? M.v[e] : 0.0, a1 = h1 ? M.v[e + 1] : 0.0;
+        v[2 * o] = a0;
+        v[2 * o + 1] = a1;
+        if (v32) {
+            v32[2 * o] = static_cast<float>(a0);
+            v32[2 * o + 1] = static_cast<float>(a1);
+        }
+    }
+}
+
 // ------------------------------------------------------------------ batched form
 
 // Sparse product by one workgroup: every row tile of M in turn.
@@ -1858,6 +2054,32 @@ __device__ void wg_kkt(const DevLP& P, int mode, double* tot, double* red16) {
     __syncthreads();
 }
 
+// The scalar state at the start of a batched or one-workgroup solve.
+__device__ inline void reset_scalars(Scalars* sc, const BatchJob& J) {
+    sc->omega = sc->omega0;
+    sc->tau = sc->eta / sc->omega;
+    sc->sigma = sc->eta * sc->omega;
+    sc->eps_rel = J.eps_rel;
+    sc->eps_infeas = J.eps_infeas;
+    sc->max_iters = J.max_iters;
+    sc->eval_every = J.eval_every;
+    sc->restarts_on = J.restarts_on;
+    sc->trace_cap = J.trace_cap;
+    sc->k = 0;
+    sc->t = 0;
+    sc->restarts = 0;
+    sc->n_trace = 0;
+    sc->status = kRunning;
+    sc->out_avg = 0;
+    sc->last_restart = 0;
+    sc->kkt_prev = __builtin_inf();
+    sc->pid_int = 0.0;
+    sc->pid_prev = 0.0;
+    sc->term_mode = 0;
+    sc->ray_src = 0;
+    sc->deadline = J.limit_ticks > 0 ? (J.t0 ? *J.t0 : static_cast<long long>(wall_clock64())) + J.limit_ticks : 0;
+}
+
 // One LP solved by one workgroup: the same restarted, averaged PDHG as the multi-kernel
 // path (same kernels' epilogues, evaluation and decision logic), with the scalar state in
 // LDS and a workgroup barrier between the phases.
@@ -1866,30 +2088,7 @@ __device__ void wg_solve(const DevLP& P, const BatchJob& J, Scalars* ssc, double
     const int tid = threadIdx.x;
     if (tid == 0) {
         *ssc = *P.sc;
-        ssc->omega = ssc->omega0;
-        ssc->tau = ssc->eta / ssc->omega;
-        ssc->sigma = ssc->eta * ssc->omega;
-        ssc->eps_rel = J.eps_rel;
-        ssc->eps_infeas = J.eps_infeas;
-        ssc->max_iters = J.max_iters;
-        ssc->eval_every = J.eval_every;
-        ssc->restarts_on = J.restarts_on;
-        ssc->trace_cap = J.trace_cap;
-        ssc->k = 0;
-        ssc->t = 0;
-        ssc->restarts = 0;
-        ssc->n_trace = 0;
-        ssc->status = kRunning;
-        ssc->out_avg = 0;
-        ssc->last_restart = 0;
-        ssc->kkt_prev = __builtin_inf();
-        ssc->pid_int = 0.0;
-        ssc->pid_prev = 0.0;
-        ssc->term_mode = 0;
-        ssc->ray_src = 0;
-        ssc->deadline = J.limit_ticks > 0
-                            ? (J.t0 ? *J.t0 : static_cast<long long>(wall_clock64())) + J.limit_ticks
-                            : 0;
+        reset_scalars(ssc, J);
     }
     __syncthreads();
     const int mx = P.m > P.n ? P.m : P.n;
@@ -2110,6 +2309,8 @@ __global__ __launch_bounds__(kBlock) void batch_kernel(const BatchJob* jobs, con
 }
 
 
+#include "lp_one_workgroup.h"
+
 // ------------------------------------------------ block-diagonal batch (many LPs per launch)
 // One launch covers the row tiles (or reduction blocks, or vector blocks) of every LP of a
 // batch; map[b] = (LP, tile-or-block of that LP). Each LP keeps its own scalars, so every
@@ -2200,30 +2401,7 @@ __global__ __launch_bounds__(kBlock) void multi_elem_kernel(const BatchJob* jobs
 __global__ void multi_reset_kernel(const BatchJob* jobs, int count) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= count) return;
-    const BatchJob& J = jobs[i];
-    Scalars* sc = J.P.sc;
-    sc->omega = sc->omega0;
-    sc->tau = sc->eta / sc->omega;
-    sc->sigma = sc->eta * sc->omega;
-    sc->eps_rel = J.eps_rel;
-    sc->eps_infeas = J.eps_infeas;
-    sc->max_iters = J.max_iters;
-    sc->eval_every = J.eval_every;
-    sc->restarts_on = J.restarts_on;
-    sc->trace_cap = J.trace_cap;
-    sc->k = 0;
-    sc->t = 0;
-    sc->restarts = 0;
-    sc->n_trace = 0;
-    sc->status = kRunning;
-    sc->out_avg = 0;
-    sc->last_restart = 0;
-    sc->kkt_prev = __builtin_inf();
-    sc->pid_int = 0.0;
-    sc->pid_prev = 0.0;
-    sc->term_mode = 0;
-    sc->ray_src = 0;
-    sc->deadline = J.limit_ticks > 0 ? (J.t0 ? *J.t0 : static_cast<long long>(wall_clock64())) + J.limit_ticks : 0;
+    reset_scalars(jobs[i].P.sc, jobs[i]);
 }
 
 __global__ void multi_status_kernel(const BatchJob* jobs, int count, int* status) {
@@ -2522,6 +2700,35 @@ void launch_batch(const BatchJob* jobs, const int* order, int count, int* counte
                        counter, lds_cap);
 }
 
+void launch_fill_sell(const Csr& M, const Sell& S, unsigned* col, double* v, float* v32, hipStream_t s) {
+    if (S.slices <= 0) return;
+    hipLaunchKernelGGL(fill_sell_kernel, dim3(grid_for(64LL * S.slices)), dim3(kBlock), 0, s, M, S, col, v, v32);
+}
+
+int solo_lds_bytes(int m, int n, int fp32, int a_slots, int at_slots) {
+    return solo_lds_layout(m, n, fp32, a_slots, at_slots).end;
+}
+
+namespace {
+template <int NT>
+void launch_solo_nt(const BatchJob* jobs, const int* order, int count, int* counter, int grid, int lds, hipStream_t s) {
+    static const bool attr = [] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&solo_kernel<NT>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, kSoloLdsMax) == hipSuccess;
+    }();
+    (void)attr;
+    hipLaunchKernelGGL(solo_kernel<NT>, dim3(grid), dim3(NT), static_cast<size_t>(lds), s, jobs, order, count, counter);
+}
+}  // namespace
+
+void launch_solo(int threads, const BatchJob* jobs, const int* order, int count, int* counter, int grid, int lds,
+                 hipStream_t s) {
+    if (count <= 0 || grid <= 0) return;
+    if (threads == 256) launch_solo_nt<256>(jobs, order, count, counter, grid, lds, s);
+    else if (threads == 512) launch_solo_nt<512>(jobs, order, count, counter, grid, lds, s);
+    else launch_solo_nt<1024>(jobs, order, count, counter, grid, lds, s);
+}
+
 size_t small_lp_lds_bytes(const DevLP& P) { return carve_small_lp(P, nullptr, nullptr); }
 
 // ------------------------------------------------------ allocation-free batched form
@@ -2538,11 +2745,9 @@ constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 char* g_scratch_addr[kMaxDevices] = {};
 
-__global__ void batch_start_kernel(int* counter, long long* t0) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        *counter = 0;
-        *t0 = static_cast<long long>(wall_clock64());
-    }
+__global__ void batch_start_kernel(int* counters, long long* t0) {
+    if (threadIdx.x < kBatchCounters) counters[threadIdx.x] = 0;
+    if (threadIdx.x == 0) *t0 = static_cast<long long>(wall_clock64());
 }
 }  // namespace
 
@@ -2566,8 +2771,8 @@ hipError_t static_batch_scratch(int device, StaticBatchScratch* out) {
 
 size_t static_batch_scratch_bytes() { return kStaticScratchBytes; }
 
-void launch_batch_start(int* counter, long long* t0, hipStream_t s) {
-    hipLaunchKernelGGL(batch_start_kernel, dim3(1), dim3(64), 0, s, counter, t0);
+void launch_batch_start(int* counters, long long* t0, hipStream_t s) {
+    hipLaunchKernelGGL(batch_start_kernel, dim3(1), dim3(64), 0, s, counters, t0);
 }
 
 void launch_to_float(const double* src, float* dst, long long n, hipStream_t s) {
