@@ -259,6 +259,20 @@ namespace {
 
 int32_t materialize(lp_handle* h);
 
+// How the one-workgroup solver runs an LP: its instance, the slices of A and A^T staged in
+// LDS, and the LDS it needs. `whole`: all of the LP's arrays there fit the budget.
+struct SoloPlan {
+    int variant = SOLO_NONE, a_slices = 0, at_slices = 0, a_slots = 0, at_slots = 0, lds = 0;
+    bool whole = false;
+    void apply(BatchJob* J) const {
+        J->variant = variant;
+        J->a_slices = a_slices;
+        J->a_slots = a_slots;
+        J->at_slices = at_slices;
+        J->at_slots = at_slots;
+    }
+};
+
 int32_t fail(lp_handle* h, int32_t code, const std::string& msg) {
     if (h) h->err = msg;
     g_last_error = msg;
@@ -424,37 +438,29 @@ BatchJob make_job(lp_handle* h, const lp_options* bo) {
     return J;
 }
 
-// How the one-workgroup solver runs an LP: its instance, the slices of A and A^T staged in
-// LDS, and the LDS it needs. `whole`: all of the LP's arrays there fit the budget.
-struct SoloPlan {
-    int variant = SOLO_NONE, a_slices = 0, at_slices = 0, a_slots = 0, at_slots = 0, lds = 0;
-    bool whole = false;
-    void apply(BatchJob* J) const {
-        J->variant = variant;
-        J->a_slices = a_slices;
-        J->a_slots = a_slots;
-        J->at_slices = at_slices;
-        J->at_slots = at_slots;
-    }
-};
-
 // An LP with at most one row and one column per thread takes the fewest threads that give it
 // that (fewer waves meet at each barrier, and several such workgroups share a CU) when all of
 // it fits the LDS budget; the wider ones stage the slices that fit, those of A (the longer
 // rows of the two in most LPs, summed by fewer threads) first. Operands that no longer fit the
 // registers of 1024 threads stay in global memory.
-SoloPlan solo_plan(const lp_handle* h, int budget) {
+SoloPlan solo_stage_plan(const lp_handle* h, int budget, bool fp32) {
     SoloPlan S;
     if (h->sell_a.empty()) return S;
-    const int m = h->m, n = h->n, fp32 = h->opt.precision == LP_PREC_FP32_REFINED;
     const int na = static_cast<int>(h->sell_a.size()) - 1, nat = static_cast<int>(h->sell_at.size()) - 1;
-    auto bytes = [&](int a, int at) { return solo_lds_bytes(m, n, fp32, h->sell_a[a], h->sell_at[at]); };
+    auto bytes = [&](int a, int at) { return solo_lds_bytes(h->m, h->n, fp32, h->sell_a[a], h->sell_at[at]); };
     while (S.a_slices < na && bytes(S.a_slices + 1, 0) <= budget) S.a_slices++;
     while (S.at_slices < nat && bytes(S.a_slices, S.at_slices + 1) <= budget) S.at_slices++;
     S.a_slots = h->sell_a[S.a_slices];
     S.at_slots = h->sell_at[S.at_slices];
     S.lds = bytes(S.a_slices, S.at_slices);
     S.whole = S.a_slices == na && S.at_slices == nat;
+    return S;
+}
+
+SoloPlan solo_plan(const lp_handle* h, int budget) {
+    const int m = h->m, n = h->n, fp32 = h->opt.precision == LP_PREC_FP32_REFINED;
+    SoloPlan S = solo_stage_plan(h, budget, fp32);
+    if (h->sell_a.empty()) return S;
     const int mx = std::max(m, n);
     if (S.whole && mx <= 512) S.variant = mx <= 256 ? SOLO_256 : SOLO_512;
     else if (solo_sorted(m, n)) S.variant = SOLO_1024;
@@ -1281,7 +1287,16 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     // chunks of pow_iters steps until a chunk's last step raises the estimate by at most
     // 1e-8 of it (it approaches ||A~||_2 from below and eta = 0.998 / estimate must keep
     // eta ||A~||_2 < 1), at most 25 chunks
-    if (!(o.step_size > 0.0)) {
+    // An LP with the one-workgroup form whose rows the product layout sums in order runs the same
+    // iteration in one launch, up to the size where its matrices come mostly from the L2 and
+    // one CU's bandwidth costs more than the launches (lp_create, four launches per step / one
+    // launch: 200 x 400 2.6 / 0.83 ms, 11,646 entries 3.6 / 1.4, 34,511 11.1 / 8.6, 56,839 8.2 / 9.1).
+    const SoloPlan power = sell && nnz <= kSoloPowerNnz ? solo_stage_plan(h, kSoloLdsMax, false) : SoloPlan{};
+    const bool ordered = P.A.layout == 1 || P.A.nlong + P.AT.nlong == 0;
+    if (!(o.step_size > 0.0) && ordered && power.lds > 0 && power.lds <= kSoloLdsMax) {
+        launch_solo_power(P, SoloStage{power.a_slices, power.a_slots, power.at_slices, power.at_slots}, power.lds, o.seed,
+                          o.pow_iters, 25, s);
+    } else if (!(o.step_size > 0.0)) {
         launch_power_start(P, o.seed, P.x, s);
         for (int chunk = 0; chunk < 25; ++chunk) {
             launch_power_steps(P, o.pow_iters, P.x, P.ax, P.aty, s);

@@ -282,6 +282,15 @@ constexpr int kSoloMaxRow = 128;            // entries of a row, summed by one t
 constexpr int kSoloLdsMax = 152 * 1024;     // dynamic LDS of a workgroup at most
 void launch_fill_sell(const Csr& M, const Sell& S, unsigned* col, double* v, float* v32, hipStream_t s);
 int solo_lds_bytes(int m, int n, int fp32, int a_slots, int at_slots);  // of one LP with that many staged slots
+// The power iteration of launch_power_start / launch_power_steps (chunks of iters steps, the
+// chunk test included) of an LP with Sell matrices in one launch; `G` are the slices of the two
+// matrices staged in LDS and lds the bytes that takes.
+constexpr long long kSoloPowerNnz = 45000;
+struct SoloStage {
+    int a_slices, a_slots, at_slices, at_slots;
+};
+void launch_solo_power(const DevLP& P, const SoloStage& G, int lds, unsigned long long seed, int iters, int chunks,
+                       hipStream_t s);
 void launch_solo(int threads, const BatchJob* jobs, const int* order, int count, int* counter, int grid, int lds,
                  hipStream_t s);
 

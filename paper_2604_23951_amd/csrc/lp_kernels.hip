@@ -2721,6 +2721,16 @@ void launch_solo_nt(const BatchJob* jobs, const int* order, int count, int* coun
 }
 }  // namespace
 
+void launch_solo_power(const DevLP& P, const SoloStage& G, int lds, unsigned long long seed, int iters, int chunks,
+                       hipStream_t s) {
+    static const bool attr = [] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&solo_power_kernel),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, kSoloLdsMax) == hipSuccess;
+    }();
+    (void)attr;
+    hipLaunchKernelGGL(solo_power_kernel, dim3(1), dim3(1024), static_cast<size_t>(lds), s, P, G, seed, iters, chunks);
+}
+
 void launch_solo(int threads, const BatchJob* jobs, const int* order, int count, int* counter, int grid, int lds,
                  hipStream_t s) {
     if (count <= 0 || grid <= 0) return;

@@ -604,3 +604,101 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void solo_kernel(const Batc
         }
     }
 }
+
+// ------------------------------------------------------------- norm estimate of a small LP
+// The whole power iteration of an LP with Sell matrices in one workgroup: the vectors in LDS,
+// the matrices staged there as far as they fit, the products summed as in solo_product, the
+// norms in the order of sumsq2_kernel and normalize_kernel (nred blocks of kBlock threads,
+// then a wave's halving sum), the chunk test of the set-up on the device: the same estimate
+// bit for bit. What bounds it is latency, as above; the kernel-per-phase loop pays four
+// launches per step (17 us) and a host round trip per chunk.
+struct SoloPowerShared {
+    double red[1024 / 64], part[kSoloEvalBlocks], total, sigma, prev;
+};
+
+// Sum of squares of a[0, count) in LDS; every thread gets it. Ends with a barrier.
+__device__ __forceinline__ double solo_sumsq(const double* a, int count, int nred, SoloPowerShared& S) {
+    const int group = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kBlock);
+    const int vt = threadIdx.x % kBlock, lane = threadIdx.x & 63;
+    constexpr int kGroups = 1024 / kBlock;
+    for (int b0 = 0; b0 < nred; b0 += kGroups) {
+        double v = 0.0;
+        if (b0 + group < nred)
+            for (int i = (b0 + group) * kBlock + vt; i < count; i += nred * kBlock) v += a[i] * a[i];
+        v = wave_sum(v);
+        if (lane == 0) S.red[threadIdx.x >> 6] = v;
+        __syncthreads();
+        if (vt == 0 && b0 + group < nred) {
+            double t = 0.0;
+            for (int k = 0; k < kBlock / 64; ++k) t += S.red[group * (kBlock / 64) + k];
+            S.part[b0 + group] = t;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x < 64) {
+        const double v = wave_sum(lane < nred ? S.part[lane] : 0.0);
+        if (lane == 0) S.total = v;
+    }
+    __syncthreads();
+    return S.total;
+}
+
+__global__ __launch_bounds__(1024) void solo_power_kernel(DevLP P, SoloStage G, unsigned long long seed, int iters,
+                                                          int chunks) {
+    extern __shared__ __align__(16) char solo_lds[];
+    __shared__ SoloPowerShared S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = P.m, n = P.n;
+    const SoloLds L = solo_lds_layout(m, n, 0, G.a_slots, G.at_slots);
+    double* u = reinterpret_cast<double*>(solo_lds);
+    double* v = reinterpret_cast<double*>(solo_lds + L.xs);
+    const SellAt A{P.sA.col, P.sA.v, L.a_col, L.a_val, G.a_slices, n + 1};
+    const SellAt AT{P.sAT.col, P.sAT.v, L.at_col, L.at_val, G.at_slices, m + 1};
+    solo_stage<1024>(solo_lds + L.a_col, P.sA.col, 4 * G.a_slots);
+    solo_stage<1024>(solo_lds + L.a_val, P.sA.v, 16 * G.a_slots);
+    solo_stage<1024>(solo_lds + L.at_col, P.sAT.col, 4 * G.at_slots);
+    solo_stage<1024>(solo_lds + L.at_val, P.sAT.v, 16 * G.at_slots);
+    for (int k = tid; k < n; k += 1024) v[k] = splitmix_centered(seed, static_cast<unsigned long long>(k));
+    if (tid == 0) {
+        u[m] = 0.0;
+        v[n] = 0.0;
+        S.sigma = S.prev = 0.0;
+    }
+    __syncthreads();
+    const double start = sqrt(solo_sumsq(v, n, P.nred, S));
+    if (start > 0.0)
+        for (int k = tid; k < n; k += 1024) v[k] = v[k] / start;
+    __syncthreads();
+    auto product = [&](const Sell& M, const SellAt& at, int rows, const double* gat, double* out) {
+        for (int sl = wave; sl < M.slices; sl += 1024 / 64) {
+            const int base = M.ptr[sl], width = (M.ptr[sl + 1] - base) >> 6, r = M.row[sl * 64 + lane];
+            const double s = sell_row<double>(0.0, sl, base + lane, width, at, solo_lds, gat);
+            if (r < rows) out[r] = s;
+        }
+        __syncthreads();
+    };
+    // Each step: u = A v, sigma = ||u||, v = A^T u / ||A^T u||. A^T u replaces v as it is formed
+    // (v is not read again); when its norm is not positive v would stay and every later step
+    // repeat this one, so the iteration ends there.
+    bool ended = false;
+    for (int c = 0; c < chunks && !ended; ++c) {
+        for (int it = 0; it < iters && !ended; ++it) {
+            product(P.sA, A, m, v, u);
+            const double su = solo_sumsq(u, m, P.nred, S);
+            if (tid == 0) {
+                S.prev = S.sigma;
+                S.sigma = sqrt(su);
+            }
+            product(P.sAT, AT, n, u, v);
+            const double nrm = sqrt(solo_sumsq(v, n, P.nred, S));
+            ended = !(nrm > 0.0);
+            if (!ended)
+                for (int i = tid; i < n; i += 1024) v[i] = v[i] / nrm;
+            __syncthreads();
+        }
+        if (S.sigma - S.prev <= 1e-8 * S.sigma) ended = true;
+    }
+    if (tid == 0) {
+        P.sc->sigma_max = S.sigma;
+        P.sc->sigma_prev = S.prev;
+    }
+}

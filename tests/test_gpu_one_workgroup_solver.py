@@ -116,3 +116,23 @@ def test_time_limited_objectives_are_the_plain_sums(oracle_lib, method):
         assert sol.status == "time_limit" and sol.info.solve_path == 1
         chk = oracle.kkt(lp, sol.x, sol.y)
         assert (sol.info.primal_obj, sol.info.dual_obj) == (chk["pobj"], chk["dobj"])
+
+
+@pytest.mark.parametrize("shape", [s for s in SHAPES + WIDE if s[1] >= 129] + [(4000, 6000, 20)], ids=lambda s: f"{s[0]}x{s[1]}r{s[2]}")
+def test_norm_estimate_equals_the_launch_per_step_iteration(shape):
+    """||A~|| from one launch (every row at most 128 entries) against the same LP with one more row
+    of 129 explicit zeros, which keeps the launches per step: the zeros change no sum."""
+    lp = _lp(*shape)
+    rows = np.repeat(np.arange(lp.m), np.diff(lp.row_ptr))
+    keys = np.concatenate([rows.astype(np.int64) * lp.n + lp.col_idx, lp.m * np.int64(lp.n) + np.arange(129)])
+    rp, ci, v = synth.csr_from_keys(keys, lp.m + 1, lp.n, np.concatenate([lp.vals, np.zeros(129)]))
+    inf = np.inf
+    big = synth.LP(lp.m + 1, lp.n, rp, ci, v, lp.c, np.append(lp.b_lo, -inf), np.append(lp.b_hi, inf), lp.x_lo, lp.x_hi)
+    sigma = []
+    for p in (lp, big):
+        with lpg.Solver(p, spmv_layout=1, max_iters=0) as s:
+            sigma.append(s.solve().info.sigma_max)
+    if (max(lp.m, lp.n) + 1023) // 1024 == (max(lp.m + 1, lp.n) + 1023) // 1024:
+        assert sigma[0] == sigma[1]
+    else:
+        assert abs(sigma[0] - sigma[1]) <= 1e-12 * sigma[1]
