@@ -46,8 +46,8 @@ struct Arena {
 };
 
 // Row tiles for the LDS-staged SpMV: consecutive rows while the tile holds at most tn
-// nonzeros and tn / 4 rows; a row longer than tn is a tile of its own.
-std::vector<int32_t> build_tiles(int32_t rows, const int32_t* rp, int32_t tn, int64_t* n_long) {
+// nonzeros and tn / 4 rows; a row longer than `longest` (<= tn) is a tile of its own.
+std::vector<int32_t> build_tiles(int32_t rows, const int32_t* rp, int32_t tn, int32_t longest, int64_t* n_long) {
     const int32_t tile_rows = tn / 4;
     std::vector<int32_t> t;
     t.reserve(static_cast<size_t>(rows) / 64 + 2);
@@ -57,14 +57,14 @@ std::vector<int32_t> build_tiles(int32_t rows, const int32_t* rp, int32_t tn, in
     while (r < rows) {
         const int32_t start = r;
         const int64_t len = rp[r + 1] - rp[r];
-        if (len > tn) {
+        if (len > longest) {
             ++r;
             ++nl;
         } else {
             int64_t nz = 0;
             while (r < rows && r - start < tile_rows) {
                 const int64_t l = rp[r + 1] - rp[r];
-                if (l > tn || nz + l > tn) break;
+                if (l > longest || nz + l > tn) break;
                 nz += l;
                 ++r;
             }
@@ -73,6 +73,41 @@ std::vector<int32_t> build_tiles(int32_t rows, const int32_t* rp, int32_t tn, in
     }
     *n_long = nl;
     return t;
+}
+
+// Panel layout: a matrix whose gathered vector fits one XCD's 4 MB L2 is swept as row tiles
+// unless a panel width was asked for. The gathers hit the L2 in any order then, and the panel
+// units (a few hundred entries per wave and step, a barrier after each, ~20 us however small
+// the matrix) only cost latency. us per iteration, Halpern form, panels / row tiles: 32k
+// entries 11.8 / 7.8, dense rows with 993k (FP64) 57 / 17, power-law columns with 1.2M 48 / 38
+// (FP32 39 / 29), 2.4M 72 / 63 (62 / 50); beyond, x at 6.4 MB: 111 / 114, y at 6.4 MB: 190 / 219.
+constexpr int64_t kFlatBytes = int64_t(4) << 20;
+
+// Row tiles of one LP's own launches (the shape the tuned table gives is for many LPs per
+// launch): a launch of few tiles is bound by one tile's chain of loads, row sums and
+// stores, which grows with the tile, and a launch of many by their number, so the largest
+// shape that still gives nearly every CU a tile (us per iteration with tiles of 1024 / 2048 /
+// 4096, FP64: 32k entries 7.9 / 9.6 / 13.0, 231k 9.2 / 11.1 / 15.2, 993k 23.3 / 20.7 / 19.3). tree_len: rows longer than this are the ones
+// the layout reduces by a workgroup; all others must fit a tile to be summed in order.
+struct FlatTiles {
+    std::vector<int32_t> tiles;
+    int shape = 0, tree_len = 0;
+};
+
+FlatTiles flat_tiles(int32_t rows, const int32_t* rp, int32_t tree_len, int cus) {
+    FlatTiles F;
+    int32_t longest = 0;
+    for (int32_t r = 0; r < rows; ++r)
+        if (rp[r + 1] - rp[r] <= tree_len) longest = std::max(longest, rp[r + 1] - rp[r]);
+    F.shape = kTileShapes - 1;
+    while (F.shape > 0 && longest <= tile_nnz_of(F.shape - 1) &&
+           static_cast<int64_t>(rp[rows]) < static_cast<int64_t>(cus) * tile_nnz_of(F.shape) * 7 / 8)
+        --F.shape;
+    F.tree_len = std::min(tree_len, tile_nnz_of(F.shape));
+    if (longest > F.tree_len) return F;
+    int64_t n_long = 0;
+    F.tiles = build_tiles(rows, rp, tile_nnz_of(F.shape), F.tree_len, &n_long);
+    return F;
 }
 
 // Structure of a Sell matrix (see lp_device.h): slice offsets and the row of every lane.
@@ -109,6 +144,7 @@ struct Prep {
     std::vector<int32_t> rpT, ciT, perm, tA, tAT;
     SellHost sA, sAT;  // empty: the LP has no one-workgroup form
     PanelLayoutHost LA, LAT;
+    FlatTiles fA[2], fAT[2];  // per layout (no tiles: none)
     int shape = 1;  // row-tile shape
     bool panels = false;
     int nred = 1;
@@ -133,6 +169,7 @@ struct Offsets {
     size_t fr[6];  // residual restarts: z - T(z) of the last iterate (x, y, A~x parts), then of the anchor
     size_t f32[15] = {0};
     size_t pA[7] = {0}, pAT[7] = {0}, pA32 = 0, pAT32 = 0;
+    size_t fA[2] = {0}, fAT[2] = {0};
     size_t sA[5] = {0}, sAT[5] = {0};  // Sell: slice offsets, rows, columns, values, FP32 values
     size_t part, sc, tr, job;
 };
@@ -897,8 +934,9 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
     Q.shape = o.tile_nnz > 0 ? (o.tile_nnz == 1024 ? 0 : o.tile_nnz == 2048 ? 1 : 2)
                              : tuned_tile_shape(o.precision == LP_PREC_FP32_REFINED, m, n, nnz);
     h->tile_shape = Q.shape;
-    Q.tA = build_tiles(m, rp, tile_nnz_of(Q.shape), &dummy_long);
-    Q.tAT = build_tiles(n, Q.rpT.data(), tile_nnz_of(Q.shape), &dummy_long);
+    const int32_t tn = tile_nnz_of(Q.shape);
+    Q.tA = build_tiles(m, rp, tn, tn, &dummy_long);
+    Q.tAT = build_tiles(n, Q.rpT.data(), tn, tn, &dummy_long);
     // One-workgroup form: 16-bit columns, LDS for the gathered vectors, short rows, and padding
     // (slices as wide as their longest row) that stays within four times the entries. Rows
     // are sorted where a thread keeps its rows' operands in registers; elsewhere the operands
@@ -929,6 +967,14 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
         h->units_at = Q.LAT.units;
         h->panels_a = Q.LA.panels;
         h->panels_at = Q.LAT.panels;
+        const int64_t sv = o.precision == LP_PREC_FP32_REFINED ? 4 : 8;
+        const bool any_width = slice == (int64_t(1) << 19);
+        if (Q.LA.panels == 1 || (any_width && sv * n <= kFlatBytes)) Q.fA[0] = flat_tiles(m, rp, long_len, cus);
+        if (Q.LAT.panels == 1 || (any_width && sv * m <= kFlatBytes)) Q.fAT[0] = flat_tiles(n, Q.rpT.data(), long_len, cus);
+    }
+    if (o.spmv_layout != LP_LAYOUT_PANELS && o.tile_nnz == 0) {  // (a shape that was asked for is kept)
+        Q.fA[1] = flat_tiles(m, rp, tn, cus);
+        Q.fAT[1] = flat_tiles(n, Q.rpT.data(), tn, cus);
     }
     const int mx = m > n ? m : n;
     Q.nred = (mx + 1023) / 1024;
@@ -1010,6 +1056,10 @@ size_t arena_layout(const lp_handle* h, Offsets* O) {
             O->pA32 = L.add(sizeof(float) * Q.LA.packed.size());
             O->pAT32 = L.add(sizeof(float) * Q.LAT.packed.size());
         }
+    }
+    for (int l = 0; l < 2; ++l) {
+        O->fA[l] = L.add(sizeof(int32_t) * Q.fA[l].tiles.size());
+        O->fAT[l] = L.add(sizeof(int32_t) * Q.fAT[l].tiles.size());
     }
     auto add_sell = [&](const SellHost& S, size_t* off) {
         const size_t slots = static_cast<size_t>(S.slots());
@@ -1112,8 +1162,10 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     P.n = n;
     P.nnz = nnz;
     P.nred = Q.nred;
-    P.A.csr = Csr{m, ntA, static_cast<int>(nnz), Q.shape, I(O.arp), I(O.aci), D(O.av), I(O.at), nullptr, nullptr, n};
-    P.AT.csr = Csr{n, ntAT, static_cast<int>(nnz), Q.shape, I(O.trp), I(O.tci), D(O.tv), I(O.tt), nullptr, nullptr, m};
+    P.A.csr = Csr{m, ntA, static_cast<int>(nnz), Q.shape, I(O.arp), I(O.aci), D(O.av), I(O.at), nullptr, nullptr, n,
+                  tile_nnz_of(Q.shape)};
+    P.AT.csr = Csr{n, ntAT, static_cast<int>(nnz), Q.shape, I(O.trp), I(O.tci), D(O.tv), I(O.tt), nullptr, nullptr, m,
+                   tile_nnz_of(Q.shape)};
     P.A.layout = P.AT.layout = panels ? 0 : 1;
     auto bind_layout = [&](const PanelLayoutHost& L, const size_t* off, Mat& M) {
         M.pan = Panels{L.units, L.panels, L.col_bits, static_cast<int>(L.nnz_packed), L.max_unit_rows, I(off[0]), I(off[1]),
@@ -1148,6 +1200,18 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
             P.A.pan.v32 = F(O.pA32);
             P.AT.pan.v32 = F(O.pAT32);
         }
+    }
+    auto bind_flat = [&](const FlatTiles& H, size_t off, const Csr& csr, Csr* M) {
+        if (H.tiles.empty()) return;
+        *M = csr;  // (with the FP32 values, bound above)
+        M->ntiles = static_cast<int>(H.tiles.size()) - 1;
+        M->shape = H.shape;
+        M->tiles = I(off);
+        M->tree_len = H.tree_len;
+    };
+    for (int l = 0; l < 2; ++l) {
+        bind_flat(Q.fA[l], O.fA[l], P.A.csr, &P.A.flat[l]);
+        bind_flat(Q.fAT[l], O.fAT[l], P.AT.csr, &P.AT.flat[l]);
     }
     const bool sell = !Q.sA.ptr.empty();
     auto bind_sell = [&](const SellHost& H, const size_t* off, Sell& S) {
@@ -1233,6 +1297,10 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     if (panels) {
         HIP_TRY(h, upload_layout(Q.LA, O.pA));
         HIP_TRY(h, upload_layout(Q.LAT, O.pAT));
+    }
+    for (int l = 0; l < 2; ++l) {
+        HIP_TRY(h, H2D(I(O.fA[l]), Q.fA[l].tiles.data(), sizeof(int32_t) * Q.fA[l].tiles.size()));
+        HIP_TRY(h, H2D(I(O.fAT[l]), Q.fAT[l].tiles.data(), sizeof(int32_t) * Q.fAT[l].tiles.size()));
     }
     if (sell) {
         HIP_TRY(h, H2D(I(O.sA[0]), Q.sA.ptr.data(), sizeof(int32_t) * Q.sA.ptr.size()));

@@ -67,6 +67,7 @@ struct Csr {
     const int* rowlist;
     const float* v32;  // FP32 copy of v (FP32 storage form only)
     int cols;          // length of the vector the products gather from
+    int tree_len;      // rows longer than this are reduced by a whole workgroup (at most the tile's nonzeros)
 };
 
 // Panel-packed layout (see lp_layout.h): unit u (one wave) owns rows
@@ -109,6 +110,9 @@ struct Mat {
     int nlong;
     const int* longrows;
     int layout;  // 0 panels, 1 row tiles
+    // Row tiles for the launches of one LP, per layout, reducing by a workgroup the rows that the
+    // layout does (null tiles: none, see flat_tiles).
+    Csr flat[2];
 };
 
 // The matrix of a one-workgroup solve: slices of 64 rows, each as wide as its longest row; a

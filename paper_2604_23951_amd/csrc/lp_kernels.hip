@@ -197,6 +197,40 @@ __device__ void row_tree_body(const Csr& M, int r, const T* __restrict__ xin, co
     if (tid == 0) epi.finish(r, s, pre);
 }
 
+// Sum of prod[q, qe) in order, eight values read together and the next eight while these are
+// added: in a tile of long rows few threads sum while the others wait, and read four at a
+// time with the adds in between every group pays the LDS latency (~130 cycles).
+template <class T>
+__device__ inline T row_sum(const T* prod, int q, int qe) {
+    constexpr int U = 8;
+    T s = 0;
+    if (qe - q >= 2 * U) {
+        T a[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) a[k] = prod[q + k];
+        for (q += U; q + U <= qe; q += U) {
+            T b[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) b[k] = prod[q + k];
+#pragma unroll
+            for (int k = 0; k < U; ++k) s += a[k];
+#pragma unroll
+            for (int k = 0; k < U; ++k) a[k] = b[k];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) s += a[k];
+    }
+    for (; q + 4 <= qe; q += 4) {
+        const T a0 = prod[q], a1 = prod[q + 1], a2 = prod[q + 2], a3 = prod[q + 3];
+        s += a0;
+        s += a1;
+        s += a2;
+        s += a3;
+    }
+    for (; q < qe; ++q) s += prod[q];
+    return s;
+}
+
 template <int TN, class T, class Epi>
 __device__ void tile_body(const Csr& M, int b, const T* __restrict__ xin, const Epi& epi, T* prod, double* red) {
     constexpr int kPerThread = TN / kBlock;
@@ -209,7 +243,7 @@ __device__ void tile_body(const Csr& M, int b, const T* __restrict__ xin, const 
     // Loads below are unconditional on clamped, in-bounds indices (every array holds at least
     // one element) so that they issue back to back; out-of-range lanes are masked afterwards.
     const int elast = M.nnz > 0 ? M.nnz - 1 : 0;
-    if (p1 - p0 <= TN) {
+    if (p1 - p0 <= TN && (r1 - r0 > 1 || p1 - p0 <= M.tree_len)) {
         int col[kPerThread];
         T val[kPerThread];
 #pragma unroll
@@ -240,18 +274,7 @@ __device__ void tile_body(const Csr& M, int b, const T* __restrict__ xin, const 
         for (int j = 0; j < kRowsPerThread; ++j) {
             const int r = r0 + tid + j * kBlock;
             if (r < r1) {
-                T s = 0;
-                int q = q0[j];
-                const int qe = q1[j];
-                for (; q + 4 <= qe; q += 4) {
-                    const T a0 = prod[q], a1 = prod[q + 1], a2 = prod[q + 2], a3 = prod[q + 3];
-                    s += a0;
-                    s += a1;
-                    s += a2;
-                    s += a3;
-                }
-                for (; q < qe; ++q) s += prod[q];
-                epi.finish(r, s, pre[j]);
+                epi.finish(r, row_sum(prod, q0[j], q1[j]), pre[j]);
             }
         }
     } else {
@@ -1115,9 +1138,14 @@ void launch_tiles(const Csr& M, const T* xin, const Epi& epi, hipStream_t s) {
 }
 
 // One sparse product with its fused epilogue: one launch holding the panel-packed units and,
-// after them, one workgroup per long row; or the row tiles when that layout is selected.
+// after them, one workgroup per long row; or row tiles, when that layout is selected or the
+// gathered vector is short enough to need no panels (Mat::flat; the sums are the same).
 template <class T, class Epi>
 void launch_spmv(const Mat& M, const T* xin, const Epi& epi, hipStream_t s) {
+    if (M.flat[M.layout].tiles) {
+        launch_tiles(M.flat[M.layout], xin, epi, s);
+        return;
+    }
     if (M.layout == 1) {
         launch_tiles(M.csr, xin, epi, s);
         return;
