@@ -110,6 +110,85 @@ FlatTiles flat_tiles(int32_t rows, const int32_t* rp, int32_t tree_len, int cus)
     return F;
 }
 
+// Host part of a two-phase layout (see lp_device.h): row tiles over the rows that are not
+// long, chunks, and the sizes of everything else.
+struct TwoPhaseHost {
+    std::vector<int32_t> tile_row, tile_chunk, trp, longs, huge;
+    int blocks = 0, width_bits = 0, tile_nnz = 0, tiles_short = 0;
+    int64_t nnz = 0;
+    int tiles() const { return tile_chunk.empty() ? 0 : static_cast<int>(tile_chunk.size()) - 1; }
+    // block starts are multiples of 4
+    size_t slots() const { return static_cast<size_t>(nnz) + 4 * static_cast<size_t>(blocks) + 4; }
+    size_t chunks() const { return static_cast<size_t>(tile_chunk.back()); }
+    size_t cells() const { return static_cast<size_t>(tiles()) * static_cast<size_t>(blocks); }
+};
+
+// Where two launches per product with streams and runs beat one with a gather per entry: a
+// gathered vector that does not fit an XCD's L2, or one of 1.5 MB and more (the gathers miss
+// L1 and queue for the L2) with enough entries to pay for the second launch. us per iteration,
+// Halpern form, row tiles or panels / two phases: 2.4M entries, x of 3.2 MB, FP64 63 / 70, FP32
+// 50 / 51; 4.8M 110 / 98, 82 / 70; 7.2M 150 / 135, 121 / 89; 1.2e7 232 / 206, 190 / 134; 1.7M
+// with vectors below 1.8 MB 38 / 57, 29 / 41.
+bool two_phase_pays(int64_t vector_bytes, int64_t nnz) {
+    return vector_bytes > kFlatBytes || (vector_bytes >= (int64_t(3) << 19) && nnz >= 3000000);
+}
+
+// Column blocks: the widest power of two whose slice fits kTpLds with at least 7/8 as many
+// blocks as CUs (every CU works on a block at a time; wider blocks give longer runs), at most
+// kTpMaxBlocks of them. False when the tiles, the blocks or the offsets would not fit.
+bool build_two_phase(int32_t rows, int32_t cols, const int32_t* rp, const std::vector<uint8_t>& is_long, bool fp32, int cus,
+                     TwoPhaseHost* H) {
+    *H = TwoPhaseHost{};
+    const int sv = fp32 ? 4 : 8;
+    // Tiles: three per CU at least. The largest were measured on 1.2e7 entries (us per iteration
+    // with tiles of 64 / 50 / 39 KB): FP64 206 / 206 / 216 (longer runs), FP32 147 / 141 / 134
+    // (more workgroups on a CU).
+    const int64_t share = (static_cast<int64_t>(rp[rows]) / (3LL * cus) + 63) / 64 * 64;
+    H->tile_nnz = static_cast<int>(std::min<int64_t>((fp32 ? kTpTileLds32 : kTpTileLds) / sv, std::max<int64_t>(share, 1024)));
+    int bits = 0;
+    while ((2 << bits) * sv <= kTpLds) ++bits;
+    while (bits > 8 && ((static_cast<int64_t>(cols) + (1 << bits) - 1) >> bits) * 8 < 7LL * cus) --bits;
+    const int64_t blocks = (static_cast<int64_t>(cols) + (1LL << bits) - 1) >> bits;
+    if (blocks > kTpMaxBlocks) return false;
+    H->blocks = static_cast<int>(blocks);
+    H->width_bits = bits;
+    H->tile_chunk.push_back(0);
+    // tiles over `count` rows of the given lengths, their entries numbered from 0
+    auto cut = [&](int32_t count, auto&& length) -> int64_t {
+        const size_t base = H->trp.size();
+        H->trp.push_back(0);
+        H->tile_row.push_back(0);
+        int32_t start = 0;
+        auto close = [&](int32_t r) {
+            H->tile_row.push_back(r);
+            H->tile_chunk.push_back(H->tile_chunk.back() + (H->trp[base + r] - H->trp[base + start] + 63) / 64);
+            start = r;
+        };
+        for (int32_t r = 0; r < count; ++r) {
+            const int32_t len = length(r);
+            if (H->trp[base + r] + len - H->trp[base + start] > H->tile_nnz || r - start >= H->tile_nnz) close(r);
+            H->trp.push_back(H->trp[base + r] + len);
+        }
+        if (count > 0) close(count);
+        return H->trp.back();
+    };
+    for (int32_t r = 0; r < rows; ++r) {
+        const bool is = !is_long.empty() && is_long[r];
+        if (rp[r + 1] - rp[r] > H->tile_nnz) {
+            if (!is) return false;
+            H->huge.push_back(r);
+        } else if (is) {
+            H->longs.push_back(r);
+        }
+    }
+    H->nnz = cut(rows, [&](int32_t r) { return !is_long.empty() && is_long[r] ? 0 : rp[r + 1] - rp[r]; });
+    H->tiles_short = H->tiles();
+    if (!H->longs.empty())
+        H->nnz += cut(static_cast<int32_t>(H->longs.size()),
+                      [&](int32_t i) { return rp[H->longs[i] + 1] - rp[H->longs[i]]; });
+    return H->cells() < (size_t(1) << 28);
+}
+
 // Structure of a Sell matrix (see lp_device.h): slice offsets and the row of every lane.
 struct SellHost {
     std::vector<int32_t> ptr, row;
@@ -145,6 +224,7 @@ struct Prep {
     SellHost sA, sAT;  // empty: the LP has no one-workgroup form
     PanelLayoutHost LA, LAT;
     FlatTiles fA[2], fAT[2];  // per layout (no tiles: none)
+    TwoPhaseHost tpA, tpAT;   // (no tiles: none)
     int shape = 1;  // row-tile shape
     bool panels = false;
     int nred = 1;
@@ -170,6 +250,8 @@ struct Offsets {
     size_t f32[15] = {0};
     size_t pA[7] = {0}, pAT[7] = {0}, pA32 = 0, pAT32 = 0;
     size_t fA[2] = {0}, fAT[2] = {0};
+    // two-phase: block starts, tile rows, tile chunks, row offsets, deltas, masks, first runs, columns, positions, values, the lists of long and of huge rows
+    size_t tpA[12] = {0}, tpAT[12] = {0}, tpbuf = 0;
     size_t sA[5] = {0}, sAT[5] = {0};  // Sell: slice offsets, rows, columns, values, FP32 values
     size_t part, sc, tr, job;
 };
@@ -971,6 +1053,11 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
         const bool any_width = slice == (int64_t(1) << 19);
         if (Q.LA.panels == 1 || (any_width && sv * n <= kFlatBytes)) Q.fA[0] = flat_tiles(m, rp, long_len, cus);
         if (Q.LAT.panels == 1 || (any_width && sv * m <= kFlatBytes)) Q.fAT[0] = flat_tiles(n, Q.rpT.data(), long_len, cus);
+        if (any_width && two_phase_pays(sv * n, nnz) && !build_two_phase(m, n, rp, Q.LA.is_long, sv == 4, cus, &Q.tpA))
+            Q.tpA = {};
+        if (any_width && two_phase_pays(sv * m, nnz) &&
+            !build_two_phase(n, m, Q.rpT.data(), Q.LAT.is_long, sv == 4, cus, &Q.tpAT))
+            Q.tpAT = {};
     }
     if (o.spmv_layout != LP_LAYOUT_PANELS && o.tile_nnz == 0) {  // (a shape that was asked for is kept)
         Q.fA[1] = flat_tiles(m, rp, tn, cus);
@@ -1061,6 +1148,18 @@ size_t arena_layout(const lp_handle* h, Offsets* O) {
         O->fA[l] = L.add(sizeof(int32_t) * Q.fA[l].tiles.size());
         O->fAT[l] = L.add(sizeof(int32_t) * Q.fAT[l].tiles.size());
     }
+    size_t tp_slots = 0;
+    auto add_tp = [&](const TwoPhaseHost& H, size_t* off) {
+        if (!H.tiles()) return;
+        const size_t bytes[12] = {4 * (static_cast<size_t>(H.blocks) + 1), 4 * H.tile_row.size(), 4 * H.tile_chunk.size(),
+                                  4 * H.trp.size(), 4 * H.cells(), 8 * (H.chunks() + 1), 4 * (H.chunks() + 1), 2 * H.slots(),
+                                  2 * 64 * H.chunks(), (fp32 ? 12 : 8) * H.slots(), 4 * H.longs.size(), 4 * H.huge.size()};
+        for (int i = 0; i < 12; ++i) off[i] = L.add(bytes[i]);
+        tp_slots = std::max(tp_slots, H.slots());
+    };
+    add_tp(Q.tpA, O->tpA);
+    add_tp(Q.tpAT, O->tpAT);
+    O->tpbuf = L.add((fp32 ? 4 : 8) * tp_slots);
     auto add_sell = [&](const SellHost& S, size_t* off) {
         const size_t slots = static_cast<size_t>(S.slots());
         off[0] = L.add(sizeof(int32_t) * S.ptr.size());
@@ -1122,6 +1221,73 @@ int32_t tune_layout(lp_handle* h, hipStream_t s) {
     Q.trial_us[1] = 1e3 * best[1] / kReps;
     int expect = -1;
     (void)Q.tuned.compare_exchange_strong(expect, best[1] < best[0] ? 1 : 0);
+    return LP_OK;
+}
+
+// Fills the two-phase layout of M on the device from its (scaled) CSR: entries per cell, the
+// cells' places (on the host), then the entries.
+int32_t setup_two_phase(lp_handle* h, const TwoPhaseHost& H, const Mat& M, char* base, const size_t* off, hipStream_t s) {
+    if (!H.tiles()) return LP_OK;
+    const TwoPhase& T = M.tp;
+    const size_t tiles = static_cast<size_t>(H.tiles()), blocks = static_cast<size_t>(H.blocks), cells = H.cells();
+    char* tmp = nullptr;  // the cells' counts, then their first places; and their places inside the tiles
+    HIP_TRY(h, hipMalloc(reinterpret_cast<void**>(&tmp), 8 * cells));
+    struct Free {
+        char* p;
+        ~Free() { (void)hipFree(p); }
+    } release{tmp};
+    int* d_cell = reinterpret_cast<int*>(tmp);
+    int* d_k = d_cell + cells;
+    HIP_TRY(h, hipMemcpyAsync(base + off[1], H.tile_row.data(), 4 * H.tile_row.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(h, hipMemcpyAsync(base + off[2], H.tile_chunk.data(), 4 * H.tile_chunk.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(h, hipMemcpyAsync(base + off[3], H.trp.data(), 4 * H.trp.size(), hipMemcpyHostToDevice, s));
+    if (!H.longs.empty()) HIP_TRY(h, hipMemcpyAsync(base + off[10], H.longs.data(), 4 * H.longs.size(), hipMemcpyHostToDevice, s));
+    if (!H.huge.empty()) HIP_TRY(h, hipMemcpyAsync(base + off[11], H.huge.data(), 4 * H.huge.size(), hipMemcpyHostToDevice, s));
+    launch_tp_count(T, M.csr, d_cell, s);
+    std::vector<int32_t> cell(cells), k(cells), delta(cells, 0), start(blocks + 1, 0), first(H.chunks(), 0);
+    std::vector<uint64_t> mask(H.chunks(), 0);
+    HIP_TRY(h, hipMemcpyAsync(cell.data(), d_cell, 4 * cells, hipMemcpyDeviceToHost, s));
+    HIP_TRY(h, hipStreamSynchronize(s));
+    std::vector<int32_t> in_tile(tiles, 0), runs(tiles, 0);
+    int32_t next = 0;
+    for (size_t b = 0; b < blocks; ++b) {
+        start[b] = next;
+        for (size_t t = 0; t < tiles; ++t) {
+            const int32_t count = cell[b * tiles + t], at = in_tile[t];
+            cell[b * tiles + t] = next;
+            k[t * blocks + b] = at;
+            if (count > 0) {
+                delta[t * blocks + static_cast<size_t>(runs[t]++)] = next - at;
+                mask[static_cast<size_t>(H.tile_chunk[t]) + at / 64] |= 1ull << (at % 64);
+            }
+            next += count;
+            in_tile[t] = at + count;
+        }
+        next = (next + 3) & ~3;
+    }
+    start[blocks] = next;
+    for (size_t t = 0; t < tiles; ++t) {
+        if ((in_tile[t] + 63) / 64 != H.tile_chunk[t + 1] - H.tile_chunk[t]) return fail(h, LP_ERR_INTERNAL, "two-phase layout lost entries");
+        int32_t seen = 0;
+        for (int32_t c = H.tile_chunk[t]; c < H.tile_chunk[t + 1]; ++c) {
+            first[c] = seen;
+            seen += __builtin_popcountll(mask[c]);
+        }
+    }
+    if (static_cast<size_t>(next) > H.slots()) return fail(h, LP_ERR_INTERNAL, "two-phase layout overflows");
+    HIP_TRY(h, hipMemcpyAsync(d_cell, cell.data(), 4 * cells, hipMemcpyHostToDevice, s));
+    HIP_TRY(h, hipMemcpyAsync(d_k, k.data(), 4 * cells, hipMemcpyHostToDevice, s));
+    HIP_TRY(h, hipMemcpyAsync(base + off[0], start.data(), 4 * start.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(h, hipMemcpyAsync(base + off[4], delta.data(), 4 * cells, hipMemcpyHostToDevice, s));
+    HIP_TRY(h, hipMemcpyAsync(base + off[5], mask.data(), 8 * mask.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(h, hipMemcpyAsync(base + off[6], first.data(), 4 * first.size(), hipMemcpyHostToDevice, s));
+    // padding between the blocks: column 0, value 0 (its products are written and never read)
+    HIP_TRY(h, hipMemsetAsync(base + off[7], 0, 2 * H.slots(), s));
+    launch_fill(const_cast<double*>(T.v), static_cast<long long>(H.slots()), 0.0, s);
+    if (T.v32) HIP_TRY(h, hipMemsetAsync(const_cast<float*>(T.v32), 0, sizeof(float) * H.slots(), s));
+    launch_tp_fill(T, M.csr, d_cell, d_k, const_cast<unsigned short*>(T.lcol), const_cast<double*>(T.v),
+                   const_cast<float*>(T.v32), const_cast<unsigned short*>(T.pos), s);
+    HIP_TRY(h, hipStreamSynchronize(s));  // the host arrays and tmp are this call's
     return LP_OK;
 }
 
@@ -1213,6 +1379,37 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
         bind_flat(Q.fA[l], O.fA[l], P.A.csr, &P.A.flat[l]);
         bind_flat(Q.fAT[l], O.fAT[l], P.AT.csr, &P.AT.flat[l]);
     }
+    auto bind_tp = [&](const TwoPhaseHost& H, const size_t* off, Mat& M) {
+        if (!H.tiles()) return;
+        TwoPhase& T = M.tp;
+        T.tiles = H.tiles();
+        T.tiles_padded = (T.tiles + kTpXcds - 1) / kTpXcds * kTpXcds;
+        T.blocks = H.blocks;
+        T.width_bits = H.width_bits;
+        T.tile_nnz = H.tile_nnz;
+        T.fp32 = fp32 ? 1 : 0;
+        T.cols = M.csr.cols;
+        T.slots = static_cast<int>(H.slots());
+        T.block_start = I(off[0]);
+        T.tile_row = I(off[1]);
+        T.tile_chunk = I(off[2]);
+        T.trp = I(off[3]);
+        T.delta = I(off[4]);
+        T.mask = reinterpret_cast<const unsigned long long*>(b + off[5]);
+        T.first = I(off[6]);
+        T.lcol = reinterpret_cast<const unsigned short*>(b + off[7]);
+        T.pos = reinterpret_cast<const unsigned short*>(b + off[8]);
+        T.v = D(off[9]);
+        T.v32 = fp32 ? reinterpret_cast<const float*>(D(off[9]) + H.slots()) : nullptr;
+        T.is_long = M.pan.is_long;
+        T.tiles_short = H.tiles_short;
+        T.longs = I(off[10]);
+        T.nhuge = static_cast<int>(H.huge.size());
+        T.huge = I(off[11]);
+        T.buf = b + O.tpbuf;
+    };
+    bind_tp(Q.tpA, O.tpA, P.A);
+    bind_tp(Q.tpAT, O.tpAT, P.AT);
     const bool sell = !Q.sA.ptr.empty();
     auto bind_sell = [&](const SellHost& H, const size_t* off, Sell& S) {
         S = Sell{static_cast<int>(H.ptr.size()) - 1, static_cast<int>(H.slots()), I(off[0]), I(off[1]),
@@ -1333,6 +1530,8 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
             launch_to_float(D(O.pAT[3]), F(O.pAT32), Q.LAT.nnz_packed, s);
         }
     }
+    if (int32_t rc = setup_two_phase(h, Q.tpA, P.A, b, O.tpA, s)) return rc;
+    if (int32_t rc = setup_two_phase(h, Q.tpAT, P.AT, b, O.tpAT, s)) return rc;
     if (sell) {
         launch_fill_sell(P.A.csr, P.sA, reinterpret_cast<unsigned*>(b + O.sA[2]), D(O.sA[3]),
                          fp32 ? F(O.sA[4]) : nullptr, s);

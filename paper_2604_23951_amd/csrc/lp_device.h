@@ -88,6 +88,38 @@ struct Panels {
     int cols;                      // length of the gathered vector
 };
 
+// Two-phase layout of a matrix (lp_two_phase.h): blocks of 2^width_bits columns and tiles of
+// rows with at most tile_nnz entries: first those of the rows that are not long (tile_row
+// numbers the matrix's rows, trp their entries without the long rows'), from tiles_short on
+// those of the long rows of at most tile_nnz entries (tile_row numbers the list longs, trp
+// continues with its entries). Entries in block order, tile by tile
+// inside a block (block b's start at block_start[b], a multiple of 4): lcol (column inside the
+// block), v. Tile t's entries in block order are positions 64 tile_chunk[t] + k of pos (CSR
+// position inside the tile); entry k's product is buf[k + delta[t * blocks + run]], run the
+// number of the run of consecutive products it belongs to: first[chunk] runs begin before its
+// chunk of 64 and the bits of mask[chunk] mark those beginning inside it.
+struct TwoPhase {
+    int tiles;  // 0: not built
+    int tiles_short, tiles_padded, blocks, width_bits, tile_nnz, fp32, cols, slots;
+    const int *block_start, *tile_row, *tile_chunk, *trp, *delta;
+    const unsigned long long* mask;
+    const int* first;
+    const unsigned short *lcol, *pos;
+    const double* v;
+    const float* v32;
+    const unsigned char* is_long;  // as in Panels
+    const int* longs;
+    int nhuge;          // rows longer than a tile, each reduced by a workgroup from its gathers
+    const int* huge;
+    void* buf;  // products of one launch, in the precision of the iterations
+};
+constexpr int kTpMaxBlocks = 1024;
+constexpr int kTpSplit = 2;  // workgroups that share a block's entries
+constexpr int kTpXcds = 8;
+constexpr int kTpLds = 64 * 1024;      // of the gathered slice at most
+constexpr int kTpTileLds = 64 * 1024;  // of a tile's products at most (FP64)
+constexpr int kTpTileLds32 = 39 * 1024;  // (FP32)
+
 // Index checks of the checked build (compiled with LPGPU_CHECKED=1): a gathered column or
 // an accumulator row outside its array sets a bit of a device word and is replaced by 0, so
 // the kernel reads nothing outside its arrays; the host reports the word after a call.
@@ -113,6 +145,7 @@ struct Mat {
     // Row tiles for the launches of one LP, per layout, reducing by a workgroup the rows that the
     // layout does (null tiles: none, see flat_tiles).
     Csr flat[2];
+    TwoPhase tp;  // panel layout, vectors beyond the L2: in place of the panels' sweep
 };
 
 // The matrix of a one-workgroup solve: slices of 64 rows, each as wide as its longest row; a
@@ -284,6 +317,11 @@ constexpr int kSoloMaxDim = 14000;          // rows and columns: the gathered FP
 constexpr long long kSoloMaxNnz = 65536;
 constexpr int kSoloMaxRow = 128;            // entries of a row, summed by one thread
 constexpr int kSoloLdsMax = 152 * 1024;     // dynamic LDS of a workgroup at most
+// Set-up of a two-phase layout: entries per cell, then the entries placed (cell_base: a cell's
+// first place in block order, [block * tiles + tile]; cell_k: in its tile, [tile * blocks + block]).
+void launch_tp_count(const TwoPhase& M, const Csr& A, int* counts, hipStream_t s);
+void launch_tp_fill(const TwoPhase& M, const Csr& A, const int* cell_base, const int* cell_k, unsigned short* lcol,
+                    double* v, float* v32, unsigned short* pos, hipStream_t s);
 void launch_fill_sell(const Csr& M, const Sell& S, unsigned* col, double* v, float* v32, hipStream_t s);
 int solo_lds_bytes(int m, int n, int fp32, int a_slots, int at_slots);  // of one LP with that many staged slots
 // The power iteration of launch_power_start / launch_power_steps (chunks of iters steps, the

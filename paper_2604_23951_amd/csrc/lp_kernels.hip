@@ -161,12 +161,14 @@ __device__ inline T block_sum_t(T v, double* red) {
 
 // Row r reduced by the whole workgroup: thread t adds the products of entries t, t + kBlock,
 // ... in order (TN / kBlock loads in flight per round; the order of the additions does not
-// depend on TN), then a fixed-shape tree over the workgroup. Called by every thread.
+// depend on TN), then a fixed-shape tree over the workgroup's first kBlock threads. Called by
+// every thread; red holds a value per wave.
 template <int TN, class T, class Epi>
 __device__ void row_tree_body(const Csr& M, int r, const T* __restrict__ xin, const Epi& epi, double* red) {
     constexpr int kPerThread = TN / kBlock;
-    const int p0 = M.rp[r], p1 = M.rp[r + 1];
     const int tid = threadIdx.x;
+    // threads past the first kBlock (a wider workgroup) add nothing
+    const int p0 = M.rp[r], p1 = tid < kBlock ? M.rp[r + 1] : p0;
     const int* __restrict__ ci = M.ci;
     const T* __restrict__ av = vals_of<T>(M);
     const int elast = M.nnz > 0 ? M.nnz - 1 : 0;
@@ -1126,6 +1128,8 @@ __host__ __device__ inline EpiDual32H epi_dual32_h(const DevLP& P, const Scalars
     return e;
 }
 
+#include "lp_two_phase.h"
+
 template <class T, class Epi>
 void launch_tiles(const Csr& M, const T* xin, const Epi& epi, hipStream_t s) {
     if (M.ntiles <= 0) return;
@@ -1139,9 +1143,26 @@ void launch_tiles(const Csr& M, const T* xin, const Epi& epi, hipStream_t s) {
 
 // One sparse product with its fused epilogue: one launch holding the panel-packed units and,
 // after them, one workgroup per long row; or row tiles, when that layout is selected or the
-// gathered vector is short enough to need no panels (Mat::flat; the sums are the same).
+// gathered vector is short enough to need no panels (Mat::flat), or the two-phase product
+// where that pays (Mat::tp). The sums are the same in all of them.
 template <class T, class Epi>
 void launch_spmv(const Mat& M, const T* xin, const Epi& epi, hipStream_t s) {
+    if (M.layout == 0 && M.tp.tiles > 0 && M.tp.fp32 == (sizeof(T) == 4)) {
+        Csr L = M.csr;
+        L.rowlist = M.tp.huge;
+        const size_t glds = sizeof(T) << M.tp.width_bits, tlds = sizeof(T) * static_cast<size_t>(M.tp.tile_nnz);
+        static const bool tp_attr = [] {
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_products_kernel<T, Epi>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kTpLds) == hipSuccess &&
+                   hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_rows_kernel<T, Epi>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kTpLds) == hipSuccess;
+        }();
+        (void)tp_attr;
+        hipLaunchKernelGGL((tp_products_kernel<T, Epi>), dim3(M.tp.blocks * kTpSplit), dim3(kTpThreads), glds, s, M.tp, xin, epi);
+        hipLaunchKernelGGL((tp_rows_kernel<T, Epi>), dim3(M.tp.tiles_padded + M.tp.nhuge), dim3(kTpThreads), tlds, s, M.tp, L,
+                           xin, epi);
+        return;
+    }
     if (M.flat[M.layout].tiles) {
         launch_tiles(M.flat[M.layout], xin, epi, s);
         return;
@@ -2726,6 +2747,15 @@ void launch_batch(const BatchJob* jobs, const int* order, int count, int* counte
     }
     hipLaunchKernelGGL(batch_kernel, dim3(grid), dim3(kBlock), static_cast<size_t>(lds_cap), s, jobs, order, count,
                        counter, lds_cap);
+}
+
+void launch_tp_count(const TwoPhase& M, const Csr& A, int* counts, hipStream_t s) {
+    hipLaunchKernelGGL(tp_count_kernel, dim3(M.tiles), dim3(kBlock), 0, s, M, A, counts);
+}
+
+void launch_tp_fill(const TwoPhase& M, const Csr& A, const int* cell_base, const int* cell_k, unsigned short* lcol,
+                    double* v, float* v32, unsigned short* pos, hipStream_t s) {
+    hipLaunchKernelGGL(tp_fill_kernel, dim3(M.tiles), dim3(64), 0, s, M, A, cell_base, cell_k, lcol, v, v32, pos);
 }
 
 void launch_fill_sell(const Csr& M, const Sell& S, unsigned* col, double* v, float* v32, hipStream_t s) {
