@@ -236,6 +236,13 @@ struct Prep {
     double trial_us[2] = {0.0, 0.0};
 };
 
+// The point of a batched or one-workgroup solve of at most this many bytes is written to pinned
+// host memory by the kernel that extracts it: lp_get_solution then copies nothing from the
+// device (three copies and a wait took 52 us per LP, twice as long as the solves of a batch of
+// 128 small LPs).
+constexpr size_t kPinnedResult = 128 * 1024;
+constexpr size_t kPinnedScalars = (sizeof(Scalars) + 63) / 64 * 64;
+
 // Device bytes of a one-workgroup lp_solve: the job (256-byte aligned), then the LP order
 // (one int), the work counter and the start clock, 256 bytes apart.
 constexpr size_t kSoloJobAligned = (sizeof(BatchJob) + 255) / 256 * 256;
@@ -353,6 +360,8 @@ struct lp_handle {
     double* d_y0 = nullptr;
     char* d_job = nullptr;  // job, LP order, work counter and start clock of a one-workgroup lp_solve
     Scalars* h_sc = nullptr;  // pinned host copy of the device scalars
+    double* h_res = nullptr;  // after it, for an LP of moderate size: x, y, z of a batched or one-workgroup solve
+    bool res_valid = false;   // h_res holds the last solve's point
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     bool graph_failed = false;
@@ -385,6 +394,10 @@ struct SoloPlan {
     bool whole = false;
     void apply(BatchJob* J) const {
         J->variant = variant;
+        if (variant == SOLO_NONE) {  // (the row-tile solver writes no host result)
+            J->host = nullptr;
+            J->host_sc = nullptr;
+        }
         J->a_slices = a_slices;
         J->a_slots = a_slots;
         J->at_slices = at_slices;
@@ -442,6 +455,8 @@ void destroy_device(lp_handle* h) {
     h->graph = nullptr;
     h->arena = nullptr;
     h->h_sc = nullptr;
+    h->h_res = nullptr;
+    h->res_valid = false;
     h->stream = nullptr;
     for (auto& e : h->ev) e = nullptr;
     h->on_device = false;
@@ -545,6 +560,8 @@ BatchJob make_job(lp_handle* h, const lp_options* bo) {
     // the time limit becomes a device-clock deadline, checked at every evaluation on the device
     J.limit_ticks = 0;
     J.t0 = nullptr;
+    J.host = h->h_res;
+    J.host_sc = h->h_res ? h->h_sc : nullptr;
     J.variant = SOLO_NONE;
     J.eval_blocks = 1;
     J.a_slices = J.a_slots = J.at_slices = J.at_slots = J.plain_stop = 0;
@@ -588,12 +605,18 @@ SoloPlan solo_plan(const lp_handle* h, int budget) {
     return S;
 }
 
-int32_t finish_batch(const std::vector<lp_handle*>& hs, hipStream_t s) {
-    for (lp_handle* h : hs) HIP_TRY(h, hipMemcpyAsync(h->h_sc, h->P.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
+// Collects the results of the handles; written(i): the kernels wrote handle i's scalars and
+// point to its pinned host memory.
+template <class Written>
+int32_t finish_batch(lp_handle* const* hs, int count, hipStream_t s, Written&& written) {
+    for (int i = 0; i < count; ++i)
+        if (!written(i))
+            HIP_TRY(hs[i], hipMemcpyAsync(hs[i]->h_sc, hs[i]->P.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
     HIP_TRY(hs[0], hipStreamSynchronize(s));
-    for (lp_handle* h : hs) {
-        fill_info(h);
-        h->solved = true;
+    for (int i = 0; i < count; ++i) {
+        fill_info(hs[i]);
+        hs[i]->solved = true;
+        hs[i]->res_valid = written(i);
     }
     return LP_OK;
 }
@@ -908,7 +931,8 @@ int32_t finish_persistent(const std::vector<lp_handle*>& hs, PersistentRun& R, b
     R.buf = nullptr;
     int32_t rc = LP_OK;
     if (e != hipSuccess) rc = fail(hs[0], LP_ERR_DEVICE, std::string("batched solve: ") + hipGetErrorString(e));
-    else if (collect) rc = finish_batch(hs, R.s[0]);
+    else if (collect)
+        rc = finish_batch(hs.data(), static_cast<int>(hs.size()), R.s[0], [&](int i) { return R.jobs[i].host != nullptr; });
     for (hipStream_t& st : R.s) {
         if (st) (void)hipStreamDestroy(st);
         st = nullptr;
@@ -968,7 +992,7 @@ int32_t solve_block_diagonal(const std::vector<lp_handle*>& hs, const lp_options
     launch_multi(all.M, MULTI_EXTRACT, 0, s);
     HIP_TRY(h0, hipGetLastError());
     HIP_TRY(h0, hipStreamSynchronize(s));
-    return finish_batch(hs, s);
+    return finish_batch(hs.data(), static_cast<int>(hs.size()), s, [&](int i) { return hs[i]->h_res != nullptr; });
 }
 
 int32_t capture_graph(lp_handle* h) {
@@ -1311,8 +1335,11 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     h->arena_bytes = arena_layout(h, &O);
     HIP_TRY(h, hipMalloc(reinterpret_cast<void**>(&h->arena), h->arena_bytes));
     if (!h->h_sc) {
-        HIP_TRY(h, hipHostMalloc(reinterpret_cast<void**>(&h->h_sc), sizeof(Scalars), hipHostMallocDefault));
+        const size_t res = sizeof(double) * (2 * static_cast<size_t>(n) + static_cast<size_t>(m));
+        const bool pinned = res <= kPinnedResult;
+        HIP_TRY(h, hipHostMalloc(reinterpret_cast<void**>(&h->h_sc), kPinnedScalars + (pinned ? res : 0), hipHostMallocDefault));
         std::memset(h->h_sc, 0, sizeof(Scalars));
+        h->h_res = pinned ? reinterpret_cast<double*>(reinterpret_cast<char*>(h->h_sc) + kPinnedScalars) : nullptr;
     }
     char* b = h->arena;
     auto D = [&](size_t off) { return reinterpret_cast<double*>(b + off); };
@@ -2243,11 +2270,7 @@ int32_t solve_one_workgroup(lp_handle* h, size_t lds_need, const SoloPlan& plan,
     int32_t* dcounter = reinterpret_cast<int32_t*>(b + kSoloJobAligned + 256);
     long long* dt0 = reinterpret_cast<long long*>(b + kSoloJobAligned + 512);
     J.t0 = dt0;
-    const int32_t first = 0;
-    HIP_TRY(h, hipMemcpyAsync(dj, &J, sizeof(BatchJob), hipMemcpyHostToDevice, s));
-    HIP_TRY(h, hipMemcpyAsync(dorder, &first, sizeof(first), hipMemcpyHostToDevice, s));
-    HIP_TRY(h, hipStreamSynchronize(s));  // J and `first` are on this stack frame
-    launch_batch_start(dcounter, dt0, s);
+    launch_solo_start(J, dj, dorder, dcounter, dt0, s);
     if (plan.variant != SOLO_NONE) {
         launch_solo(solo_threads(plan.variant), dj, dorder, 1, dcounter, 1, plan.lds, s);
     } else {
@@ -2255,12 +2278,13 @@ int32_t solve_one_workgroup(lp_handle* h, size_t lds_need, const SoloPlan& plan,
         launch_batch(dj, dorder, 1, dcounter, 1, s, lds_cap);
     }
     if (int32_t rc = check_launch(h, "one-workgroup solve")) return rc;
-    HIP_TRY(h, hipMemcpyAsync(h->h_sc, h->P.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
+    if (!J.host) HIP_TRY(h, hipMemcpyAsync(h->h_sc, h->P.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
     fill_info(h);
     h->info.solve_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     h->info.solve_path = 1;
     h->solved = true;
+    h->res_valid = J.host != nullptr;
     return LP_OK;
 }
 
@@ -2272,6 +2296,7 @@ int32_t solve_from(lp_handle* h, const double* x0s, const double* y0s, int term_
     hipStream_t s = h->stream;
     const DevLP& P = h->P;
     h->resumable = false;
+    h->res_valid = false;
     if (term_mode == 0 && omega0 == 0.0 && pause_k == 0 && x0s == h->d_x0 && y0s == h->d_y0 && !h->timing &&
         h->opt.small_lp_lds > 0) {
         const size_t need = small_lp_lds_bytes(P);
@@ -2456,6 +2481,7 @@ int32_t with_checks(lp_handle* h, int device, int32_t rc) {
 // Statistics and extraction of the paused point (after a pause or a state import).
 int32_t finish_paused(lp_handle* h) {
     hipStream_t s = h->stream;
+    h->res_valid = false;
     launch_evaluate(h->P, 2, s);
     launch_extract(h->P, s);
     if (int32_t rc = check_launch(h, "paused point")) return rc;
@@ -2610,6 +2636,7 @@ int32_t lp_resume(lp_handle* h, int64_t k_pause) {
         HIP_TRY(h, hipStreamSynchronize(s));
         set_form(h->P, h->opt);
         h->resumable = false;
+        h->res_valid = false;
         h->solved = false;
         const int32_t rc = run_periods(h, t0, k_pause);
         h->info.polish_primal_iterations = h->info.polish_dual_iterations = 0;
@@ -2809,15 +2836,10 @@ int32_t lp_solve_batch_static(lp_handle* const* hs, int32_t count, const lp_opti
         for (int g = 0; g < BG_COUNT; ++g) launch_group(G, g, S.jobs, S.order, S.counter, cus, wpc, s);
         if (int32_t rc = check_launch(h0, "allocation-free batched solve")) return rc;
         HIP_TRY(h0, hipStreamSynchronize(s));
-        for (int32_t i = 0; i < count; ++i)
-            HIP_TRY(hs[i], hipMemcpyAsync(hs[i]->h_sc, hs[i]->P.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
-        HIP_TRY(h0, hipStreamSynchronize(s));
+        auto written = [&](int i) { return group[i] <= BG_SOLO_256 && hs[i]->h_res != nullptr; };
+        if (int32_t rc = finish_batch(hs, count, s, written)) return rc;
         const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-        for (int32_t i = 0; i < count; ++i) {
-            fill_info(hs[i]);
-            hs[i]->info.solve_seconds = secs;
-            hs[i]->solved = true;
-        }
+        for (int32_t i = 0; i < count; ++i) hs[i]->info.solve_seconds = secs;
         return with_checks(nullptr, dev, LP_OK);
     } catch (...) {
         return fail(nullptr, LP_ERR_INTERNAL, "unexpected exception");
@@ -2865,6 +2887,14 @@ int32_t lp_get_solution(lp_handle* h, double* x, double* y, double* z, lp_info* 
         if (x) std::memcpy(x, h->res_x.data(), sizeof(double) * h->n);
         if (y && h->m > 0) std::memcpy(y, h->res_y.data(), sizeof(double) * h->m);
         if (z) std::memcpy(z, h->res_z.data(), sizeof(double) * h->n);
+        if (info) *info = h->info;
+        return LP_OK;
+    }
+    if (h->res_valid) {  // written by the solve's kernels, which have ended
+        const double* r = h->h_res;
+        if (x) std::memcpy(x, r, sizeof(double) * h->n);
+        if (y && h->m > 0) std::memcpy(y, r + h->n, sizeof(double) * h->m);
+        if (z) std::memcpy(z, r + h->n + h->m, sizeof(double) * h->n);
         if (info) *info = h->info;
         return LP_OK;
     }

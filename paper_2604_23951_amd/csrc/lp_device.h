@@ -217,6 +217,9 @@ struct BatchJob {
     const double* y0;
     long long limit_ticks;  // time limit in device wall-clock ticks (0: none)
     const long long* t0;    // device wall clock at the start of the call (null: the LP's reset)
+    // pinned host memory of the result, when the LP has it: the scalar state, and x, y, z
+    Scalars* host_sc;
+    double* host;
     // one-workgroup solver: the SoloVariant, the reduction blocks whose order its evaluations
     // keep, and the slices (slots) of A and A^T staged in LDS
     int variant, eval_blocks;
@@ -350,8 +353,11 @@ struct StaticBatchScratch {
 };
 hipError_t static_batch_scratch(int device, StaticBatchScratch* out);
 size_t static_batch_scratch_bytes();
+// launch_solo_start does the same and writes the job table of one LP (the job travels as a
+// kernel argument: no copies and no wait for them).
 // Clears kBatchCounters counters and sets *t0 to the device wall clock, with a kernel (no
 // memset node if the caller captures the stream).
+void launch_solo_start(const BatchJob& J, BatchJob* job, int* order, int* counters, long long* t0, hipStream_t s);
 void launch_batch_start(int* counters, long long* t0, hipStream_t s);
 // One launch of a block-diagonal batch; it_or_mode is the iteration inside the bundle for
 // MULTI_PRIMAL / MULTI_DUAL and the evaluation mode for MULTI_PARTIALS / MULTI_DECIDE.

@@ -1956,6 +1956,18 @@ __device__ inline void extract_at(const DevLP& P, int avg, int status, double sc
     if (g < P.m) P.out_y[g] = dual_ray ? ((ry[g] - by[g]) * P.R[g]) * scale : ys[g] * P.R[g];
 }
 
+// The extracted element g, and with it (g = 0) the scalar state, to the job's pinned host memory.
+__device__ inline void result_to_host(const BatchJob& J, const Scalars* sc, int g) {
+    if (!J.host) return;
+    const DevLP& P = J.P;
+    if (g < P.n) {
+        J.host[g] = P.out_x[g];
+        J.host[static_cast<long long>(P.n) + P.m + g] = P.out_z[g];
+    }
+    if (g < P.m) J.host[P.n + g] = P.out_y[g];
+    if (g == 0) *J.host_sc = *sc;
+}
+
 __global__ void extract_kernel(DevLP P) {
     extract_at(P, P.sc->out_avg, P.sc->status, P.sc->ray_scale, P.sc->ray_src, blockIdx.x * blockDim.x + threadIdx.x);
 }
@@ -2444,6 +2456,7 @@ __global__ __launch_bounds__(kBlock) void multi_elem_kernel(const BatchJob* jobs
         else apply_restart_at(P, lr, g);
     } else {
         extract_at(P, sc->out_avg, sc->status, sc->ray_scale, sc->ray_src, g);
+        result_to_host(J, sc, g);
     }
 }
 
@@ -2817,7 +2830,21 @@ __global__ void batch_start_kernel(int* counters, long long* t0) {
     if (threadIdx.x < kBatchCounters) counters[threadIdx.x] = 0;
     if (threadIdx.x == 0) *t0 = static_cast<long long>(wall_clock64());
 }
+
+__global__ void solo_start_kernel(BatchJob J, BatchJob* job, int* order, int* counters, long long* t0) {
+    if (threadIdx.x < kBatchCounters) counters[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        *job = J;
+        *order = 0;
+        *t0 = static_cast<long long>(wall_clock64());
+    }
+}
 }  // namespace
+
+static_assert(sizeof(BatchJob) + 64 <= 4096, "a job fits the kernel arguments");
+void launch_solo_start(const BatchJob& J, BatchJob* job, int* order, int* counters, long long* t0, hipStream_t s) {
+    hipLaunchKernelGGL(solo_start_kernel, dim3(1), dim3(64), 0, s, J, job, order, counters, t0);
+}
 
 hipError_t static_batch_scratch(int device, StaticBatchScratch* out) {
     if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;

@@ -564,7 +564,10 @@ __device__ __forceinline__ void solo_solve(const BatchJob& J) {
         solo_evaluate<NT, kFp32>(J, 0);
     }
     if (J.plain_stop && S.sc.status == 2 && tid == 0) plain_statistics(P, &S.sc);
-    for (int g = tid; g < mx; g += NT) extract_at(P, S.sc.out_avg, S.sc.status, S.sc.ray_scale, S.sc.ray_src, g);
+    for (int g = tid; g < mx; g += NT) {
+        extract_at(P, S.sc.out_avg, S.sc.status, S.sc.ray_scale, S.sc.ray_src, g);
+        result_to_host(J, &S.sc, g);
+    }
     __syncthreads();
     if (tid == 0) *P.sc = S.sc;
 }

@@ -136,3 +136,26 @@ def test_norm_estimate_equals_the_launch_per_step_iteration(shape):
         assert sigma[0] == sigma[1]
     else:
         assert abs(sigma[0] - sigma[1]) <= 1e-12 * sigma[1]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_the_latest_point_is_returned(precision):
+    """Points written to host memory by the solve's kernel (one workgroup, batches) and copied
+    from the device (kernel loop, polishing, pauses) replace each other."""
+    lp = _lp(130, 300, 6)
+    opts = dict(method=1, precision=precision, eps_rel=0.0)
+    ref = {k: _run(lp, k, False, method=1, precision=precision)[1].x for k in (64, 128, 192)}
+    with lpg.Solver(lp, spmv_layout=1, max_iters=64, **opts) as s:
+        np.testing.assert_array_equal(s.solve().x, ref[64])
+        s.update(max_iters=1000, **{k: v for k, v in opts.items() if k != "precision"})
+        np.testing.assert_array_equal(s.solve_until(128).x, ref[128])
+        np.testing.assert_array_equal(lpg.solve_batch([s], max_iters=64, **opts)[0].x, ref[64])
+        np.testing.assert_array_equal(lpg.solve_batch([s], max_iters=192, batch_split_nnz=0, **opts)[0].x, ref[192])
+        s.update(max_iters=128, **{k: v for k, v in opts.items() if k != "precision"})
+        a = s.solve()
+        np.testing.assert_array_equal(a.x, ref[128])
+        p = s.polish(1e-6, 200)
+        again = np.empty(lp.n)
+        lpg.lp_get_solution(s.h, again)
+        np.testing.assert_array_equal(again, p.x)
+        assert not np.array_equal(p.x, a.x)
