@@ -83,6 +83,13 @@ std::vector<int32_t> build_tiles(int32_t rows, const int32_t* rp, int32_t tn, in
 // (FP32 39 / 29), 2.4M 72 / 63 (62 / 50); beyond, x at 6.4 MB: 111 / 114, y at 6.4 MB: 190 / 219.
 constexpr int64_t kFlatBytes = int64_t(4) << 20;
 
+std::vector<TileRec> tile_recs(const std::vector<int32_t>& tiles, const int32_t* rp) {
+    std::vector<TileRec> out;
+    for (size_t b = 0; b + 1 < tiles.size(); ++b)
+        out.push_back(TileRec{tiles[b], tiles[b + 1], rp[tiles[b]], rp[tiles[b + 1]]});
+    return out;
+}
+
 // Row tiles of one LP's own launches (the shape the tuned table gives is for many LPs per
 // launch): a launch of few tiles is bound by one tile's chain of loads, row sums and
 // stores, which grows with the tile, and a launch of many by their number, so the largest
@@ -90,7 +97,7 @@ constexpr int64_t kFlatBytes = int64_t(4) << 20;
 // 4096, FP64: 32k entries 7.9 / 9.6 / 13.0, 231k 9.2 / 11.1 / 15.2, 993k 23.3 / 20.7 / 19.3). tree_len: rows longer than this are the ones
 // the layout reduces by a workgroup; all others must fit a tile to be summed in order.
 struct FlatTiles {
-    std::vector<int32_t> tiles;
+    std::vector<TileRec> recs;
     int shape = 0, tree_len = 0;
 };
 
@@ -106,7 +113,7 @@ FlatTiles flat_tiles(int32_t rows, const int32_t* rp, int32_t tree_len, int cus)
     F.tree_len = std::min(tree_len, tile_nnz_of(F.shape));
     if (longest > F.tree_len) return F;
     int64_t n_long = 0;
-    F.tiles = build_tiles(rows, rp, tile_nnz_of(F.shape), F.tree_len, &n_long);
+    F.recs = tile_recs(build_tiles(rows, rp, tile_nnz_of(F.shape), F.tree_len, &n_long), rp);
     return F;
 }
 
@@ -221,6 +228,7 @@ bool build_sell(int32_t rows, const int32_t* rp, bool sorted, SellHost* S) {
 // Host-side integer structure of an LP, built once at lp_create.
 struct Prep {
     std::vector<int32_t> rpT, ciT, perm, tA, tAT;
+    std::vector<TileRec> rA, rAT;  // the same tiles as records
     SellHost sA, sAT;  // empty: the LP has no one-workgroup form
     PanelLayoutHost LA, LAT;
     FlatTiles fA[2], fAT[2];  // per layout (no tiles: none)
@@ -256,7 +264,7 @@ struct Offsets {
     size_t fr[6];  // residual restarts: z - T(z) of the last iterate (x, y, A~x parts), then of the anchor
     size_t f32[15] = {0};
     size_t pA[7] = {0}, pAT[7] = {0}, pA32 = 0, pAT32 = 0;
-    size_t fA[2] = {0}, fAT[2] = {0};
+    size_t rA = 0, rAT = 0, fA[2] = {0}, fAT[2] = {0};
     // two-phase: block starts, tile rows, tile chunks, row offsets, deltas, masks, first runs, columns, positions, values, the lists of long and of huge rows
     size_t tpA[12] = {0}, tpAT[12] = {0}, tpbuf = 0;
     size_t sA[5] = {0}, sAT[5] = {0};  // Sell: slice offsets, rows, columns, values, FP32 values
@@ -469,6 +477,7 @@ struct lp_handle {
     int64_t samples = 0;
     std::shared_ptr<Prep> prep;     // shared with the server's per-request clones
     std::shared_ptr<HostData> raw;
+    std::shared_ptr<const std::vector<TileRec>> recs_a, recs_at;  // row tiles, for the maps of block-diagonal launches
     std::vector<int32_t> sell_a, sell_at;  // slice offsets of the Sell matrices (empty: none)
     bool has_x0 = false, has_y0 = false;
     bool deferred = false;
@@ -729,14 +738,14 @@ int32_t finish_batch(lp_handle* const* hs, int count, hipStream_t s, Written&& w
 // padded with entries of the stand-in job `pad_job`. Short lists keep their order.
 constexpr int kXcds = 8;
 
-void append_xcd_order(const std::vector<int2>& tiles, int pad_job, std::vector<int2>& out) {
+void append_xcd_order(const std::vector<MapTile>& tiles, int pad_job, std::vector<MapTile>& out) {
     const size_t len = tiles.size();
     if (len < static_cast<size_t>(4 * kXcds)) {
         out.insert(out.end(), tiles.begin(), tiles.end());
         return;
     }
     const size_t per = (len + kXcds - 1) / kXcds, base = out.size();
-    out.resize(base + per * kXcds, make_int2(pad_job, 0));
+    out.resize(base + per * kXcds, MapTile{pad_job, TileRec{0, 0, 0, 0}});
     for (size_t t = 0; t < len; ++t) out[base + (t % per) * kXcds + t / per] = tiles[t];
 }
 
@@ -772,17 +781,18 @@ struct DevMaps {
         // jobs[count] is a stand-in whose scalar block says "stopped": map entries that pad
         // the XCD runs below point at it and their workgroups return at once
         std::vector<BatchJob> jobs(static_cast<size_t>(count) + 1);
-        std::vector<int2> ma, mat, mred, melem;
+        std::vector<MapTile> ma, mat;
+        std::vector<int2> mred, melem;
         int off_a[kMapGroups], cnt_a[kMapGroups], off_at[kMapGroups], cnt_at[kMapGroups];
         for (int i = 0; i < count; ++i) jobs[i] = make_job(hs[i], o);
         for (int v = 0; v < kMapGroups; ++v) {  // tile maps grouped by form and shape, each in XCD order
-            std::vector<int2> ta, tat;
+            std::vector<MapTile> ta, tat;
             for (int i = 0; i < count; ++i) {
                 const lp_handle* h = hs[i];
                 const int form = (jobs[i].P.fp32 ? 2 : 0) + (jobs[i].P.method ? 1 : 0);
                 if (form * kTileShapes + jobs[i].P.A.csr.shape != v) continue;
-                for (int t = 0; t < h->P.A.csr.ntiles; ++t) ta.push_back(make_int2(i, t));
-                for (int t = 0; t < h->P.AT.csr.ntiles; ++t) tat.push_back(make_int2(i, t));
+                for (const TileRec& t : *h->recs_a) ta.push_back(MapTile{i, t});
+                for (const TileRec& t : *h->recs_at) tat.push_back(MapTile{i, t});
             }
             off_a[v] = static_cast<int>(ma.size());
             off_at[v] = static_cast<int>(mat.size());
@@ -801,8 +811,8 @@ struct DevMaps {
         for (int i = 0; i < count; ++i)
             if (jobs[i].eval_every != E) return fail(err_to, LP_ERR_INVALID_ARG, "block-diagonal LPs must share eval_every");
         Arena L;
-        const size_t oj = L.add(sizeof(BatchJob) * jobs.size()), oa = L.add(sizeof(int2) * ma.size()),
-                     oat = L.add(sizeof(int2) * mat.size()), ored = L.add(sizeof(int2) * mred.size()),
+        const size_t oj = L.add(sizeof(BatchJob) * jobs.size()), oa = L.add(sizeof(MapTile) * ma.size()),
+                     oat = L.add(sizeof(MapTile) * mat.size()), ored = L.add(sizeof(int2) * mred.size()),
                      oel = L.add(sizeof(int2) * melem.size()), ost = L.add(sizeof(int) * (count + 1)),
                      osc = L.add(sizeof(Scalars));
         if (L.off > cap) {
@@ -824,9 +834,9 @@ struct DevMaps {
         M = MultiMaps{};
         M.jobs = reinterpret_cast<const BatchJob*>(buf + oj);
         M.count = count;
-        M.map_a = reinterpret_cast<const int2*>(buf + oa);
+        M.map_a = reinterpret_cast<const MapTile*>(buf + oa);
         M.n_a = static_cast<int>(ma.size());
-        M.map_at = reinterpret_cast<const int2*>(buf + oat);
+        M.map_at = reinterpret_cast<const MapTile*>(buf + oat);
         M.n_at = static_cast<int>(mat.size());
         for (int v = 0; v < kMapGroups; ++v) {
             M.off_a[v] = off_a[v];
@@ -850,8 +860,8 @@ struct DevMaps {
             HIP_TRY(err_to, H2D(osc, &stopped, sizeof(Scalars)));
         }
         HIP_TRY(err_to, H2D(oj, jobs.data(), sizeof(BatchJob) * jobs.size()));
-        HIP_TRY(err_to, H2D(oa, ma.data(), sizeof(int2) * ma.size()));
-        HIP_TRY(err_to, H2D(oat, mat.data(), sizeof(int2) * mat.size()));
+        HIP_TRY(err_to, H2D(oa, ma.data(), sizeof(MapTile) * ma.size()));
+        HIP_TRY(err_to, H2D(oat, mat.data(), sizeof(MapTile) * mat.size()));
         HIP_TRY(err_to, H2D(ored, mred.data(), sizeof(int2) * mred.size()));
         HIP_TRY(err_to, H2D(oel, melem.data(), sizeof(int2) * melem.size()));
         return LP_OK;
@@ -1151,6 +1161,10 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
     const int32_t tn = tile_nnz_of(Q.shape);
     Q.tA = build_tiles(m, rp, tn, tn, &dummy_long);
     Q.tAT = build_tiles(n, Q.rpT.data(), tn, tn, &dummy_long);
+    Q.rA = tile_recs(Q.tA, rp);
+    Q.rAT = tile_recs(Q.tAT, Q.rpT.data());
+    h->recs_a = std::make_shared<const std::vector<TileRec>>(Q.rA);
+    h->recs_at = std::make_shared<const std::vector<TileRec>>(Q.rAT);
     // One-workgroup form: 16-bit columns, LDS for the gathered vectors, short rows, and padding
     // (slices as wide as their longest row) that stays within four times the entries. Rows
     // are sorted where a thread keeps its rows' operands in registers; elsewhere the operands
@@ -1277,9 +1291,11 @@ size_t arena_layout(const lp_handle* h, Offsets* O) {
         }
     }
     for (int l = 0; l < 2; ++l) {
-        O->fA[l] = L.add(sizeof(int32_t) * Q.fA[l].tiles.size());
-        O->fAT[l] = L.add(sizeof(int32_t) * Q.fAT[l].tiles.size());
+        O->fA[l] = L.add(sizeof(TileRec) * Q.fA[l].recs.size());
+        O->fAT[l] = L.add(sizeof(TileRec) * Q.fAT[l].recs.size());
     }
+    O->rA = L.add(sizeof(TileRec) * Q.rA.size());
+    O->rAT = L.add(sizeof(TileRec) * Q.rAT.size());
     size_t tp_slots = 0;
     auto add_tp = [&](const TwoPhaseHost& H, size_t* off) {
         if (!H.tiles()) return;
@@ -1472,9 +1488,9 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     P.nnz = nnz;
     P.nred = Q.nred;
     P.A.csr = Csr{m, ntA, static_cast<int>(nnz), Q.shape, I(O.arp), I(O.aci), D(O.av), I(O.at), nullptr, nullptr, n,
-                  tile_nnz_of(Q.shape)};
+                  tile_nnz_of(Q.shape), reinterpret_cast<const TileRec*>(b + O.rA)};
     P.AT.csr = Csr{n, ntAT, static_cast<int>(nnz), Q.shape, I(O.trp), I(O.tci), D(O.tv), I(O.tt), nullptr, nullptr, m,
-                   tile_nnz_of(Q.shape)};
+                   tile_nnz_of(Q.shape), reinterpret_cast<const TileRec*>(b + O.rAT)};
     P.A.layout = P.AT.layout = panels ? 0 : 1;
     auto bind_layout = [&](const PanelLayoutHost& L, const size_t* off, Mat& M) {
         M.pan = Panels{L.units, L.panels, L.col_bits, static_cast<int>(L.nnz_packed), L.max_unit_rows, I(off[0]), I(off[1]),
@@ -1511,11 +1527,12 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
         }
     }
     auto bind_flat = [&](const FlatTiles& H, size_t off, const Csr& csr, Csr* M) {
-        if (H.tiles.empty()) return;
+        if (H.recs.empty()) return;
         *M = csr;  // (with the FP32 values, bound above)
-        M->ntiles = static_cast<int>(H.tiles.size()) - 1;
+        M->ntiles = static_cast<int>(H.recs.size());
         M->shape = H.shape;
-        M->tiles = I(off);
+        M->tiles = nullptr;
+        M->recs = reinterpret_cast<const TileRec*>(b + off);
         M->tree_len = H.tree_len;
     };
     for (int l = 0; l < 2; ++l) {
@@ -1639,9 +1656,11 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
         HIP_TRY(h, upload_layout(Q.LAT, O.pAT));
     }
     for (int l = 0; l < 2; ++l) {
-        HIP_TRY(h, H2D(I(O.fA[l]), Q.fA[l].tiles.data(), sizeof(int32_t) * Q.fA[l].tiles.size()));
-        HIP_TRY(h, H2D(I(O.fAT[l]), Q.fAT[l].tiles.data(), sizeof(int32_t) * Q.fAT[l].tiles.size()));
+        HIP_TRY(h, H2D(b + O.fA[l], Q.fA[l].recs.data(), sizeof(TileRec) * Q.fA[l].recs.size()));
+        HIP_TRY(h, H2D(b + O.fAT[l], Q.fAT[l].recs.data(), sizeof(TileRec) * Q.fAT[l].recs.size()));
     }
+    HIP_TRY(h, H2D(b + O.rA, Q.rA.data(), sizeof(TileRec) * Q.rA.size()));
+    HIP_TRY(h, H2D(b + O.rAT, Q.rAT.data(), sizeof(TileRec) * Q.rAT.size()));
     if (sell) {
         HIP_TRY(h, H2D(I(O.sA[0]), Q.sA.ptr.data(), sizeof(int32_t) * Q.sA.ptr.size()));
         HIP_TRY(h, H2D(I(O.sA[1]), Q.sA.row.data(), sizeof(int32_t) * Q.sA.row.size()));
@@ -1757,6 +1776,8 @@ lp_handle* clone_for_request(const lp_handle* t) {
     h->arena_bytes = t->arena_bytes;
     h->prep = t->prep;
     h->raw = t->raw;
+    h->recs_a = t->recs_a;
+    h->recs_at = t->recs_at;
     h->sell_a = t->sell_a;
     h->sell_at = t->sell_at;
     h->has_x0 = t->has_x0;

@@ -53,8 +53,15 @@ struct Scalars {
     int ray_src;       // candidate ray of a certificate: 1 displacement since the previous evaluation, 2 anchored average
 };
 
+// A row tile: rows [r0, r1), entries [p0, p1).
+struct TileRec {
+    int r0, r1, p0, p1;
+};
+
 // CSR matrix with its LDS tiling: tile b covers rows [tiles[b], tiles[b+1]), or, when
-// rowlist is set, the single row rowlist[b].
+// rowlist is set, the single row rowlist[b]. The launches read a tile's bounds from recs in
+// one load: offset by offset (tiles, then row pointers) they are two more links in the chain of
+// loads that such a short-lived workgroup is bound by.
 struct Csr {
     int rows;
     int ntiles;
@@ -68,6 +75,7 @@ struct Csr {
     const float* v32;  // FP32 copy of v (FP32 storage form only)
     int cols;          // length of the vector the products gather from
     int tree_len;      // rows longer than this are reduced by a whole workgroup (at most the tile's nonzeros)
+    const TileRec* recs;
 };
 
 // Panel-packed layout (see lp_layout.h): unit u (one wave) owns rows
@@ -143,7 +151,7 @@ struct Mat {
     const int* longrows;
     int layout;  // 0 panels, 1 row tiles
     // Row tiles for the launches of one LP, per layout, reducing by a workgroup the rows that the
-    // layout does (null tiles: none, see flat_tiles).
+    // layout does (null recs: none, see flat_tiles).
     Csr flat[2];
     TwoPhase tp;  // panel layout, vectors beyond the L2: in place of the panels' sweep
 };
@@ -228,12 +236,16 @@ struct BatchJob {
 };
 
 // Block maps of a block-diagonal batch: entry b of a map is (LP index, tile or block of it).
+struct MapTile {
+    int job;
+    TileRec tile;
+};
 struct MultiMaps {
     const BatchJob* jobs;
     int count;
-    const int2* map_a;    // row tiles of every A
+    const MapTile* map_a;    // row tiles of every A
     int n_a;
-    const int2* map_at;   // row tiles of every A^T
+    const MapTile* map_at;   // row tiles of every A^T
     int n_at;
     const int2* map_red;  // reduction blocks (nred per LP)
     int n_red;

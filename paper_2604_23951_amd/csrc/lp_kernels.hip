@@ -234,11 +234,10 @@ __device__ inline T row_sum(const T* prod, int q, int qe) {
 }
 
 template <int TN, class T, class Epi>
-__device__ void tile_body(const Csr& M, int b, const T* __restrict__ xin, const Epi& epi, T* prod, double* red) {
+__device__ void tile_body(const Csr& M, const TileRec& tile, const T* __restrict__ xin, const Epi& epi, T* prod, double* red) {
     constexpr int kPerThread = TN / kBlock;
     constexpr int kRowsPerThread = TN / 4 / kBlock;
-    const int r0 = M.tiles[b], r1 = M.tiles[b + 1];
-    const int p0 = M.rp[r0], p1 = M.rp[r1];
+    const int r0 = tile.r0, r1 = tile.r1, p0 = tile.p0, p1 = tile.p1;
     const int tid = threadIdx.x;
     const int* __restrict__ ci = M.ci;
     const T* __restrict__ av = vals_of<T>(M);
@@ -288,9 +287,11 @@ __device__ void tile_body(const Csr& M, int b, const T* __restrict__ xin, const 
 template <class T, class Epi>
 __device__ inline void tile_body_any(const Csr& M, int b, const T* __restrict__ xin, const Epi& epi, T* prod,
                                      double* red) {
-    if (M.shape == 0) tile_body<tile_nnz_of(0)>(M, b, xin, epi, prod, red);
-    else if (M.shape == 1) tile_body<tile_nnz_of(1)>(M, b, xin, epi, prod, red);
-    else tile_body<tile_nnz_of(2)>(M, b, xin, epi, prod, red);
+    const int r0 = M.tiles[b], r1 = M.tiles[b + 1];
+    const TileRec tile{r0, r1, M.rp[r0], M.rp[r1]};
+    if (M.shape == 0) tile_body<tile_nnz_of(0)>(M, tile, xin, epi, prod, red);
+    else if (M.shape == 1) tile_body<tile_nnz_of(1)>(M, tile, xin, epi, prod, red);
+    else tile_body<tile_nnz_of(2)>(M, tile, xin, epi, prod, red);
 }
 
 template <class T, class Epi, int TN>
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(kBlock) void spmv_tiles_kernel(Csr M, const T* __re
     __shared__ T prod[TN];
     __shared__ double red[kBlock / 64];
     if (!epi.begin()) return;
-    tile_body<TN>(M, static_cast<int>(blockIdx.x), xin, epi, prod, red);
+    tile_body<TN>(M, M.recs[blockIdx.x], xin, epi, prod, red);
 }
 
 // Panel-packed SpMV over wave units of rows. The entries of a unit are walked in packed order,
@@ -1163,7 +1164,7 @@ void launch_spmv(const Mat& M, const T* xin, const Epi& epi, hipStream_t s) {
                            xin, epi);
         return;
     }
-    if (M.flat[M.layout].tiles) {
+    if (M.flat[M.layout].recs) {
         launch_tiles(M.flat[M.layout], xin, epi, s);
         return;
     }
@@ -2381,31 +2382,31 @@ enum MultiKind { MK_PRIMAL = 0, MK_DUAL, MK_AX_ALL, MK_AX_FP32, MK_ATY, MK_AXA, 
 
 // One row tile with an epilogue whose begin() may decline the work (LP stopped).
 template <int TN, class T, class Epi>
-__device__ inline void run_tile(const Csr& M, int b, const T* xin, Epi e, T* prod, double* red) {
+__device__ inline void run_tile(const Csr& M, const TileRec& tile, const T* xin, Epi e, T* prod, double* red) {
     if (!e.begin()) return;
-    tile_body<TN>(M, b, xin, e, prod, red);
+    tile_body<TN>(M, tile, xin, e, prod, red);
 }
 
 // FORM = 2 * fp32 + method for the iteration kinds (one instance per form: the four fused
 // epilogues in one kernel would hold the registers of the largest and halve occupancy), -1
 // for the evaluation products; TN the row-tile shape of the LPs of the launch.
 template <int KIND, int FORM, int TN>
-__global__ __launch_bounds__(kBlock) void multi_tiles_kernel(const BatchJob* jobs, const int2* map, int it) {
+__global__ __launch_bounds__(kBlock) void multi_tiles_kernel(const BatchJob* jobs, const MapTile* map, int it) {
     __shared__ double lds[TN];
     __shared__ double red[kBlock / 64];
-    const int2 mt = map[blockIdx.x];
-    const DevLP& P = jobs[mt.x].P;
+    const MapTile mt = map[blockIdx.x];
+    const DevLP& P = jobs[mt.job].P;
     float* lds32 = reinterpret_cast<float*>(lds);
     if constexpr (KIND == MK_PRIMAL) {
-        if constexpr (FORM == 3) run_tile<TN>(P.AT.csr, mt.y, static_cast<const float*>(P.dy), epi_primal32_h(P, P.sc, it), lds32, red);
-        else if constexpr (FORM == 2) run_tile<TN>(P.AT.csr, mt.y, static_cast<const float*>(P.dy), epi_primal32(P, P.sc, it), lds32, red);
-        else if constexpr (FORM == 1) run_tile<TN>(P.AT.csr, mt.y, static_cast<const double*>(P.y), epi_primal_h(P, P.sc, it), lds, red);
-        else run_tile<TN>(P.AT.csr, mt.y, static_cast<const double*>(P.y), epi_primal(P, P.sc, it), lds, red);
+        if constexpr (FORM == 3) run_tile<TN>(P.AT.csr, mt.tile, static_cast<const float*>(P.dy), epi_primal32_h(P, P.sc, it), lds32, red);
+        else if constexpr (FORM == 2) run_tile<TN>(P.AT.csr, mt.tile, static_cast<const float*>(P.dy), epi_primal32(P, P.sc, it), lds32, red);
+        else if constexpr (FORM == 1) run_tile<TN>(P.AT.csr, mt.tile, static_cast<const double*>(P.y), epi_primal_h(P, P.sc, it), lds, red);
+        else run_tile<TN>(P.AT.csr, mt.tile, static_cast<const double*>(P.y), epi_primal(P, P.sc, it), lds, red);
     } else if constexpr (KIND == MK_DUAL) {
-        if constexpr (FORM == 3) run_tile<TN>(P.A.csr, mt.y, static_cast<const float*>(P.dxa), epi_dual32_h(P, P.sc, it), lds32, red);
-        else if constexpr (FORM == 2) run_tile<TN>(P.A.csr, mt.y, static_cast<const float*>(P.dx), epi_dual32(P, P.sc, it), lds32, red);
-        else if constexpr (FORM == 1) run_tile<TN>(P.A.csr, mt.y, static_cast<const double*>(P.xa), epi_dual_h(P, P.sc, it), lds, red);
-        else run_tile<TN>(P.A.csr, mt.y, static_cast<const double*>(P.x), epi_dual(P, P.sc, it), lds, red);
+        if constexpr (FORM == 3) run_tile<TN>(P.A.csr, mt.tile, static_cast<const float*>(P.dxa), epi_dual32_h(P, P.sc, it), lds32, red);
+        else if constexpr (FORM == 2) run_tile<TN>(P.A.csr, mt.tile, static_cast<const float*>(P.dx), epi_dual32(P, P.sc, it), lds32, red);
+        else if constexpr (FORM == 1) run_tile<TN>(P.A.csr, mt.tile, static_cast<const double*>(P.xa), epi_dual_h(P, P.sc, it), lds, red);
+        else run_tile<TN>(P.A.csr, mt.tile, static_cast<const double*>(P.x), epi_dual(P, P.sc, it), lds, red);
     } else {
         if (P.sc->status != kRunning) return;
         if (KIND == MK_AX_FP32 && (!P.fp32 || P.method)) return;
@@ -2416,7 +2417,7 @@ __global__ __launch_bounds__(kBlock) void multi_tiles_kernel(const BatchJob* job
         const bool onA = KIND == MK_AX_ALL || KIND == MK_AX_FP32 || KIND == MK_AXA;
         const double* xin = KIND == MK_ATY ? P.y : KIND == MK_ATYA ? P.ya : KIND == MK_AXA ? P.xa : P.x;
         double* out = KIND == MK_ATY ? P.aty : KIND == MK_ATYA ? P.atya : KIND == MK_AXA ? P.axa : P.ax;
-        tile_body<TN>(onA ? P.A.csr : P.AT.csr, mt.y, xin, EpiStore{out, nullptr}, lds, red);
+        tile_body<TN>(onA ? P.A.csr : P.AT.csr, mt.tile, xin, EpiStore{out, nullptr}, lds, red);
     }
 }
 
@@ -2689,7 +2690,7 @@ template <int KIND, int FORM>
 void multi_tiles_group(const MultiMaps& M, int g, bool on_a, int it_or_mode, hipStream_t s) {
     const int n = on_a ? M.cnt_a[g] : M.cnt_at[g];
     if (n <= 0) return;
-    const int2* map = on_a ? M.map_a + M.off_a[g] : M.map_at + M.off_at[g];
+    const MapTile* map = on_a ? M.map_a + M.off_a[g] : M.map_at + M.off_at[g];
     switch (g % kTileShapes) {
         case 0: hipLaunchKernelGGL((multi_tiles_kernel<KIND, FORM, tile_nnz_of(0)>), dim3(n), dim3(kBlock), 0, s, M.jobs, map, it_or_mode); break;
         case 1: hipLaunchKernelGGL((multi_tiles_kernel<KIND, FORM, tile_nnz_of(1)>), dim3(n), dim3(kBlock), 0, s, M.jobs, map, it_or_mode); break;
