@@ -79,8 +79,8 @@ std::vector<int32_t> build_tiles(int32_t rows, const int32_t* rp, int32_t tn, in
 // unless a panel width was asked for. The gathers hit the L2 in any order then, and the panel
 // units (a few hundred entries per wave and step, a barrier after each, ~20 us however small
 // the matrix) only cost latency. us per iteration, Halpern form, panels / row tiles: 32k
-// entries 11.8 / 7.8, dense rows with 993k (FP64) 57 / 17, power-law columns with 1.2M 48 / 38
-// (FP32 39 / 29), 2.4M 72 / 63 (62 / 50); beyond, x at 6.4 MB: 111 / 114, y at 6.4 MB: 190 / 219.
+// entries 11.8 / 7.8, dense rows with 993k (FP64) 57 / 16, power-law columns with 1.2M 48 / 38
+// (FP32 39 / 29), 2.4M 72 / 57 (62 / 50); beyond, x at 6.4 MB: 111 / 114, y at 6.4 MB: 190 / 219.
 constexpr int64_t kFlatBytes = int64_t(4) << 20;
 
 std::vector<TileRec> tile_recs(const std::vector<int32_t>& tiles, const int32_t* rp) {
@@ -134,7 +134,7 @@ struct TwoPhaseHost {
 // gathered vector that does not fit an XCD's L2, or one of 1.5 MB and more (the gathers miss
 // L1 and queue for the L2) with enough entries to pay for the second launch. us per iteration,
 // Halpern form, row tiles or panels / two phases: 2.4M entries, x of 3.2 MB, FP64 63 / 70, FP32
-// 50 / 51; 4.8M 110 / 98, 82 / 70; 7.2M 150 / 135, 121 / 89; 1.2e7 232 / 206, 190 / 134; 1.7M
+// 50 / 51; 4.8M 110 / 86, 82 / 61; 7.2M 150 / 138, 121 / 80; 1.2e7 232 / 207, 190 / 137; 1.7M
 // with vectors below 1.8 MB 38 / 57, 29 / 41.
 bool two_phase_pays(int64_t vector_bytes, int64_t nnz) {
     return vector_bytes > kFlatBytes || (vector_bytes >= (int64_t(3) << 19) && nnz >= 3000000);
@@ -1562,6 +1562,7 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
         T.v = D(off[9]);
         T.v32 = fp32 ? reinterpret_cast<const float*>(D(off[9]) + H.slots()) : nullptr;
         T.is_long = M.pan.is_long;
+        T.keep = nnz * (fp32 ? 20LL : 32LL) <= kTpKeepBytes ? 1 : 0;
         T.tiles_short = H.tiles_short;
         T.longs = I(off[10]);
         T.nhuge = static_cast<int>(H.huge.size());

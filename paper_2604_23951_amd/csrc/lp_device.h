@@ -115,6 +115,7 @@ struct TwoPhase {
     const unsigned short *lcol, *pos;
     const double* v;
     const float* v32;
+    int keep;                      // plain loads of the matrix (see kTpKeepBytes), else non-temporal ones
     const unsigned char* is_long;  // as in Panels
     const int* longs;
     int nhuge;          // rows longer than a tile, each reduced by a workgroup from its gathers
@@ -124,6 +125,10 @@ struct TwoPhase {
 constexpr int kTpMaxBlocks = 1024;
 constexpr int kTpSplit = 2;  // workgroups that share a block's entries
 constexpr int kTpXcds = 8;
+// What an iteration streams (entries of both matrices, the products) up to which plain loads,
+// which may stay in the 256 MB Infinity Cache, beat non-temporal ones. us per iteration, plain /
+// non-temporal: 144 MB 80 / 91, 154 MB 86 / 99, 230 MB 144 / 138, 240 MB 140 / 137, 384 MB 209 / 207.
+constexpr long long kTpKeepBytes = 192LL << 20;
 constexpr int kTpLds = 64 * 1024;      // of the gathered slice at most
 constexpr int kTpTileLds = 64 * 1024;  // of a tile's products at most (FP64)
 constexpr int kTpTileLds32 = 39 * 1024;  // (FP32)

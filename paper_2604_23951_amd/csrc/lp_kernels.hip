@@ -233,7 +233,19 @@ __device__ inline T row_sum(const T* prod, int q, int qe) {
     return s;
 }
 
-template <int TN, class T, class Epi>
+// A load of matrix entries that may (KEEP) or may not displace what the caches hold.
+template <bool KEEP, class T>
+__device__ __forceinline__ T stream_load(const T* p) {
+    if constexpr (KEEP) return *p;
+    else return __builtin_nontemporal_load(p);
+}
+
+// KEEP: matrices that the 256 MB Infinity Cache holds from one iteration to the next are read
+// with plain loads, which may stay in it (us per iteration, non-temporal / plain: 22 LPs with
+// 5.5M entries together, FP32, 44 / 38; FP64, single: 993k entries 17.2 / 16.2, 1.7M 38.7 / 35.2,
+// 2.4M 62.0 / 57.1). A single FP32 launch keeps the non-temporal loads: its smaller matrix
+// then competes with the gathered vectors for the L2 (1.7M entries 29.3 / 30.2).
+template <int TN, bool KEEP, class T, class Epi>
 __device__ void tile_body(const Csr& M, const TileRec& tile, const T* __restrict__ xin, const Epi& epi, T* prod, double* red) {
     constexpr int kPerThread = TN / kBlock;
     constexpr int kRowsPerThread = TN / 4 / kBlock;
@@ -250,8 +262,8 @@ __device__ void tile_body(const Csr& M, const TileRec& tile, const T* __restrict
 #pragma unroll
         for (int k = 0; k < kPerThread; ++k) {
             const int e = min(p0 + tid + k * kBlock, elast);
-            col[k] = __builtin_nontemporal_load(ci + e);
-            val[k] = __builtin_nontemporal_load(av + e);
+            col[k] = stream_load<KEEP>(ci + e);
+            val[k] = stream_load<KEEP>(av + e);
         }
         typename Epi::Pre pre[kRowsPerThread];
         int q0[kRowsPerThread], q1[kRowsPerThread];
@@ -289,9 +301,9 @@ __device__ inline void tile_body_any(const Csr& M, int b, const T* __restrict__ 
                                      double* red) {
     const int r0 = M.tiles[b], r1 = M.tiles[b + 1];
     const TileRec tile{r0, r1, M.rp[r0], M.rp[r1]};
-    if (M.shape == 0) tile_body<tile_nnz_of(0)>(M, tile, xin, epi, prod, red);
-    else if (M.shape == 1) tile_body<tile_nnz_of(1)>(M, tile, xin, epi, prod, red);
-    else tile_body<tile_nnz_of(2)>(M, tile, xin, epi, prod, red);
+    if (M.shape == 0) tile_body<tile_nnz_of(0), false>(M, tile, xin, epi, prod, red);
+    else if (M.shape == 1) tile_body<tile_nnz_of(1), false>(M, tile, xin, epi, prod, red);
+    else tile_body<tile_nnz_of(2), false>(M, tile, xin, epi, prod, red);
 }
 
 template <class T, class Epi, int TN>
@@ -299,7 +311,7 @@ __global__ __launch_bounds__(kBlock) void spmv_tiles_kernel(Csr M, const T* __re
     __shared__ T prod[TN];
     __shared__ double red[kBlock / 64];
     if (!epi.begin()) return;
-    tile_body<TN>(M, M.recs[blockIdx.x], xin, epi, prod, red);
+    tile_body<TN, sizeof(T) == 8>(M, M.recs[blockIdx.x], xin, epi, prod, red);
 }
 
 // Panel-packed SpMV over wave units of rows. The entries of a unit are walked in packed order,
@@ -2384,7 +2396,7 @@ enum MultiKind { MK_PRIMAL = 0, MK_DUAL, MK_AX_ALL, MK_AX_FP32, MK_ATY, MK_AXA, 
 template <int TN, class T, class Epi>
 __device__ inline void run_tile(const Csr& M, const TileRec& tile, const T* xin, Epi e, T* prod, double* red) {
     if (!e.begin()) return;
-    tile_body<TN>(M, tile, xin, e, prod, red);
+    tile_body<TN, true>(M, tile, xin, e, prod, red);
 }
 
 // FORM = 2 * fp32 + method for the iteration kinds (one instance per form: the four fused
@@ -2417,7 +2429,7 @@ __global__ __launch_bounds__(kBlock) void multi_tiles_kernel(const BatchJob* job
         const bool onA = KIND == MK_AX_ALL || KIND == MK_AX_FP32 || KIND == MK_AXA;
         const double* xin = KIND == MK_ATY ? P.y : KIND == MK_ATYA ? P.ya : KIND == MK_AXA ? P.xa : P.x;
         double* out = KIND == MK_ATY ? P.aty : KIND == MK_ATYA ? P.atya : KIND == MK_AXA ? P.axa : P.ax;
-        tile_body<TN>(onA ? P.A.csr : P.AT.csr, mt.tile, xin, EpiStore{out, nullptr}, lds, red);
+        tile_body<TN, true>(onA ? P.A.csr : P.AT.csr, mt.tile, xin, EpiStore{out, nullptr}, lds, red);
     }
 }
 

@@ -52,23 +52,27 @@ __global__ __launch_bounds__(kTpThreads) void tp_products_kernel(TwoPhase M, con
     V* __restrict__ out = reinterpret_cast<V*>(M.buf);
     for (int j = tid; j < width; j += kTpThreads) g[j] = xin[c0 + j];
     __syncthreads();
-    for (int i = i0 + tid; i < i1; i += kTpThreads * kTpUnroll) {
-        V v[kTpUnroll];
-        Cols c[kTpUnroll];
+    auto stream = [&](auto keep) {
+        for (int i = i0 + tid; i < i1; i += kTpThreads * kTpUnroll) {
+            V v[kTpUnroll];
+            Cols c[kTpUnroll];
 #pragma unroll
-        for (int k = 0; k < kTpUnroll; ++k) {
-            const int q = min(i + k * kTpThreads, i1 - 1);
-            v[k] = __builtin_nontemporal_load(vp + q);
-            c[k] = __builtin_nontemporal_load(cp + q);
+            for (int k = 0; k < kTpUnroll; ++k) {
+                const int q = min(i + k * kTpThreads, i1 - 1);
+                v[k] = stream_load<keep.value>(vp + q);
+                c[k] = stream_load<keep.value>(cp + q);
+            }
+#pragma unroll
+            for (int k = 0; k < kTpUnroll; ++k) {
+                V p;
+#pragma unroll
+                for (int e = 0; e < N; ++e) p[e] = v[k][e] * g[checked_index(static_cast<int>(c[k][e]), width, 1u)];
+                if (i + k * kTpThreads < i1) out[i + k * kTpThreads] = p;
+            }
         }
-#pragma unroll
-        for (int k = 0; k < kTpUnroll; ++k) {
-            V p;
-#pragma unroll
-            for (int e = 0; e < N; ++e) p[e] = v[k][e] * g[checked_index(static_cast<int>(c[k][e]), width, 1u)];
-            if (i + k * kTpThreads < i1) out[i + k * kTpThreads] = p;
-        }
-    }
+    };
+    if (M.keep) stream(std::true_type{});
+    else stream(std::false_type{});
 }
 
 // Phase 2: one tile of rows per workgroup. The tiles of long rows (the last ones, numbered
@@ -120,30 +124,34 @@ __global__ __launch_bounds__(kTpThreads, 6) void tp_rows_kernel(TwoPhase M, Csr 
         }
     }
     constexpr int U = 8;
-    for (int i = 0; wave + i * kWaves < chunks; i += U) {  // the wave's chunks i, i + 1, ...
-        int src[U];
-        unsigned short pos[U];
-        T v[U];
+    auto fetch = [&](auto keep) {
+        for (int i = 0; wave + i * kWaves < chunks; i += U) {  // the wave's chunks i, i + 1, ...
+            int src[U];
+            unsigned short pos[U];
+            T v[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int at = min(i + k, 63);
-            const unsigned lo = __builtin_amdgcn_readlane(static_cast<unsigned>(mask_l), at);
-            const unsigned hi = __builtin_amdgcn_readlane(static_cast<unsigned>(mask_l >> 32), at);
-            const int first = __builtin_amdgcn_readlane(first_l, at);
-            const int c = min(wave + (i + k) * kWaves, chunks - 1);
-            const int run = first + __popcll(((static_cast<unsigned long long>(hi) << 32) | lo) & upto) - 1;
-            const int e = min(c * 64 + lane, count - 1);
-            src[k] = e + delta[min(max(run, 0), M.blocks - 1)];
-            pos[k] = __builtin_nontemporal_load(posp + e);
+            for (int k = 0; k < U; ++k) {
+                const int at = min(i + k, 63);
+                const unsigned lo = __builtin_amdgcn_readlane(static_cast<unsigned>(mask_l), at);
+                const unsigned hi = __builtin_amdgcn_readlane(static_cast<unsigned>(mask_l >> 32), at);
+                const int first = __builtin_amdgcn_readlane(first_l, at);
+                const int c = min(wave + (i + k) * kWaves, chunks - 1);
+                const int run = first + __popcll(((static_cast<unsigned long long>(hi) << 32) | lo) & upto) - 1;
+                const int e = min(c * 64 + lane, count - 1);
+                src[k] = e + delta[min(max(run, 0), M.blocks - 1)];
+                pos[k] = stream_load<keep.value>(posp + e);
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) v[k] = buf[checked_index(max(0, min(src[k], M.slots - 1)), M.slots, 1u)];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int c = wave + (i + k) * kWaves;
+                if (c < chunks && c * 64 + lane < count) prod[checked_index(static_cast<int>(pos[k]), M.tile_nnz, 2u)] = v[k];
+            }
         }
-#pragma unroll
-        for (int k = 0; k < U; ++k) v[k] = buf[checked_index(max(0, min(src[k], M.slots - 1)), M.slots, 1u)];
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int c = wave + (i + k) * kWaves;
-            if (c < chunks && c * 64 + lane < count) prod[checked_index(static_cast<int>(pos[k]), M.tile_nnz, 2u)] = v[k];
-        }
-    }
+    };
+    if (M.keep) fetch(std::true_type{});
+    else fetch(std::false_type{});
     __syncthreads();
     if (longs) {
         // as row_tree_body: thread t of kBlock adds the row's products t, t + kBlock, ... in
