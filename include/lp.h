@@ -123,7 +123,9 @@ typedef struct lp_options {
     void *hip_stream;      /* hipStream_t to run on; NULL: the library creates its own */
     int32_t device;        /* HIP device ordinal (default 0) */
     int32_t trace_cap;     /* number of evaluation records kept for lp_get_trace (default 4096) */
-    int32_t spmv_layout;   /* sparse-product layout: 0 panel-packed wave units (default), 1 row tiles,
+    int32_t spmv_layout;   /* sparse-product layout: 0 panel-packed wave units (default; matrices whose
+                            * gathered vector is short run as row tiles and large ones in two
+                            * phases unless panel_slice_bytes is set, with the same sums), 1 row tiles,
                             * 2 tuned: both are built and timed on the device at set-up (a few
                             * products each, on scratch buffers) and the faster one is kept; the
                             * choice depends on the measurement, so two handles of one LP may
@@ -140,14 +142,17 @@ typedef struct lp_options {
                               allocated (and the setup run) when the LP is first solved or admitted
                               by a server, and released by the server when it completes (default 0) */
     int32_t small_lp_lds;  /* bytes of LDS per workgroup (0 to 114688, default 114688) for LPs
-                              held on chip. lp_solve_batch: an LP of the persistent launch whose
-                              matrices and iteration vectors (in its precision) fit is solved from
-                              LDS by a launch of its own (one workgroup per CU), bit-identical to
-                              the solve from global memory. lp_solve: such an LP is solved by one
-                              workgroup from LDS (the whole loop in one launch, the row-tile
-                              products; not with kernel timing on, and not for lp_polish's
-                              solves), bit-identical to the kernel-per-phase loop with row tiles
-                              (lp_info.solve_path = 1). 0 turns both off */
+                              held on chip. Batched solves: an LP of the persistent launches is
+                              solved by one workgroup with as much of its matrices in LDS as fits
+                              beside the vectors that are gathered, bit-identical to the solve
+                              with all of them in global memory. lp_solve: an LP whose matrices
+                              fit (16-bit columns, rows of at most 128 entries; or, as row tiles,
+                              matrices and iteration vectors) is solved by one workgroup (the
+                              whole loop in one launch, the row-tile sums; not with kernel timing
+                              on, and not for lp_polish's solves), bit-identical to the
+                              kernel-per-phase loop with row tiles (lp_info.solve_path = 1);
+                              stopped by its time limit it returns objectives summed in index
+                              order. 0 turns both off */
     const double *x0;      /* optional warm start (host, length n, original scale) */
     const double *y0;      /* optional warm start (host, length m, original scale) */
     double eps_infeas;     /* relative tolerance of the infeasibility certificates (default 1e-8;
@@ -272,8 +277,8 @@ int32_t lp_create(lp_handle **out, int32_t m, int32_t n, int64_t nnz, const int3
 
 /* Run restarted PDHG (the form of opt->method) from the start point until E_rel <= eps_rel,
  * a certificate or a limit. Every call starts again from x0, y0 (the handle keeps the
- * problem, not the iterates). An LP whose iteration arrays fit small_lp_lds bytes of LDS
- * runs the whole loop on one workgroup in one launch; any other runs one kernel per phase,
+ * problem, not the iterates). An LP that small_lp_lds admits (see there) runs the whole
+ * loop on one workgroup in one launch; any other runs one or two kernels per phase,
  * an evaluation period (eval_every iterations, the evaluation, the decision) per hipGraph
  * replay, the host reading the status once per period. lp_info.solve_path says which. */
 int32_t lp_solve(lp_handle *h);

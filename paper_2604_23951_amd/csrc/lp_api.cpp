@@ -136,7 +136,10 @@ struct TwoPhaseHost {
 // Halpern form, row tiles or panels / two phases: 2.4M entries, x of 3.2 MB, FP64 63 / 70, FP32
 // 50 / 51; 4.8M 110 / 86, 82 / 61; 7.2M 150 / 138, 121 / 80; 1.2e7 232 / 207, 190 / 137; 1.7M
 // with vectors below 1.8 MB 38 / 57, 29 / 41.
+// Not beyond 2^29 entries: the 32 (FP64) or 36 bytes per entry that the two matrices' layouts
+// and the products take more could be what no longer fits.
 bool two_phase_pays(int64_t vector_bytes, int64_t nnz) {
+    if (nnz > (int64_t(1) << 29)) return false;
     return vector_bytes > kFlatBytes || (vector_bytes >= (int64_t(3) << 19) && nnz >= 3000000);
 }
 
@@ -1199,9 +1202,12 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
         const bool any_width = slice == (int64_t(1) << 19);
         if (Q.LA.panels == 1 || (any_width && sv * n <= kFlatBytes)) Q.fA[0] = flat_tiles(m, rp, long_len, cus);
         if (Q.LAT.panels == 1 || (any_width && sv * m <= kFlatBytes)) Q.fAT[0] = flat_tiles(n, Q.rpT.data(), long_len, cus);
-        if (any_width && two_phase_pays(sv * n, nnz) && !build_two_phase(m, n, rp, Q.LA.is_long, sv == 4, cus, &Q.tpA))
+        // not for deferred handles: servers and batches iterate with row tiles, and the layout
+        // would count against a server's budget
+        const bool two = any_width && !h->deferred;
+        if (two && two_phase_pays(sv * n, nnz) && !build_two_phase(m, n, rp, Q.LA.is_long, sv == 4, cus, &Q.tpA))
             Q.tpA = {};
-        if (any_width && two_phase_pays(sv * m, nnz) &&
+        if (two && two_phase_pays(sv * m, nnz) &&
             !build_two_phase(n, m, Q.rpT.data(), Q.LAT.is_long, sv == 4, cus, &Q.tpAT))
             Q.tpAT = {};
     }
