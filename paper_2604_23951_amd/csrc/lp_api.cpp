@@ -75,14 +75,6 @@ std::vector<int32_t> build_tiles(int32_t rows, const int32_t* rp, int32_t tn, in
     return t;
 }
 
-// Panel layout: a matrix whose gathered vector fits one XCD's 4 MB L2 is swept as row tiles
-// unless a panel width was asked for. The gathers hit the L2 in any order then, and the panel
-// units (a few hundred entries per wave and step, a barrier after each, ~20 us however small
-// the matrix) only cost latency. us per iteration, Halpern form, panels / row tiles: 32k
-// entries 11.8 / 7.8, dense rows with 993k (FP64) 57 / 16, power-law columns with 1.2M 48 / 38
-// (FP32 39 / 29), 2.4M 72 / 57 (62 / 50); beyond, x at 6.4 MB: 111 / 114, y at 6.4 MB: 190 / 219.
-constexpr int64_t kFlatBytes = int64_t(4) << 20;
-
 std::vector<TileRec> tile_recs(const std::vector<int32_t>& tiles, const int32_t* rp) {
     std::vector<TileRec> out;
     for (size_t b = 0; b + 1 < tiles.size(); ++b)
@@ -136,8 +128,8 @@ struct TwoPhaseHost {
 // Halpern form, row tiles or panels / two phases: 2.4M entries, x of 3.2 MB, FP64 63 / 70, FP32
 // 50 / 51; 4.8M 110 / 86, 82 / 61; 7.2M 150 / 138, 121 / 80; 1.2e7 232 / 207, 190 / 137; 1.7M
 // with vectors below 1.8 MB 38 / 57, 29 / 41.
-// Not beyond 2^29 entries: the 32 (FP64) or 36 bytes per entry that the two matrices' layouts
-// and the products take more could be what no longer fits.
+// Not beyond 2^29 entries: the 32 (FP32 storage: 20) bytes per entry that the two matrices'
+// layouts and the products take more could be what no longer fits.
 bool two_phase_pays(int64_t vector_bytes, int64_t nnz) {
     if (nnz > (int64_t(1) << 29)) return false;
     return vector_bytes > kFlatBytes || (vector_bytes >= (int64_t(3) << 19) && nnz >= 3000000);
@@ -1200,8 +1192,8 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
         h->panels_at = Q.LAT.panels;
         const int64_t sv = o.precision == LP_PREC_FP32_REFINED ? 4 : 8;
         const bool any_width = slice == (int64_t(1) << 19);
-        if (Q.LA.panels == 1 || (any_width && sv * n <= kFlatBytes)) Q.fA[0] = flat_tiles(m, rp, long_len, cus);
-        if (Q.LAT.panels == 1 || (any_width && sv * m <= kFlatBytes)) Q.fAT[0] = flat_tiles(n, Q.rpT.data(), long_len, cus);
+        if ((Q.LA.panels == 1 || any_width) && sv * n <= kFlatBytes) Q.fA[0] = flat_tiles(m, rp, long_len, cus);
+        if ((Q.LAT.panels == 1 || any_width) && sv * m <= kFlatBytes) Q.fAT[0] = flat_tiles(n, Q.rpT.data(), long_len, cus);
         // not for deferred handles: servers and batches iterate with row tiles, and the layout
         // would count against a server's budget
         const bool two = any_width && !h->deferred;
@@ -1307,7 +1299,7 @@ size_t arena_layout(const lp_handle* h, Offsets* O) {
         if (!H.tiles()) return;
         const size_t bytes[12] = {4 * (static_cast<size_t>(H.blocks) + 1), 4 * H.tile_row.size(), 4 * H.tile_chunk.size(),
                                   4 * H.trp.size(), 4 * H.cells(), 8 * (H.chunks() + 1), 4 * (H.chunks() + 1), 2 * H.slots(),
-                                  2 * 64 * H.chunks(), (fp32 ? 12 : 8) * H.slots(), 4 * H.longs.size(), 4 * H.huge.size()};
+                                  2 * 64 * H.chunks(), (fp32 ? 4 : 8) * H.slots(), 4 * H.longs.size(), 4 * H.huge.size()};
         for (int i = 0; i < 12; ++i) off[i] = L.add(bytes[i]);
         tp_slots = std::max(tp_slots, H.slots());
     };
@@ -1437,8 +1429,8 @@ int32_t setup_two_phase(lp_handle* h, const TwoPhaseHost& H, const Mat& M, char*
     HIP_TRY(h, hipMemcpyAsync(base + off[6], first.data(), 4 * first.size(), hipMemcpyHostToDevice, s));
     // padding between the blocks: column 0, value 0 (its products are written and never read)
     HIP_TRY(h, hipMemsetAsync(base + off[7], 0, 2 * H.slots(), s));
-    launch_fill(const_cast<double*>(T.v), static_cast<long long>(H.slots()), 0.0, s);
-    if (T.v32) HIP_TRY(h, hipMemsetAsync(const_cast<float*>(T.v32), 0, sizeof(float) * H.slots(), s));
+    if (T.v) launch_fill(const_cast<double*>(T.v), static_cast<long long>(H.slots()), 0.0, s);
+    else HIP_TRY(h, hipMemsetAsync(const_cast<float*>(T.v32), 0, sizeof(float) * H.slots(), s));
     launch_tp_fill(T, M.csr, d_cell, d_k, const_cast<unsigned short*>(T.lcol), const_cast<double*>(T.v),
                    const_cast<float*>(T.v32), const_cast<unsigned short*>(T.pos), s);
     HIP_TRY(h, hipStreamSynchronize(s));  // the host arrays and tmp are this call's
@@ -1565,8 +1557,8 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
         T.first = I(off[6]);
         T.lcol = reinterpret_cast<const unsigned short*>(b + off[7]);
         T.pos = reinterpret_cast<const unsigned short*>(b + off[8]);
-        T.v = D(off[9]);
-        T.v32 = fp32 ? reinterpret_cast<const float*>(D(off[9]) + H.slots()) : nullptr;
+        T.v = fp32 ? nullptr : D(off[9]);
+        T.v32 = fp32 ? reinterpret_cast<const float*>(b + off[9]) : nullptr;
         T.is_long = M.pan.is_long;
         T.keep = nnz * (fp32 ? 20LL : 32LL) <= kTpKeepBytes ? 1 : 0;
         T.tiles_short = H.tiles_short;

@@ -96,6 +96,16 @@ struct Panels {
     int cols;                      // length of the gathered vector
 };
 
+// Panel layout: a matrix whose gathered vector fits one XCD's 4 MB L2 is swept as row tiles
+// unless a panel width was asked for. The gathers hit the L2 in any order then, and the panel
+// units (a few hundred entries per wave and step, a barrier after each, ~20 us however small
+// the matrix) only cost latency. us per iteration, Halpern form, panels / row tiles: 32k
+// entries 11.8 / 7.8, dense rows with 993k (FP64) 57 / 16, power-law columns with 1.2M 48 / 38
+// (FP32 39 / 29), 2.4M 72 / 57 (62 / 50); beyond, x at 6.4 MB: 111 / 114, y at 6.4 MB: 190 / 219.
+// The FP64 products of the FP32 storage form gather twice the bytes and keep the panels where
+// those exceed it (y at 8 MB, 1.2e7 entries: panels 107, row tiles 159).
+constexpr long long kFlatBytes = 4LL << 20;
+
 // Two-phase layout of a matrix (lp_two_phase.h): blocks of 2^width_bits columns and tiles of
 // rows with at most tile_nnz entries: first those of the rows that are not long (tile_row
 // numbers the matrix's rows, trp their entries without the long rows'), from tiles_short on
@@ -113,8 +123,8 @@ struct TwoPhase {
     const unsigned long long* mask;
     const int* first;
     const unsigned short *lcol, *pos;
-    const double* v;
-    const float* v32;
+    const double* v;   // FP64 form only
+    const float* v32;  // FP32 storage form only
     int keep;                      // plain loads of the matrix (see kTpKeepBytes), else non-temporal ones
     const unsigned char* is_long;  // as in Panels
     const int* longs;

@@ -1176,7 +1176,7 @@ void launch_spmv(const Mat& M, const T* xin, const Epi& epi, hipStream_t s) {
                            xin, epi);
         return;
     }
-    if (M.flat[M.layout].recs) {
+    if (M.flat[M.layout].recs && (M.layout == 1 || static_cast<long long>(sizeof(T)) * M.csr.cols <= kFlatBytes)) {
         launch_tiles(M.flat[M.layout], xin, epi, s);
         return;
     }

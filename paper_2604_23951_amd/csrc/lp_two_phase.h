@@ -243,8 +243,8 @@ __global__ __launch_bounds__(64) void tp_fill_kernel(TwoPhase M, Csr A, const in
             if (before == 0) placed[b] += __popcll(same);
             const long long o = cell_base[static_cast<long long>(b) * M.tiles + t] + at;
             lcol[o] = static_cast<unsigned short>(col - (b << M.width_bits));
-            v[o] = A.v[e];
             if (v32) v32[o] = static_cast<float>(A.v[e]);
+            else v[o] = A.v[e];
             pos[static_cast<long long>(M.tile_chunk[t]) * 64 + cell_k[static_cast<long long>(t) * M.blocks + b] + at] =
                 static_cast<unsigned short>(p - p0);
         }
