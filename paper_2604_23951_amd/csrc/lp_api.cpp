@@ -27,6 +27,7 @@
 #include "lp_device.h"
 #include "lp_layout.h"
 #include "lp_check.h"
+#include "lp_server_pool.h"
 #include "lp_tile_table.h"
 
 using namespace lpgpu;
@@ -345,92 +346,25 @@ void set_last_error(const std::string& msg) { g_last_error = msg; }
 
 namespace {
 
-// Device allocations and pinned scalar blocks of a server's requests, kept for the next ones:
-// hipMalloc and hipFree per request cost more than the set-up of a small LP, and hipFree waits
-// for every stream of the device. Memory is returned only after its last work was waited
-// for, so any stream may take it next. Requests are admitted here: the footprints admitted, what
-// reused blocks exceed theirs by and the free blocks stay within the budget. Everything is
-// given back when the server and its requests are gone.
-class ServerPool {
-public:
-    explicit ServerPool(int64_t budget) : budget_(budget) {}
-    ~ServerPool() {
-        for (auto& f : free_) (void)hipFree(f.first);
-        for (Scalars* p : scalars_) (void)hipHostFree(p);
+// The memory behind a server's pool (see lp_server_pool.h).
+struct HipMemory {
+    using Error = hipError_t;
+    using Stream = hipStream_t;
+    using Pinned = Scalars;
+    static hipError_t ok() { return hipSuccess; }
+    static bool out_of_memory(hipError_t e) {
+        if (e == hipErrorOutOfMemory) (void)hipGetLastError();
+        return e == hipErrorOutOfMemory;
     }
-    ServerPool(const ServerPool&) = delete;
-    ServerPool& operator=(const ServerPool&) = delete;
-
-    bool admit(size_t need) {
-        std::lock_guard<std::mutex> lk(mu_);
-        if (admitted_ + over_ + static_cast<int64_t>(need) > budget_) return false;
-        admitted_ += static_cast<int64_t>(need);
-        return true;
-    }
-    void retire(size_t need) {
-        std::lock_guard<std::mutex> lk(mu_);
-        admitted_ -= static_cast<int64_t>(need);
-    }
-    // Memory for an admitted request: a free block (*held bytes of it) or a new one.
-    hipError_t take(size_t need, char** out, size_t* held) {
-        std::lock_guard<std::mutex> lk(mu_);
-        size_t best = free_.size();
-        for (size_t i = 0; i < free_.size(); ++i)
-            if (free_[i].second >= need && (best == free_.size() || free_[i].second < free_[best].second)) best = i;
-        if (best < free_.size() && admitted_ + over_ + static_cast<int64_t>(free_[best].second - need) <= budget_) {
-            *out = free_[best].first;
-            *held = free_[best].second;
-            free_bytes_ -= static_cast<int64_t>(*held);
-            taken_ += static_cast<int64_t>(*held);
-            over_ += static_cast<int64_t>(*held - need);
-            free_.erase(free_.begin() + static_cast<std::ptrdiff_t>(best));
-            return hipSuccess;
-        }
-        while (!free_.empty() && taken_ + free_bytes_ + static_cast<int64_t>(need) > budget_) drop_one();
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(out), need);
-        while (e == hipErrorOutOfMemory && !free_.empty()) {
-            (void)hipGetLastError();
-            drop_one();
-            e = hipMalloc(reinterpret_cast<void**>(out), need);
-        }
-        if (e == hipSuccess) {
-            *held = need;
-            taken_ += static_cast<int64_t>(need);
-        }
-        return e;
-    }
-    void give(char* p, size_t held, size_t need) {
-        std::lock_guard<std::mutex> lk(mu_);
-        taken_ -= static_cast<int64_t>(held);
-        over_ -= static_cast<int64_t>(held - need);
-        free_bytes_ += static_cast<int64_t>(held);
-        free_.emplace_back(p, held);
-    }
-    hipError_t take_scalars(Scalars** out) {
-        std::lock_guard<std::mutex> lk(mu_);
-        if (!scalars_.empty()) {
-            *out = scalars_.back();
-            scalars_.pop_back();
-            return hipSuccess;
-        }
+    hipError_t allocate(char** out, size_t bytes) { return hipMalloc(reinterpret_cast<void**>(out), bytes); }
+    void release(char* p) { (void)hipFree(p); }
+    hipError_t allocate_pinned(Scalars** out) {
         return hipHostMalloc(reinterpret_cast<void**>(out), sizeof(Scalars), hipHostMallocDefault);
     }
-    void give_scalars(Scalars* p) {
-        std::lock_guard<std::mutex> lk(mu_);
-        scalars_.push_back(p);
-    }
-
-private:
-    void drop_one() {
-        (void)hipFree(free_.back().first);
-        free_bytes_ -= static_cast<int64_t>(free_.back().second);
-        free_.pop_back();
-    }
-    std::mutex mu_;
-    int64_t budget_, admitted_ = 0, over_ = 0, taken_ = 0, free_bytes_ = 0;
-    std::vector<std::pair<char*, size_t>> free_;
-    std::vector<Scalars*> scalars_;
+    void release_pinned(Scalars* p) { (void)hipHostFree(p); }
+    hipError_t wait(hipStream_t s) { return hipStreamSynchronize(s); }
 };
+using RequestPool = ServerPool<HipMemory>;
 
 }  // namespace
 
@@ -449,7 +383,7 @@ struct lp_handle {
     char* arena = nullptr;
     size_t arena_bytes = 0;
     size_t arena_held = 0;                // bytes of the allocation behind arena
-    std::shared_ptr<ServerPool> pool;     // a server's request: where its memory comes from and goes
+    std::shared_ptr<RequestPool> pool;     // a server's request: where its memory comes from and goes
     DevLP P{};
     int* d_perm = nullptr;
     double* d_x0 = nullptr;
@@ -552,7 +486,7 @@ void destroy_device(lp_handle* h) {
     for (auto& e : h->ev)
         if (e) (void)hipEventDestroy(e);
     free_arena(h);
-    if (h->h_sc && h->pool) h->pool->give_scalars(h->h_sc);
+    if (h->h_sc && h->pool) h->pool->give_pinned(h->h_sc);
     else if (h->h_sc) (void)hipHostFree(h->h_sc);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     h->gexec = nullptr;
@@ -568,8 +502,8 @@ void destroy_device(lp_handle* h) {
 // Keep the result on the host and give the device memory back (the handle stays usable:
 // a later solve places it on the device again).
 int32_t release_device(lp_handle* h) {
-    if (!h->on_device) {  // a set-up that failed part way may still hold its allocation
-        free_arena(h);
+    if (!h->on_device) {  // a set-up that failed part way may still hold its allocation (a request's
+        free_arena(h);    // went to the pool when it failed)
         if (!h->own_stream) h->stream = nullptr;
         return LP_OK;
     }
@@ -590,7 +524,7 @@ int32_t release_device(lp_handle* h) {
     h->graph_failed = false;
     free_arena(h);
     if (h->pool && h->h_sc) {
-        h->pool->give_scalars(h->h_sc);
+        h->pool->give_pinned(h->h_sc);
         h->h_sc = nullptr;
     }
     h->on_device = false;
@@ -1462,7 +1396,7 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
         h->arena_held = h->arena_bytes;
     }
     if (h->pool && !h->h_sc) {
-        HIP_TRY(h, h->pool->take_scalars(&h->h_sc));
+        HIP_TRY(h, h->pool->take_pinned(&h->h_sc));
         std::memset(h->h_sc, 0, sizeof(Scalars));
     } else if (!h->h_sc) {
         const size_t res = sizeof(double) * (2 * static_cast<size_t>(n) + static_cast<size_t>(m));
@@ -1812,7 +1746,7 @@ struct lp_server {
     static constexpr int kSetups = 3;
     std::thread setup_worker[kSetups];
     hipStream_t setup_stream[kSetups] = {nullptr, nullptr, nullptr};
-    std::shared_ptr<ServerPool> pool;
+    std::shared_ptr<RequestPool> pool;
     std::mutex mu;
     std::condition_variable cv_work, cv_idle, cv_setup;
     std::deque<Ticket> queue;
@@ -1989,6 +1923,17 @@ void server_round(lp_server* S, DevMaps& run_maps, DevMaps& new_maps, bool& dirt
     }
 }
 
+// A request whose set-up failed part way: its memory goes back to the pool after the work that
+// was queued on it (device memory and pinned scalars; kept by the handle if the wait failed).
+void abandon_setup(lp_handle* h) {
+    const bool done = h->pool->give_unfinished(h->stream, h->arena, h->arena_held, h->arena_bytes);
+    h->arena = nullptr;
+    if (h->h_sc && done) {
+        h->pool->give_pinned(h->h_sc);
+        h->h_sc = nullptr;
+    }
+}
+
 void setup_loop(lp_server* S, int which) {
     (void)hipSetDevice(S->device);
     for (;;) {
@@ -2012,6 +1957,7 @@ void setup_loop(lp_server* S, int which) {
         t.h->stream = S->setup_stream[which];
         t.h->own_stream = false;
         t.setup_rc = materialize(t.h);
+        if (t.setup_rc != LP_OK) abandon_setup(t.h);  // while its stream is at hand
         std::unique_lock<std::mutex> lk(S->mu);
         S->ready.push_back(t);
         S->cv_work.notify_one();
@@ -2060,7 +2006,7 @@ int32_t lp_server_create(lp_server** out, int32_t device, int64_t hbm_budget_byt
         S->opt = o;
         S->t0 = std::chrono::steady_clock::now();
         S->st.hbm_budget = hbm_budget_bytes;
-        S->pool = std::make_shared<ServerPool>(hbm_budget_bytes);
+        S->pool = std::make_shared<RequestPool>(hbm_budget_bytes);
         hipError_t e = hipSetDevice(device);
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&S->stream, hipStreamNonBlocking);
         for (hipStream_t& st : S->setup_stream)
