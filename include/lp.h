@@ -539,7 +539,7 @@ void lp_destroy(lp_handle *h);
 /* The checked build (liblpgpu_checked.so, compiled with LPGPU_CHECKED=1) bounds-checks every
  * gathered column and every accumulator row in the product kernels: an index outside its
  * array sets a bit of a per-device word (1 panel gather, 2 panel accumulator row, 4 row-tile
- * gather, 8 long-row gather) and is replaced by 0, so the kernel goes on without reading
+ * gather, 8 long-row gather, 16 one-workgroup solver's matrix slot) and is replaced by 0, so the kernel goes on without reading
  * outside its arrays. lp_solve, lp_solve_until, lp_resume, lp_polish, lp_solve_batch and
  * lp_solve_batch_static of that build return LP_ERR_INTERNAL when the word is set after them.
  * lp_check_word reads and clears the word of `device` (for servers and for callers of the

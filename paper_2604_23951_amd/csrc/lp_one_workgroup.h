@@ -90,6 +90,7 @@ struct SellAt {
     int col_off, val_off;
     int staged;
     int limit;  // columns + 1 (the zero slot): the checked build's bound
+    int staged_slots, slots;  // bounds of a slot number in LDS and in global memory (checked build)
 };
 
 template <class T, int C>
@@ -106,10 +107,11 @@ __device__ __forceinline__ SellChunk<T, C> sell_load(int slot, const SellAt& M, 
     SellChunk<T, C> K;
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-        if constexpr (LC) K.c[k] = *reinterpret_cast<const unsigned*>(lds + M.col_off + 4 * (slot + 64 * k));
-        else K.c[k] = M.col[slot + 64 * k];
-        if constexpr (LV) K.v[k] = *reinterpret_cast<const V*>(lds + M.val_off + static_cast<int>(sizeof(V)) * (slot + 64 * k));
-        else K.v[k] = static_cast<const V*>(M.val)[slot + 64 * k];
+        const int at = checked_index(slot + 64 * k, LC ? M.staged_slots : M.slots, 16u);
+        if constexpr (LC) K.c[k] = *reinterpret_cast<const unsigned*>(lds + M.col_off + 4 * at);
+        else K.c[k] = M.col[at];
+        if constexpr (LV) K.v[k] = *reinterpret_cast<const V*>(lds + M.val_off + static_cast<int>(sizeof(V)) * at);
+        else K.v[k] = static_cast<const V*>(M.val)[at];
     }
     return K;
 }
@@ -315,11 +317,14 @@ struct SoloRegRow {
     __device__ __forceinline__ void load(int slot, int width, const SellAt& M, const char* lds) {
 #pragma unroll
         for (int k = 0; k < kSoloRegSlots; ++k) {
-            const SellChunk<T, 1> one = sell_load<T, 1, true, true>(slot + 64 * (k < width ? k : 0), M, lds);
             const unsigned zero = static_cast<unsigned>(M.limit - 1);
-            K.c[k] = k < width ? one.c[0] : (zero | (zero << 16));
-            K.v[k] = one.v[0];
-            if (k >= width) K.v[k].x = K.v[k].y = 0;
+            K.c[k] = zero | (zero << 16);
+            K.v[k].x = K.v[k].y = 0;
+            if (k < width) {  // (a slice without entries has no slot to read)
+                const SellChunk<T, 1> one = sell_load<T, 1, true, true>(slot + 64 * k, M, lds);
+                K.c[k] = one.c[0];
+                K.v[k] = one.v[0];
+            }
         }
     }
     __device__ __forceinline__ T sum(int slot, int width, const SellAt& M, const char* lds, const T* gat) const {
@@ -351,8 +356,8 @@ __device__ __forceinline__ void solo_period(const BatchJob& J, int steps) {
     T* xs = reinterpret_cast<T*>(solo_lds + L.xs);
     const int m = P.m, n = P.n;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const SellAt A{P.sA.col, sell_vals<T>(P.sA), L.a_col, L.a_val, J.a_slices, n + 1};
-    const SellAt AT{P.sAT.col, sell_vals<T>(P.sAT), L.at_col, L.at_val, J.at_slices, m + 1};
+    const SellAt A{P.sA.col, sell_vals<T>(P.sA), L.a_col, L.a_val, J.a_slices, n + 1, J.a_slots, P.sA.slots};
+    const SellAt AT{P.sAT.col, sell_vals<T>(P.sAT), L.at_col, L.at_val, J.at_slices, m + 1, J.at_slots, P.sAT.slots};
     const double tau = S.sc.tau, sigma = S.sc.sigma;
     const long long t0 = S.sc.t;
     const bool resid = kHalpern && P.restart_metric == 1;
@@ -495,8 +500,8 @@ __device__ __noinline__ void solo_evaluate(const BatchJob& J, int mode) {
     const DevLP& P = J.P;
     const SoloLds L = solo_lds_layout(P.m, P.n, FP32, J.a_slots, J.at_slots);
     const int tid = threadIdx.x, m = P.m, n = P.n, mx = m > n ? m : n;
-    const SellAt A{P.sA.col, P.sA.v, L.a_col, L.a_val, J.a_slices, n + 1};
-    const SellAt AT{P.sAT.col, P.sAT.v, L.at_col, L.at_val, J.at_slices, m + 1};
+    const SellAt A{P.sA.col, P.sA.v, L.a_col, L.a_val, J.a_slices, n + 1, J.a_slots, P.sA.slots};
+    const SellAt AT{P.sAT.col, P.sAT.v, L.at_col, L.at_val, J.at_slices, m + 1, J.at_slots, P.sAT.slots};
     const bool halpern = P.method != 0;
     if (FP32 && mode == 0) {
         for (int g = tid; g < mx; g += NT) materialize_at(P, g);
@@ -654,8 +659,8 @@ __global__ __launch_bounds__(1024) void solo_power_kernel(DevLP P, SoloStage G, 
     const SoloLds L = solo_lds_layout(m, n, 0, G.a_slots, G.at_slots);
     double* u = reinterpret_cast<double*>(solo_lds);
     double* v = reinterpret_cast<double*>(solo_lds + L.xs);
-    const SellAt A{P.sA.col, P.sA.v, L.a_col, L.a_val, G.a_slices, n + 1};
-    const SellAt AT{P.sAT.col, P.sAT.v, L.at_col, L.at_val, G.at_slices, m + 1};
+    const SellAt A{P.sA.col, P.sA.v, L.a_col, L.a_val, G.a_slices, n + 1, G.a_slots, P.sA.slots};
+    const SellAt AT{P.sAT.col, P.sAT.v, L.at_col, L.at_val, G.at_slices, m + 1, G.at_slots, P.sAT.slots};
     solo_stage<1024>(solo_lds + L.a_col, P.sA.col, 4 * G.a_slots);
     solo_stage<1024>(solo_lds + L.a_val, P.sA.v, 16 * G.a_slots);
     solo_stage<1024>(solo_lds + L.at_col, P.sAT.col, 4 * G.at_slots);
