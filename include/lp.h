@@ -588,7 +588,11 @@ int32_t lp_get_kernel_times(lp_handle *h, double *primal_ms, double *dual_ms, in
  * [9] = layout of the products (0 panels, 1 row tiles; -1 before the handle is on the
  * device), [10] / [11] = the layout tuner's time in nanoseconds of one A x + A^T y pair in
  * panels / row tiles (0 unless spmv_layout is 2), [12] = nonzeros per row tile (the shape
- * chosen from tile_nnz or the tuned table). */
+ * chosen from tile_nnz or the tuned table), [13] / [14] = tiles of the two-phase products of A /
+ * A^T (0: not used), [15] = what ran the handle's last solve (-1 none, 0 one kernel per phase,
+ * 1 the one-workgroup solver, 2 one workgroup over row tiles in LDS, 3 one workgroup over row
+ * tiles in global memory, 4 the block-diagonal launches), [16] / [17] = row tiles of A / A^T
+ * that the solve's own launches use in place of the panels or of the shape in [12] (0: none). */
 int32_t lp_get_layout(lp_handle *h, int64_t *sizes, int32_t cap);
 
 #ifdef __cplusplus

@@ -348,10 +348,11 @@ def lp_get_kernel_times(h):
 
 
 def lp_get_layout(h):
-    out = np.zeros(13, np.int64)
-    _check(lib().lp_get_layout(h, _p(out), 13), h)
+    out = np.zeros(18, np.int64)
+    _check(lib().lp_get_layout(h, _p(out), len(out)), h)
     keys = ("tiles_a", "tiles_at", "long_rows_a", "long_rows_at", "device_bytes", "units_a", "units_at",
-            "panels_a", "panels_at", "layout", "trial_ns_panels", "trial_ns_tiles", "tile_nnz")
+            "panels_a", "panels_at", "layout", "trial_ns_panels", "trial_ns_tiles", "tile_nnz", "two_phase_a", "two_phase_at",
+            "last_solver", "flat_a", "flat_at")
     return {k: int(v) for k, v in zip(keys, out)}
 
 

@@ -252,6 +252,9 @@ constexpr size_t kPinnedScalars = (sizeof(Scalars) + 63) / 64 * 64;
 constexpr size_t kSoloJobAligned = (sizeof(BatchJob) + 255) / 256 * 256;
 constexpr size_t kSoloJobBytes = kSoloJobAligned + 768;
 
+// Kernels that ran a solve, as lp_get_layout reports them.
+enum SolverKind { RAN_KERNEL_LOOP = 0, RAN_ONE_WORKGROUP, RAN_TILES_LDS, RAN_TILES_GLOBAL, RAN_BLOCK_DIAGONAL };
+
 // Offsets of every device array inside a handle's allocation.
 struct Offsets {
     size_t arp, aci, av, at, trp, tci, tv, tt, perm, c, xl, xu, C, Ci, bl, bu, R, Ri;
@@ -380,6 +383,7 @@ struct lp_handle {
     int64_t units_a = 0, units_at = 0, panels_a = 0, panels_at = 0;
     int tile_shape = 1;  // row-tile shape chosen at lp_create
     double trial_us[2] = {0.0, 0.0};  // layout tuner's times (panels, row tiles)
+    int last_solver = -1;             // kernels of the last solve (lp_get_layout [15])
     char* arena = nullptr;
     size_t arena_bytes = 0;
     size_t arena_held = 0;                // bytes of the allocation behind arena
@@ -645,9 +649,9 @@ SoloPlan solo_plan(const lp_handle* h, int budget, bool widest = false) {
 }
 
 // Collects the results of the handles; written(i): the kernels wrote handle i's scalars and
-// point to its pinned host memory.
-template <class Written>
-int32_t finish_batch(lp_handle* const* hs, int count, hipStream_t s, Written&& written) {
+// point to its pinned host memory; ran(i): the kernels that solved it.
+template <class Written, class Ran>
+int32_t finish_batch(lp_handle* const* hs, int count, hipStream_t s, Written&& written, Ran&& ran) {
     for (int i = 0; i < count; ++i)
         if (!written(i))
             HIP_TRY(hs[i], hipMemcpyAsync(hs[i]->h_sc, hs[i]->P.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
@@ -656,6 +660,7 @@ int32_t finish_batch(lp_handle* const* hs, int count, hipStream_t s, Written&& w
         fill_info(hs[i]);
         hs[i]->solved = true;
         hs[i]->res_valid = written(i);
+        hs[i]->last_solver = ran(i);
     }
     return LP_OK;
 }
@@ -856,6 +861,7 @@ void run_round(DevMaps& D, hipStream_t s, int capture_after) {
 struct PersistentRun {
     std::vector<BatchJob> jobs;
     std::vector<int32_t> order;
+    std::vector<uint8_t> group;  // every LP's launch (BatchGroup)
     char* buf = nullptr;
     hipStream_t s[4] = {nullptr, nullptr, nullptr, nullptr};
 };
@@ -863,6 +869,10 @@ struct PersistentRun {
 // The launches of a persistent batch: LPs of one kernel, their dynamic LDS.
 enum BatchGroup { BG_SOLO_1024 = 0, BG_SOLO_512, BG_SOLO_256, BG_TILES_LDS, BG_TILES, BG_COUNT };
 static_assert(BG_COUNT <= kBatchCounters, "one work counter per launch");
+
+int group_solver(int group) {
+    return group <= BG_SOLO_256 ? RAN_ONE_WORKGROUP : group == BG_TILES_LDS ? RAN_TILES_LDS : RAN_TILES_GLOBAL;
+}
 
 struct BatchGroups {
     int first[BG_COUNT] = {0}, count[BG_COUNT] = {0}, lds[BG_COUNT] = {0};
@@ -931,9 +941,9 @@ int32_t start_persistent(const std::vector<lp_handle*>& hs, const lp_options* bo
         R.jobs[i] = make_job(hs[i], bo);
         solo_plan(hs[i], budget).apply(&R.jobs[i]);
     }
-    std::vector<uint8_t> group(static_cast<size_t>(count));
+    R.group.resize(static_cast<size_t>(count));
     BatchGroups G;
-    group_batch(hs.data(), count, budget, false, R.order.data(), group.data(), &G);
+    group_batch(hs.data(), count, budget, false, R.order.data(), R.group.data(), &G);
     int cus = 256;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h0->device) != hipSuccess || cus < 1)
         cus = 256;
@@ -979,7 +989,8 @@ int32_t finish_persistent(const std::vector<lp_handle*>& hs, PersistentRun& R, b
     int32_t rc = LP_OK;
     if (e != hipSuccess) rc = fail(hs[0], LP_ERR_DEVICE, std::string("batched solve: ") + hipGetErrorString(e));
     else if (collect)
-        rc = finish_batch(hs.data(), static_cast<int>(hs.size()), R.s[0], [&](int i) { return R.jobs[i].host != nullptr; });
+        rc = finish_batch(hs.data(), static_cast<int>(hs.size()), R.s[0], [&](int i) { return R.jobs[i].host != nullptr; },
+                          [&](int i) { return group_solver(R.group[i]); });
     for (hipStream_t& st : R.s) {
         if (st) (void)hipStreamDestroy(st);
         st = nullptr;
@@ -1039,7 +1050,8 @@ int32_t solve_block_diagonal(const std::vector<lp_handle*>& hs, const lp_options
     launch_multi(all.M, MULTI_EXTRACT, 0, s);
     HIP_TRY(h0, hipGetLastError());
     HIP_TRY(h0, hipStreamSynchronize(s));
-    return finish_batch(hs.data(), static_cast<int>(hs.size()), s, [&](int i) { return hs[i]->h_res != nullptr; });
+    return finish_batch(hs.data(), static_cast<int>(hs.size()), s, [&](int i) { return hs[i]->h_res != nullptr; },
+                        [](int) { return RAN_BLOCK_DIAGONAL; });
 }
 
 int32_t capture_graph(lp_handle* h) {
@@ -2376,6 +2388,7 @@ int32_t solve_one_workgroup(lp_handle* h, size_t lds_need, const SoloPlan& plan,
     h->info.solve_path = 1;
     h->solved = true;
     h->res_valid = J.host != nullptr;
+    h->last_solver = plan.variant != SOLO_NONE ? RAN_ONE_WORKGROUP : RAN_TILES_LDS;
     return LP_OK;
 }
 
@@ -2418,6 +2431,7 @@ int32_t solve_from(lp_handle* h, const double* x0s, const double* y0s, int term_
 int32_t run_periods(lp_handle* h, std::chrono::steady_clock::time_point t0, long long pause_k) {
     hipStream_t s = h->stream;
     const DevLP& P = h->P;
+    h->last_solver = RAN_KERNEL_LOOP;
     bool paused = false;
     const bool use_graph = !h->timing;
     if (h->timing && !h->ev[0])
@@ -2931,7 +2945,7 @@ int32_t lp_solve_batch_static(lp_handle* const* hs, int32_t count, const lp_opti
         if (int32_t rc = check_launch(h0, "allocation-free batched solve")) return rc;
         HIP_TRY(h0, hipStreamSynchronize(s));
         auto written = [&](int i) { return group[i] <= BG_SOLO_256 && hs[i]->h_res != nullptr; };
-        if (int32_t rc = finish_batch(hs, count, s, written)) return rc;
+        if (int32_t rc = finish_batch(hs, count, s, written, [&](int i) { return group_solver(group[i]); })) return rc;
         const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         for (int32_t i = 0; i < count; ++i) hs[i]->info.solve_seconds = secs;
         return with_checks(nullptr, dev, LP_OK);
@@ -3087,12 +3101,20 @@ int32_t lp_get_kernel_times(lp_handle* h, double* primal_ms, double* dual_ms, in
 
 int32_t lp_get_layout(lp_handle* h, int64_t* sizes, int32_t cap) {
     if (!h || !sizes || cap < 0) return fail(h, LP_ERR_INVALID_ARG, "bad layout arguments");
-    const int64_t v[13] = {h->P.A.csr.ntiles, h->P.AT.csr.ntiles, h->long_a, h->long_at,
+    // the row tiles in use by the solve's own products, if they are not the layout's own
+    auto flat = [&](const Mat& M) -> int64_t {
+        const int64_t sv = h->P.fp32 ? 4 : 8;
+        const Csr& F = M.flat[M.layout];
+        if (M.layout == 0 && M.tp.tiles > 0) return 0;
+        return F.recs && (M.layout == 1 || sv * F.cols <= kFlatBytes) ? F.ntiles : 0;
+    };
+    const int64_t v[18] = {h->P.A.csr.ntiles, h->P.AT.csr.ntiles, h->long_a, h->long_at,
                            static_cast<int64_t>(h->arena_bytes), h->units_a, h->units_at, h->panels_a, h->panels_at,
                            h->on_device ? h->P.A.layout : -1,
                            static_cast<int64_t>(h->trial_us[0] * 1e3), static_cast<int64_t>(h->trial_us[1] * 1e3),
-                           tile_nnz_of(h->tile_shape)};
-    for (int32_t i = 0; i < cap && i < 13; ++i) sizes[i] = v[i];
+                           tile_nnz_of(h->tile_shape), h->P.A.tp.tiles, h->P.AT.tp.tiles, h->last_solver,
+                           h->on_device ? flat(h->P.A) : 0, h->on_device ? flat(h->P.AT) : 0};
+    for (int32_t i = 0; i < cap && i < 18; ++i) sizes[i] = v[i];
     return LP_OK;
 }
 
