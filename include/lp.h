@@ -142,10 +142,12 @@ typedef struct lp_options {
                               allocated (and the setup run) when the LP is first solved or admitted
                               by a server, and released by the server when it completes (default 0) */
     int32_t small_lp_lds;  /* bytes of LDS per workgroup (0 to 114688, default 114688) for LPs
-                              held on chip. Batched solves: an LP of the persistent launches is
-                              solved by one workgroup with as much of its matrices in LDS as fits
-                              beside the vectors that are gathered, bit-identical to the solve
-                              with all of them in global memory. lp_solve: an LP whose matrices
+                              held on chip. Batched solves: an LP of the persistent launches (16-bit
+                              columns, rows of at most 128 entries) whose gathered vectors fit (at
+                              114688: 155648 bytes of them) is solved by one workgroup with as much
+                              of its matrices in LDS as fits beside them; other LPs, if their matrices and iteration vectors
+                              fit, as row tiles in LDS; the rest, and all LPs at 0, as row tiles
+                              in global memory, all bit-identical. lp_solve: an LP whose matrices
                               fit (16-bit columns, rows of at most 128 entries; or, as row tiles,
                               matrices and iteration vectors) is solved by one workgroup (the
                               whole loop in one launch, the row-tile sums; not with kernel timing

@@ -621,10 +621,15 @@ BatchJob make_job(lp_handle* h, const lp_options* bo) {
 // that (fewer waves meet at each barrier, and several such workgroups share a CU) when all of
 // it fits the LDS budget; the wider ones stage the slices that fit, those of A (the longer
 // rows of the two in most LPs, summed by fewer threads) first. Operands that no longer fit the
-// registers of 1024 threads stay in global memory. widest: 1024 threads whatever the size.
+// registers of 1024 threads stay in global memory. widest: 1024 threads whatever the size. An LP
+// whose gathered vectors alone exceed the budget (every LP, at a budget of 0) has no plan; at
+// the largest budget an LP may ask for, they may take all of a workgroup's LDS (kSoloLdsMax),
+// since such an LP runs ~5 times faster with them there than as row tiles in global memory.
 SoloPlan solo_stage_plan(const lp_handle* h, int budget, bool fp32) {
     SoloPlan S;
-    if (h->sell_a.empty()) return S;
+    if (h->sell_a.empty() || budget <= 0 ||
+        solo_lds_bytes(h->m, h->n, fp32, 0, 0) > (budget < kSmallLpLdsMax ? budget : kSoloLdsMax))
+        return S;
     const int na = static_cast<int>(h->sell_a.size()) - 1, nat = static_cast<int>(h->sell_at.size()) - 1;
     auto bytes = [&](int a, int at) { return solo_lds_bytes(h->m, h->n, fp32, h->sell_a[a], h->sell_at[at]); };
     while (S.a_slices < na && bytes(S.a_slices + 1, 0) <= budget) S.a_slices++;
@@ -639,7 +644,7 @@ SoloPlan solo_stage_plan(const lp_handle* h, int budget, bool fp32) {
 SoloPlan solo_plan(const lp_handle* h, int budget, bool widest = false) {
     const int m = h->m, n = h->n, fp32 = h->opt.precision == LP_PREC_FP32_REFINED;
     SoloPlan S = solo_stage_plan(h, budget, fp32);
-    if (h->sell_a.empty()) return S;
+    if (S.lds == 0) return S;
     const int mx = std::max(m, n);
     if (S.whole && mx <= 512 && !widest) S.variant = mx <= 256 ? SOLO_256 : SOLO_512;
     else if (solo_sorted(m, n)) S.variant = SOLO_1024;
