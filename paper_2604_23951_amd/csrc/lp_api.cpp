@@ -6,7 +6,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <condition_variable>
 #include <array>
@@ -26,6 +25,7 @@
 
 #include "lp_device.h"
 #include "lp_layout.h"
+#include "lp_layout_trial.h"
 #include "lp_check.h"
 #include "lp_server_pool.h"
 #include "lp_tile_table.h"
@@ -233,11 +233,7 @@ struct Prep {
     bool panels = false;
     int nred = 1;
     bool ready = false;
-    // layout tuner (spmv_layout 2): the chosen layout (-1 before the first trial) and the
-    // mean time in microseconds of one A x + A^T y pair in each layout; shared by the
-    // clones of a deferred handle, which take the first trial's choice
-    std::atomic<int> tuned{-1};
-    double trial_us[2] = {0.0, 0.0};
+    SharedLayoutTrial trial;  // spmv_layout 2
 };
 
 // The point of a batched or one-workgroup solve of at most this many bytes is written to pinned
@@ -1278,10 +1274,9 @@ size_t arena_layout(const lp_handle* h, Offsets* O) {
 
 // Device part (a2, a3): allocate, bind, upload, scale, permute values, estimate ||A~||_2 and
 // the step size. Runs on the handle's stream and waits.
-// Times reps pairs of products in each layout, twice in alternation, keeps the smaller
-// time of each and records the faster layout in the shared host structure.
-int32_t tune_layout(lp_handle* h, hipStream_t s) {
-    Prep& Q = *h->prep;
+// Times reps pairs of products in each layout, twice in alternation, and keeps the smaller
+// time of each and the faster layout.
+int32_t tune_layout(lp_handle* h, hipStream_t s, LayoutTrial* out) {
     const DevLP& P = h->P;
     constexpr int kReps = 8;
     if (P.fp32) {
@@ -1314,10 +1309,9 @@ int32_t tune_layout(lp_handle* h, hipStream_t s) {
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (e != hipSuccess) return fail(h, LP_ERR_DEVICE, std::string("layout trial: ") + hipGetErrorString(e));
-    Q.trial_us[0] = 1e3 * best[0] / kReps;
-    Q.trial_us[1] = 1e3 * best[1] / kReps;
-    int expect = -1;
-    (void)Q.tuned.compare_exchange_strong(expect, best[1] < best[0] ? 1 : 0);
+    out->us[0] = 1e3 * best[0] / kReps;
+    out->us[1] = 1e3 * best[1] / kReps;
+    out->layout = best[1] < best[0] ? 1 : 0;
     return LP_OK;
 }
 
@@ -1655,12 +1649,11 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     // layout tuner: time both product layouts on this device and keep the faster one for
     // every product of the solve, the power iteration below included
     if (o.spmv_layout == 2) {
-        if (Q.tuned.load() < 0) {
-            if (int32_t rc = tune_layout(h, s)) return rc;
-        }
-        P.A.layout = P.AT.layout = Q.tuned.load();
-        h->trial_us[0] = Q.trial_us[0];
-        h->trial_us[1] = Q.trial_us[1];
+        LayoutTrial trial;
+        if (int32_t rc = h->prep->trial.get(&trial, [&](LayoutTrial* t) { return tune_layout(h, s, t); })) return rc;
+        P.A.layout = P.AT.layout = trial.layout;
+        h->trial_us[0] = trial.us[0];
+        h->trial_us[1] = trial.us[1];
     }
     // a3: ||A~||_2 by power iteration (x, A~x and A~^T y buffers are free at this point), in
     // chunks of pow_iters steps until a chunk's last step raises the estimate by at most
