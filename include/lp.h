@@ -152,9 +152,10 @@ typedef struct lp_options {
                               matrices and iteration vectors) is solved by one workgroup (the
                               whole loop in one launch, the row-tile sums; not with kernel timing
                               on, and not for lp_polish's solves), bit-identical to the
-                              kernel-per-phase loop with row tiles (lp_info.solve_path = 1);
-                              stopped by its time limit it returns objectives summed in index
-                              order. 0 turns both off */
+                              kernel-per-phase loop with row tiles (lp_info.solve_path = 1); the
+                              evaluation that finds its time limit passed sums in index order
+                              (rows, then columns), decides on those sums and records them in the
+                              trace. 0 turns both off */
     const double *x0;      /* optional warm start (host, length n, original scale) */
     const double *y0;      /* optional warm start (host, length m, original scale) */
     double eps_infeas;     /* relative tolerance of the infeasibility certificates (default 1e-8;

@@ -247,7 +247,7 @@ struct BatchJob {
     // keep, and the slices (slots) of A and A^T staged in LDS
     int variant, eval_blocks;
     int a_slices, a_slots, at_slices, at_slots;
-    int plain_stop;  // one-workgroup solver: statistics of a time-limit stop in plain index order
+    int plain_stop;  // an evaluation past the time limit sums in plain index order (time_limit_passed)
 };
 
 // Block maps of a block-diagonal batch: entry b of a map is (LP index, tile or block of it).

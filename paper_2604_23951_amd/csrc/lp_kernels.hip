@@ -1666,6 +1666,10 @@ __device__ inline void set_output(Scalars* sc, const Kkt& K, int avg) {
     sc->out_erel = K.erel;
 }
 
+__device__ inline bool deadline_passed(const Scalars* sc) {
+    return sc->deadline > 0 && static_cast<long long>(wall_clock64()) >= sc->deadline;
+}
+
 // Evaluation and decision, one workgroup:
 //  E_rel = max(||r_p||/(1+||q||), ||r_d||/(1+||c||), |p-d|/(1+|p|+|d|)) on the original data;
 //  termination when E_rel(current) <= eps (then the average), or at max_iters the better one;
@@ -1675,8 +1679,8 @@ __device__ inline void set_output(Scalars* sc, const Kkt& K, int avg) {
 //  omega_steps times, or the PID rule (log omega -= kp e + ki I + kd (e - e_prev) with
 //  e = log(omega dx / dy), I the sum of the errors so far).
 // Thread-0 part of the evaluation: tot holds the summed KKT quantities of the current
-// iterate (0..7) and, in mode 0, of the average (8..15).
-__device__ void decide_logic(const DevLP& P, Scalars* sc, const double* tot, int mode) {
+// iterate (0..7) and, in mode 0, of the average (8..15); late: the time limit has run out.
+__device__ void decide_logic(const DevLP& P, Scalars* sc, const double* tot, int mode, bool late) {
     const Kkt cur = make_kkt(tot, sc);
     if (mode == 2) {  // statistics of the returned point after a host-side stop
         set_output(sc, cur, P.method ? 1 : 0);
@@ -1756,7 +1760,7 @@ __device__ void decide_logic(const DevLP& P, Scalars* sc, const double* tot, int
             out_avg = halpern ? 1 : term_value(avg, sc->term_mode) < term_value(cur, sc->term_mode);
         }
         // time limit: the evaluated point is returned, as after a stop between evaluations
-        if (status == kRunning && sc->deadline > 0 && static_cast<long long>(wall_clock64()) >= sc->deadline) {
+        if (status == kRunning && late) {
             status = 2;
             out_avg = halpern;
         }
@@ -1846,7 +1850,7 @@ __device__ void decide_body(const DevLP& P, int mode) {
         if (threadIdx.x == 0) tot[q] = v;
     }
     if (threadIdx.x != 0) return;
-    decide_logic(P, P.sc, tot, mode);
+    decide_logic(P, P.sc, tot, mode, deadline_passed(P.sc));
 }
 
 __global__ __launch_bounds__(kBlock) void decide_kernel(DevLP P, int mode) { decide_body(P, mode); }
@@ -2154,6 +2158,54 @@ __device__ inline void reset_scalars(Scalars* sc, const BatchJob& J) {
     sc->deadline = J.limit_ticks > 0 ? (J.t0 ? *J.t0 : static_cast<long long>(wall_clock64())) + J.limit_ticks : 0;
 }
 
+// The evaluated candidate's sums (tot's slots 0..7 of mode 0) formed again in plain index order:
+// rows first, then columns. The terms are computed by all threads and staged in buf (cap
+// values); one thread per quantity adds them. Ends with a barrier.
+template <int NT>
+__device__ void plain_sums(const DevLP& P, double* tot, double* buf, int cap) {
+    const double* ax = P.method ? P.axa : P.ax;
+    const double* y = P.method ? P.ya : P.y;
+    const double* x = P.method ? P.xa : P.x;
+    const double* aty = P.method ? P.atya : P.aty;
+    const int chunk = min(NT, cap / kNQ), tid = threadIdx.x, count = P.m + P.n;
+    double s = 0.0;
+    for (int base = 0; base < count; base += chunk) {
+        const int here = min(chunk, count - base), e = base + tid;
+        if (tid < here) {
+            double acc[kNQ] = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (e < P.m) row_terms(P, e, ax, y, acc);
+            else col_terms(P, e - P.m, x, aty, acc);
+#pragma unroll
+            for (int q = 0; q < kNQ; ++q) buf[q * chunk + tid] = acc[q];
+        }
+        __syncthreads();
+        if (tid < kNQ)
+            for (int i = 0; i < here; ++i) s += buf[tid * chunk + i];
+        __syncthreads();
+    }
+    if (tid < kNQ) tot[tid] = s;
+    __syncthreads();
+}
+
+// Whether the job's time limit has run out, the same in every thread that calls decide_logic. In
+// a one-workgroup lp_solve (plain_stop) the evaluation that finds it so decides on sums in
+// index order: such a solve gets as close to the optimum as its limit allows, the gap is then
+// the difference of two nearly equal objective sums, and what it returns is the plain definition
+// of E_rel at the returned point, on which the stop was decided and which the trace records.
+// `flag` and `buf` (cap values) are LDS; every thread calls it.
+template <int NT>
+__device__ inline bool time_limit_passed(const DevLP& P, const BatchJob& J, const Scalars* sc, double* tot, double* flag,
+                                         double* buf, int cap) {
+    if (!J.plain_stop) return deadline_passed(sc);
+    if (sc->deadline <= 0) return false;
+    if (threadIdx.x == 0) *flag = deadline_passed(sc) ? 1.0 : 0.0;
+    __syncthreads();
+    const bool late = *flag != 0.0;
+    __syncthreads();
+    if (late) plain_sums<NT>(P, tot, buf, cap);
+    return late;
+}
+
 // One LP solved by one workgroup: the same restarted, averaged PDHG as the multi-kernel
 // path (same kernels' epilogues, evaluation and decision logic), with the scalar state in
 // LDS and a workgroup barrier between the phases.
@@ -2171,7 +2223,7 @@ __device__ void wg_solve(const DevLP& P, const BatchJob& J, Scalars* ssc, double
     if (P.m > 0) wg_spmv(P.A.csr, static_cast<const double*>(P.x), EpiStore{P.ax, nullptr}, lds, red);
     wg_spmv(P.AT.csr, static_cast<const double*>(P.y), EpiStore{P.aty, nullptr}, lds, red);
     wg_kkt(P, 1, tot, red16);
-    if (tid == 0) decide_logic(P, ssc, tot, 1);
+    if (tid == 0) decide_logic(P, ssc, tot, 1, false);
     __syncthreads();
     if (ssc->status == kRunning) {
         for (int g = tid; g < mx; g += kBlock) save_prev_at(P, 0, true, g);
@@ -2213,7 +2265,8 @@ __device__ void wg_solve(const DevLP& P, const BatchJob& J, Scalars* ssc, double
             wg_spmv(P.A.csr, static_cast<const double*>(P.xa), EpiStore{P.axa, nullptr}, lds, red);
         wg_spmv(P.AT.csr, static_cast<const double*>(P.ya), EpiStore{P.atya, nullptr}, lds, red);
         wg_kkt(P, 0, tot, red16);
-        if (tid == 0) decide_logic(P, ssc, tot, 0);
+        const bool late = time_limit_passed<kBlock>(P, J, ssc, tot, red, lds, kTileNnzMax);
+        if (tid == 0) decide_logic(P, ssc, tot, 0, late);
         __syncthreads();
         const int lr = ssc->last_restart;
         if (ssc->status == kRunning) {

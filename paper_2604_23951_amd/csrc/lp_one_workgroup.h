@@ -513,7 +513,8 @@ __device__ __noinline__ void solo_evaluate(const BatchJob& J, int mode) {
     if (mode == 0 && (!halpern || FP32)) solo_product<NT, !FP32>(P.sA, A, m, n, P.xa, P.axa);
     if (mode == 0) solo_product<NT, !FP32>(P.sAT, AT, n, m, P.ya, P.atya);
     solo_kkt<NT>(P, mode, J.eval_blocks);
-    if (tid == 0) decide_logic(P, &S.sc, S.tot, mode);
+    const bool late = mode == 0 && time_limit_passed<NT>(P, J, &S.sc, S.tot, S.red, S.part, kSoloEvalBlocks * kNT);
+    if (tid == 0) decide_logic(P, &S.sc, S.tot, mode, late);
     __syncthreads();
     const bool running = S.sc.status == kRunning;
     const int lr = mode == 1 ? 1 : S.sc.last_restart;
@@ -528,18 +529,6 @@ __device__ __noinline__ void solo_evaluate(const BatchJob& J, int mode) {
         }
         __syncthreads();
     }
-}
-
-// Statistics of the point a time limit stopped at, with every sum in plain index order. Near
-// convergence the gap term is the difference of two nearly equal objective sums and the
-// grouping of their terms shows in it: a time-limited lp_solve, which gets arbitrarily close
-// within its limit, returns what the plain definition gives for the returned point.
-__device__ __noinline__ void plain_statistics(const DevLP& P, Scalars* sc) {
-    const bool cand = P.method != 0;
-    double acc[kNQ] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int i = 0; i < P.m; ++i) row_terms(P, i, cand ? P.axa : P.ax, cand ? P.ya : P.y, acc);
-    for (int j = 0; j < P.n; ++j) col_terms(P, j, cand ? P.xa : P.x, cand ? P.atya : P.aty, acc);
-    set_output(sc, make_kkt(acc, sc), sc->out_avg);
 }
 
 // One LP from start to stop in one workgroup; the phases are those of wg_solve.
@@ -568,7 +557,6 @@ __device__ __forceinline__ void solo_solve(const BatchJob& J) {
         solo_period<FORM, NT, KC, KR>(J, static_cast<int>(left < S.sc.eval_every ? left : S.sc.eval_every));
         solo_evaluate<NT, kFp32>(J, 0);
     }
-    if (J.plain_stop && S.sc.status == 2 && tid == 0) plain_statistics(P, &S.sc);
     for (int g = tid; g < mx; g += NT) {
         extract_at(P, S.sc.out_avg, S.sc.status, S.sc.ray_scale, S.sc.ray_src, g);
         result_to_host(J, &S.sc, g);
