@@ -345,36 +345,38 @@ int32_t lp_import_state(lp_handle *h, const void *buf, int64_t size);
 int32_t lp_update_options(lp_handle *h, const lp_options *opt);
 
 /* Batched form: solve the LPs of `count` handles (created on the same device) together.
- *  - LPs with at most batch_split_nnz nonzeros run in one persistent launch: each workgroup
- *    takes the next LP from a device work counter (largest first) and runs that LP's whole
- *    restarted PDHG on chip (row-tile sparse products with the fused updates, FP64
- *    evaluations, restart and termination decisions).
+ *  - LPs with at most batch_split_nnz nonzeros run in persistent launches (one per solver and
+ *    workgroup size that small_lp_lds gives them, beside one another): each workgroup takes the
+ *    next LP of its launch from a device work counter (largest first) and runs that LP's whole
+ *    restarted PDHG on chip (sparse products with the fused updates, FP64 evaluations, restart
+ *    and termination decisions).
  *  - Larger LPs advance together as one block-diagonal problem: every launch covers the row
  *    tiles of all of them, each LP with its own step sizes, restarts and termination;
  *    evaluation periods are replayed as one hipGraph for the group; when a quarter of the
  *    group has stopped the launches are rebuilt over the running LPs. Each such LP follows
  *    exactly the trajectory of its own lp_solve with the row-tile layout. The persistent
- *    launch runs on a stream of its own beside these launches.
+ *    launches run on streams of their own beside these launches.
  * Each LP's result depends only on that LP (not on the other LPs or on where it ran), so it
  * is the same alone and in any batch. The handles' precisions may differ.
  * Solve-time options: batch_opt's eps_rel, max_iters, time_limit_s, eval_every and restarts for every LP
  * when batch_opt is given, each handle's own otherwise (the LPs of the block-diagonal group
  * must then share eval_every); batch_opt->batch_wg_per_cu and batch_split_nnz set the
  * launches. Afterwards every handle is solved and lp_get_solution returns its result
- * (info.solve_seconds is the batch time). Runs on the first handle's stream (and a
- * temporary second stream for the persistent launch) and waits. */
+ * (info.solve_seconds is the batch time). Runs on the first handle's stream (and
+ * temporary streams for the persistent launches) and waits. */
 int32_t lp_solve_batch(lp_handle *const *hs, int32_t count, const lp_options *batch_opt);
 
 /* Allocation-free form of lp_solve_batch, for callers that cannot allocate device memory
  * (work issued inside a stream capture, tight serving loops, harnesses that forbid
  * hipMalloc). On success it calls no hipMalloc, hipFree, stream or event creation and no
  * other allocating routine; it still waits for the GPU before returning.
- *  - Every LP runs in the persistent one-workgroup-per-LP launch of lp_solve_batch, whatever
+ *  - Every LP runs in the persistent one-workgroup-per-LP launches of lp_solve_batch, whatever
  *    its size (lp_solve_batch sends LPs above batch_split_nnz to block-diagonal launches,
  *    whose per-call maps would need allocations). An LP's result is bit-identical to the one
- *    lp_solve_batch gives it in the persistent launch.
+ *    lp_solve_batch gives it in the persistent launches. Several launches run beside one another
+ *    on streams that the first lp_create of the device made.
  *  - The launch's job table, LP order and work counter live in a library-owned static device
- *    array of fixed size (LP_STATIC_BATCH_MAX jobs, 3.2 MB), one copy per device, held
+ *    array of fixed size (LP_STATIC_BATCH_MAX jobs, 7.2 MB), one copy per device, held
  *    until the process ends; the counter is cleared by a kernel at every call. count above
  *    LP_STATIC_BATCH_MAX returns LP_ERR_INVALID_ARG.
  *  - Every handle must already hold its device memory (created with deferred = 0, or solved

@@ -617,7 +617,7 @@ BatchJob make_job(lp_handle* h, const lp_options* bo) {
 // that (fewer waves meet at each barrier, and several such workgroups share a CU) when all of
 // it fits the LDS budget; the wider ones stage the slices that fit, those of A (the longer
 // rows of the two in most LPs, summed by fewer threads) first. Operands that no longer fit the
-// registers of 1024 threads stay in global memory. widest: 1024 threads whatever the size. An LP
+// registers of 1024 threads stay in global memory. least: as many threads at least. An LP
 // whose gathered vectors alone exceed the budget (every LP, at a budget of 0) has no plan; at
 // the largest budget an LP may ask for, they may take all of a workgroup's LDS (kSoloLdsMax),
 // since such an LP runs ~5 times faster with them there than as row tiles in global memory.
@@ -637,12 +637,12 @@ SoloPlan solo_stage_plan(const lp_handle* h, int budget, bool fp32) {
     return S;
 }
 
-SoloPlan solo_plan(const lp_handle* h, int budget, bool widest = false) {
+SoloPlan solo_plan(const lp_handle* h, int budget, int least = 256) {
     const int m = h->m, n = h->n, fp32 = h->opt.precision == LP_PREC_FP32_REFINED;
     SoloPlan S = solo_stage_plan(h, budget, fp32);
     if (S.lds == 0) return S;
     const int mx = std::max(m, n);
-    if (S.whole && mx <= 512 && !widest) S.variant = mx <= 256 ? SOLO_256 : SOLO_512;
+    if (S.whole && mx <= 512 && least <= 512) S.variant = mx <= 256 && least <= 256 ? SOLO_256 : SOLO_512;
     else if (solo_sorted(m, n)) S.variant = SOLO_1024;
     else if (n <= 4096 && m <= 2048) S.variant = SOLO_WIDE;
     else S.variant = solo_register_dims(m, n, fp32) ? SOLO_WIDE32 : SOLO_GLOBAL;
@@ -877,23 +877,26 @@ int group_solver(int group) {
 
 struct BatchGroups {
     int first[BG_COUNT] = {0}, count[BG_COUNT] = {0}, lds[BG_COUNT] = {0};
+    int least = 256, launches = 0;  // the least threads of the one-workgroup solver; groups with LPs
 };
 
-// A batch whose launches follow one another on one stream and whose LPs number at most the CUs
-// runs the one-workgroup solver in a single launch of 1024 threads per LP: the launches' times
-// would add up (their slowest LPs take about as long), and no workgroup has to share a CU. 64
-// LPs of 50 to 900 rows in FP32: three launches 5.06 ms, one 3.42 ms.
-bool one_launch(int count, int cus) { return count <= cus; }
+// A static batch whose LPs number at most the CUs runs the one-workgroup solver in a single
+// launch of 1024 threads per LP: no workgroup has to share a CU. 64 LPs of 50 to 900 rows in
+// FP32: three launches of 256 to 1024 threads, one behind the other, 5.06 ms, one 3.42 ms.
+int static_least_threads(int count, int cus) { return count <= cus ? 1024 : 256; }
 
 // Assigns every LP its launch: the one-workgroup solver for those that have its form, else the
 // row tiles (staged in LDS when the LP fits the budget). order[] lists the LPs launch by
 // launch, in each largest first (ties by position: a strict order, so the sort needs no
-// buffer).
-void group_batch(lp_handle* const* hs, int count, int budget, bool single, int32_t* order, uint8_t* group,
+// buffer). Launches on one stream follow one another: their slowest LPs' times add up, and an
+// LP of a later one may find its time limit passed before it starts. So there are at most
+// `streams` of them: the launches of 256, then of 512 threads join the next wider one.
+void group_batch(lp_handle* const* hs, int count, int budget, int least, int streams, int32_t* order, uint8_t* group,
                  BatchGroups* G) {
     *G = BatchGroups{};
+    G->least = least;
     for (int32_t i = 0; i < count; ++i) {
-        const SoloPlan plan = solo_plan(hs[i], budget, single);
+        const SoloPlan plan = solo_plan(hs[i], budget, least);
         int g, lds = plan.lds;
         if (plan.variant != SOLO_NONE) {
             const int threads = solo_threads(plan.variant);
@@ -909,6 +912,8 @@ void group_batch(lp_handle* const* hs, int count, int budget, bool single, int32
         G->count[g]++;
         G->lds[g] = std::max(G->lds[g], lds);
     }
+    for (int n : G->count) G->launches += n > 0;
+    if (G->launches > streams && least < 1024) return group_batch(hs, count, budget, 2 * least, streams, order, group, G);
     for (int g = 1; g < BG_COUNT; ++g) G->first[g] = G->first[g - 1] + G->count[g - 1];
     std::sort(order, order + count, [&](int32_t a, int32_t b) {
         if (group[a] != group[b]) return group[a] < group[b];
@@ -930,7 +935,50 @@ void launch_group(const BatchGroups& G, int g, const BatchJob* jobs, const int32
                      G.lds[g]);
 }
 
-int32_t start_persistent(const std::vector<lp_handle*>& hs, const lp_options* bo, PersistentRun& R) {
+// Every launch on a stream of its own, the row tiles' (the slowest LPs) first.
+hipError_t launch_groups(const BatchGroups& G, const BatchJob* jobs, const int32_t* order, int32_t* counters, int cus,
+                         int wpc, const hipStream_t* streams) {
+    static constexpr int kFirstTo[BG_COUNT] = {BG_TILES, BG_TILES_LDS, BG_SOLO_1024, BG_SOLO_512, BG_SOLO_256};
+    hipError_t e = hipSuccess;
+    int l = 0;
+    for (int g : kFirstTo) {
+        if (G.count[g] == 0 || e != hipSuccess) continue;
+        launch_group(G, g, jobs, order, counters, cus, wpc, streams[l++]);
+        e = hipGetLastError();
+    }
+    return e;
+}
+
+// The streams of lp_solve_batch_static's launches when it has several. It creates nothing, so
+// they are made with the first handle that a device holds, and kept until the process ends
+// like the call's device array. Created together they lie on hardware queues of their own (see
+// PersistentRun). Without them (none could be created) the launches follow one another.
+constexpr int kStaticStreams = 3;  // the row tiles' two launches and one of the one-workgroup solver
+
+bool static_batch_streams(int device, bool create, hipStream_t* out) {
+    constexpr int kMaxDevices = 64;
+    static std::mutex mu;
+    static hipStream_t streams[kMaxDevices][kStaticStreams] = {};
+    static bool tried[kMaxDevices] = {};
+    if (device < 0 || device >= kMaxDevices) return false;
+    std::lock_guard<std::mutex> lk(mu);
+    hipStream_t* st = streams[device];
+    if (create && !tried[device]) {
+        tried[device] = true;
+        int made = 0;
+        while (made < kStaticStreams && hipStreamCreateWithFlags(&st[made], hipStreamNonBlocking) == hipSuccess) ++made;
+        if (made < kStaticStreams) {
+            (void)hipGetLastError();
+            for (int i = 0; i < made; ++i) (void)hipStreamDestroy(st[i]);
+            for (int i = 0; i < kStaticStreams; ++i) st[i] = nullptr;
+        }
+    }
+    for (int i = 0; out && i < kStaticStreams; ++i) out[i] = st[i];
+    return st[0] != nullptr;
+}
+
+// streams: how many of R.s its launches may take (the block-diagonal launches get the last).
+int32_t start_persistent(const std::vector<lp_handle*>& hs, const lp_options* bo, int streams, PersistentRun& R) {
     const int count = static_cast<int>(hs.size());
     lp_handle* h0 = hs[0];
     for (lp_handle* h : hs)
@@ -938,13 +986,13 @@ int32_t start_persistent(const std::vector<lp_handle*>& hs, const lp_options* bo
     const int budget = bo ? bo->small_lp_lds : h0->opt.small_lp_lds;
     R.jobs.resize(static_cast<size_t>(count));
     R.order.resize(static_cast<size_t>(count));
-    for (int i = 0; i < count; ++i) {
-        R.jobs[i] = make_job(hs[i], bo);
-        solo_plan(hs[i], budget).apply(&R.jobs[i]);
-    }
     R.group.resize(static_cast<size_t>(count));
     BatchGroups G;
-    group_batch(hs.data(), count, budget, false, R.order.data(), R.group.data(), &G);
+    group_batch(hs.data(), count, budget, 256, streams, R.order.data(), R.group.data(), &G);
+    for (int i = 0; i < count; ++i) {
+        R.jobs[i] = make_job(hs[i], bo);
+        solo_plan(hs[i], budget, G.least).apply(&R.jobs[i]);
+    }
     int cus = 256;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h0->device) != hipSuccess || cus < 1)
         cus = 256;
@@ -967,11 +1015,7 @@ int32_t start_persistent(const std::vector<lp_handle*>& hs, const lp_options* bo
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(R.s[0]);
-    static constexpr int kStreamOf[BG_COUNT] = {0, 1, 2, 1, 2};
-    for (int g = 0; g < BG_COUNT && e == hipSuccess; ++g) {
-        launch_group(G, g, djobs, dorder, dcounters, cus, wpc, R.s[kStreamOf[g]]);
-        e = hipGetLastError();
-    }
+    if (e == hipSuccess) e = launch_groups(G, djobs, dorder, dcounters, cus, wpc, R.s);
     if (e != hipSuccess) return fail(h0, LP_ERR_DEVICE, std::string("batched solve: ") + hipGetErrorString(e));
     return LP_OK;
 }
@@ -1683,6 +1727,7 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     if (int32_t rc = check_launch(h, "setup kernels")) return rc;
     HIP_TRY(h, hipMemcpyAsync(h->h_sc, P.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
+    if (!h->pool) (void)static_batch_streams(h->device, true, nullptr);
     h->on_device = true;
     return LP_OK;
 }
@@ -2858,7 +2903,7 @@ int32_t lp_solve_batch(lp_handle* const* hs, int32_t count, const lp_options* bo
         const auto t0 = std::chrono::steady_clock::now();
         PersistentRun pr;
         if (!small.empty()) {
-            if (int32_t rc = start_persistent(small, bo, pr)) {
+            if (int32_t rc = start_persistent(small, bo, big.empty() ? 4 : 3, pr)) {
                 (void)finish_persistent(small, pr, false);
                 return rc;
             }
@@ -2920,8 +2965,10 @@ int32_t lp_solve_batch_static(lp_handle* const* hs, int32_t count, const lp_opti
         BatchGroups G;
         int cus = 256;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-        const bool single = one_launch(count, cus);
-        group_batch(hs, count, budget, single, order, group, &G);
+        hipStream_t side[kStaticStreams];
+        const bool beside = static_batch_streams(dev, false, side);
+        group_batch(hs, count, budget, static_least_threads(count, cus), kStaticStreams, order, group, &G);
+        if (!beside || G.launches == 1) std::fill(side, side + kStaticStreams, s);
         // job table through a small stack buffer, copied chunk by chunk on the stream
         constexpr int32_t kChunk = 16;
         BatchJob buf[kChunk];
@@ -2930,7 +2977,7 @@ int32_t lp_solve_batch_static(lp_handle* const* hs, int32_t count, const lp_opti
             for (int32_t j = 0; j < nb; ++j) {
                 buf[j] = make_job(hs[i + j], bo);
                 buf[j].t0 = S.t0;
-                solo_plan(hs[i + j], budget, single).apply(&buf[j]);
+                solo_plan(hs[i + j], budget, G.least).apply(&buf[j]);
             }
             HIP_TRY(h0, hipMemcpyAsync(S.jobs + i, buf, sizeof(BatchJob) * nb, hipMemcpyHostToDevice, s));
             HIP_TRY(h0, hipStreamSynchronize(s));
@@ -2939,9 +2986,14 @@ int32_t lp_solve_batch_static(lp_handle* const* hs, int32_t count, const lp_opti
         HIP_TRY(h0, hipStreamSynchronize(s));  // `order` is on this stack frame
         launch_batch_start(S.counter, S.t0, s);
         const int wpc = (bo && bo->batch_wg_per_cu > 0) ? bo->batch_wg_per_cu : 3;
-        for (int g = 0; g < BG_COUNT; ++g) launch_group(G, g, S.jobs, S.order, S.counter, cus, wpc, s);
-        if (int32_t rc = check_launch(h0, "allocation-free batched solve")) return rc;
-        HIP_TRY(h0, hipStreamSynchronize(s));
+        if (G.launches > 1) HIP_TRY(h0, hipStreamSynchronize(s));  // the other streams start after it
+        hipError_t e = launch_groups(G, S.jobs, S.order, S.counter, cus, wpc, side);
+        for (int l = 0; l < G.launches; ++l) {  // all of them, also after an error
+            const hipError_t e1 = hipStreamSynchronize(side[l]);
+            if (e == hipSuccess) e = e1;
+        }
+        if (e != hipSuccess)
+            return fail(h0, LP_ERR_DEVICE, std::string("allocation-free batched solve: ") + hipGetErrorString(e));
         auto written = [&](int i) { return group[i] <= BG_SOLO_256 && hs[i]->h_res != nullptr; };
         if (int32_t rc = finish_batch(hs, count, s, written, [&](int i) { return group_solver(group[i]); })) return rc;
         const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
