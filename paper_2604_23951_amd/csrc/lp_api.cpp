@@ -784,6 +784,9 @@ struct DevMaps {
         M.map_elem = reinterpret_cast<const int2*>(buf + oel);
         M.n_elem = static_cast<int>(melem.size());
         M.active = reinterpret_cast<int*>(buf + ost);
+        long long bytes[2] = {0, 0};  // entries of A and A^T: value and column
+        for (const lp_handle* h : hs) bytes[h->P.fp32 ? 1 : 0] += 2LL * h->nnz * (h->P.fp32 ? 8 : 12);
+        M.keep = keep_multi(bytes[0], bytes[1]) ? 1 : 0;
         auto H2D = [&](size_t off, const void* src, size_t bytes) {
             return bytes ? hipMemcpyAsync(buf + off, src, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
         };
@@ -1475,9 +1478,9 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     P.nnz = nnz;
     P.nred = Q.nred;
     P.A.csr = Csr{m, ntA, static_cast<int>(nnz), Q.shape, I(O.arp), I(O.aci), D(O.av), I(O.at), nullptr, nullptr, n,
-                  tile_nnz_of(Q.shape), reinterpret_cast<const TileRec*>(b + O.rA)};
+                  tile_nnz_of(Q.shape), reinterpret_cast<const TileRec*>(b + O.rA), nnz * 24 <= kKeepTiles ? 1 : 0};
     P.AT.csr = Csr{n, ntAT, static_cast<int>(nnz), Q.shape, I(O.trp), I(O.tci), D(O.tv), I(O.tt), nullptr, nullptr, m,
-                   tile_nnz_of(Q.shape), reinterpret_cast<const TileRec*>(b + O.rAT)};
+                   tile_nnz_of(Q.shape), reinterpret_cast<const TileRec*>(b + O.rAT), P.A.csr.keep};
     P.A.layout = P.AT.layout = panels ? 0 : 1;
     auto bind_layout = [&](const PanelLayoutHost& L, const size_t* off, Mat& M) {
         M.pan = Panels{L.units, L.panels, L.col_bits, static_cast<int>(L.nnz_packed), L.max_unit_rows, I(off[0]), I(off[1]),
@@ -1549,7 +1552,7 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
         T.v = fp32 ? nullptr : D(off[9]);
         T.v32 = fp32 ? reinterpret_cast<const float*>(b + off[9]) : nullptr;
         T.is_long = M.pan.is_long;
-        T.keep = nnz * (fp32 ? 20LL : 32LL) <= kTpKeepBytes ? 1 : 0;
+        T.keep = nnz * (fp32 ? 20LL : 32LL) <= kKeepTwoPhase ? 1 : 0;
         T.tiles_short = H.tiles_short;
         T.longs = I(off[10]);
         T.nhuge = static_cast<int>(H.huge.size());

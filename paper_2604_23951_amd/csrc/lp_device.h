@@ -53,6 +53,23 @@ struct Scalars {
     int ray_src;       // candidate ray of a certificate: 1 displacement since the previous evaluation, 2 anchored average
 };
 
+// What an iteration streams of its matrices up to which plain loads, which may stay in the 256 MB
+// Infinity Cache from one iteration to the next, beat non-temporal ones. us per iteration, plain /
+// non-temporal:
+// - two phases (entries of both matrices and the products): 144 MB 80 / 91, 154 MB 86 / 99, 230 MB
+//   144 / 138, 240 MB 140 / 137, 384 MB 209 / 207;
+// - FP64 row tiles of one LP (entries of both): power-law columns 69 MB 67 / 73, 115 MB 117 / 121,
+//   137 MB 144 / 147, 165 MB 184 / 180, 184 MB 213 / 207, 275 MB 361 / 354; uniform columns 92 MB
+//   76 / 83, 137 MB 126 / 128, 184 MB 195 / 191;
+// - block-diagonal launches (all their LPs), FP64: 137 MB 86 / 94, 179 MB 117 / 119, 211 MB 139 /
+//   136, 579 MB 367 / 362; FP32: 140 MB 86 / 93, 211 MB 129 / 133, 281 MB 172 / 173, 421 MB 256 /
+//   252.
+constexpr long long kKeepTwoPhase = 192LL << 20, kKeepTiles = 144LL << 20;
+// Of the block-diagonal launches' LPs: `bytes64` in the FP64 form, `bytes32` in the FP32 form.
+constexpr bool keep_multi(long long bytes64, long long bytes32) {
+    return 5 * bytes64 + 3 * bytes32 <= 5 * (192LL << 20);
+}
+
 // A row tile: rows [r0, r1), entries [p0, p1).
 struct TileRec {
     int r0, r1, p0, p1;
@@ -76,6 +93,7 @@ struct Csr {
     int cols;          // length of the vector the products gather from
     int tree_len;      // rows longer than this are reduced by a whole workgroup (at most the tile's nonzeros)
     const TileRec* recs;
+    int keep;  // row tiles of FP64 launches: plain loads of the matrix (kKeepTiles), else non-temporal ones
 };
 
 // Panel-packed layout (see lp_layout.h): unit u (one wave) owns rows
@@ -125,7 +143,7 @@ struct TwoPhase {
     const unsigned short *lcol, *pos;
     const double* v;   // FP64 form only
     const float* v32;  // FP32 storage form only
-    int keep;                      // plain loads of the matrix (see kTpKeepBytes), else non-temporal ones
+    int keep;                      // plain loads of the matrix (see kKeepTwoPhase), else non-temporal ones
     const unsigned char* is_long;  // as in Panels
     const int* longs;
     int nhuge;          // rows longer than a tile, each reduced by a workgroup from its gathers
@@ -135,10 +153,6 @@ struct TwoPhase {
 constexpr int kTpMaxBlocks = 1024;
 constexpr int kTpSplit = 2;  // workgroups that share a block's entries
 constexpr int kTpXcds = 8;
-// What an iteration streams (entries of both matrices, the products) up to which plain loads,
-// which may stay in the 256 MB Infinity Cache, beat non-temporal ones. us per iteration, plain /
-// non-temporal: 144 MB 80 / 91, 154 MB 86 / 99, 230 MB 144 / 138, 240 MB 140 / 137, 384 MB 209 / 207.
-constexpr long long kTpKeepBytes = 192LL << 20;
 constexpr int kTpLds = 64 * 1024;      // of the gathered slice at most
 constexpr int kTpTileLds = 64 * 1024;  // of a tile's products at most (FP64)
 constexpr int kTpTileLds32 = 39 * 1024;  // (FP32)
@@ -272,6 +286,7 @@ struct MultiMaps {
     // [off_a[g], off_a[g] + cnt_a[g]) of map_a (and likewise of map_at), so every launch runs
     // one kernel specialised per form and shape present.
     int off_a[12], cnt_a[12], off_at[12], cnt_at[12];
+    int keep;  // plain loads of the matrices (see keep_multi)
 };
 
 constexpr int kMapGroups = 4 * kTileShapes;

@@ -240,11 +240,9 @@ __device__ __forceinline__ T stream_load(const T* p) {
     else return __builtin_nontemporal_load(p);
 }
 
-// KEEP: matrices that the 256 MB Infinity Cache holds from one iteration to the next are read
-// with plain loads, which may stay in it (us per iteration, non-temporal / plain: 22 LPs with
-// 5.5M entries together, FP32, 44 / 38; FP64, single: 993k entries 17.2 / 16.2, 1.7M 38.7 / 35.2,
-// 2.4M 62.0 / 57.1). A single FP32 launch keeps the non-temporal loads: its smaller matrix
-// then competes with the gathered vectors for the L2 (1.7M entries 29.3 / 30.2).
+// KEEP: plain loads of the matrix (see kKeepTiles and keep_multi). A single FP32 launch keeps the
+// non-temporal loads: its smaller matrix then competes with the gathered vectors for the L2
+// (1.7M entries, us per iteration non-temporal / plain: 29.3 / 30.2).
 template <int TN, bool KEEP, class T, class Epi>
 __device__ void tile_body(const Csr& M, const TileRec& tile, const T* __restrict__ xin, const Epi& epi, T* prod, double* red) {
     constexpr int kPerThread = TN / kBlock;
@@ -306,12 +304,12 @@ __device__ inline void tile_body_any(const Csr& M, int b, const T* __restrict__ 
     else tile_body<tile_nnz_of(2), false>(M, tile, xin, epi, prod, red);
 }
 
-template <class T, class Epi, int TN>
+template <class T, class Epi, int TN, bool KEEP>
 __global__ __launch_bounds__(kBlock) void spmv_tiles_kernel(Csr M, const T* __restrict__ xin, Epi epi) {
     __shared__ T prod[TN];
     __shared__ double red[kBlock / 64];
     if (!epi.begin()) return;
-    tile_body<TN, sizeof(T) == 8>(M, M.recs[blockIdx.x], xin, epi, prod, red);
+    tile_body<TN, KEEP>(M, M.recs[blockIdx.x], xin, epi, prod, red);
 }
 
 // Panel-packed SpMV over wave units of rows. The entries of a unit are walked in packed order,
@@ -1146,12 +1144,16 @@ __host__ __device__ inline EpiDual32H epi_dual32_h(const DevLP& P, const Scalars
 template <class T, class Epi>
 void launch_tiles(const Csr& M, const T* xin, const Epi& epi, hipStream_t s) {
     if (M.ntiles <= 0) return;
-    if (M.shape == 0)
-        hipLaunchKernelGGL((spmv_tiles_kernel<T, Epi, tile_nnz_of(0)>), dim3(M.ntiles), dim3(kBlock), 0, s, M, xin, epi);
-    else if (M.shape == 1)
-        hipLaunchKernelGGL((spmv_tiles_kernel<T, Epi, tile_nnz_of(1)>), dim3(M.ntiles), dim3(kBlock), 0, s, M, xin, epi);
-    else
-        hipLaunchKernelGGL((spmv_tiles_kernel<T, Epi, tile_nnz_of(2)>), dim3(M.ntiles), dim3(kBlock), 0, s, M, xin, epi);
+    constexpr bool kMayKeep = sizeof(T) == 8;
+    const dim3 grid(M.ntiles), block(kBlock);
+    auto run = [&](auto tn) {
+        constexpr int TN = decltype(tn)::value;
+        if (kMayKeep && M.keep) hipLaunchKernelGGL((spmv_tiles_kernel<T, Epi, TN, kMayKeep>), grid, block, 0, s, M, xin, epi);
+        else hipLaunchKernelGGL((spmv_tiles_kernel<T, Epi, TN, false>), grid, block, 0, s, M, xin, epi);
+    };
+    if (M.shape == 0) run(std::integral_constant<int, tile_nnz_of(0)>{});
+    else if (M.shape == 1) run(std::integral_constant<int, tile_nnz_of(1)>{});
+    else run(std::integral_constant<int, tile_nnz_of(2)>{});
 }
 
 // One sparse product with its fused epilogue: one launch holding the panel-packed units and,
@@ -2446,16 +2448,16 @@ __global__ __launch_bounds__(kBlock) void batch_kernel(const BatchJob* jobs, con
 enum MultiKind { MK_PRIMAL = 0, MK_DUAL, MK_AX_ALL, MK_AX_FP32, MK_ATY, MK_AXA, MK_ATYA };
 
 // One row tile with an epilogue whose begin() may decline the work (LP stopped).
-template <int TN, class T, class Epi>
+template <int TN, bool KEEP, class T, class Epi>
 __device__ inline void run_tile(const Csr& M, const TileRec& tile, const T* xin, Epi e, T* prod, double* red) {
     if (!e.begin()) return;
-    tile_body<TN, true>(M, tile, xin, e, prod, red);
+    tile_body<TN, KEEP>(M, tile, xin, e, prod, red);
 }
 
 // FORM = 2 * fp32 + method for the iteration kinds (one instance per form: the four fused
 // epilogues in one kernel would hold the registers of the largest and halve occupancy), -1
 // for the evaluation products; TN the row-tile shape of the LPs of the launch.
-template <int KIND, int FORM, int TN>
+template <int KIND, int FORM, int TN, bool KEEP>
 __global__ __launch_bounds__(kBlock) void multi_tiles_kernel(const BatchJob* jobs, const MapTile* map, int it) {
     __shared__ double lds[TN];
     __shared__ double red[kBlock / 64];
@@ -2463,15 +2465,15 @@ __global__ __launch_bounds__(kBlock) void multi_tiles_kernel(const BatchJob* job
     const DevLP& P = jobs[mt.job].P;
     float* lds32 = reinterpret_cast<float*>(lds);
     if constexpr (KIND == MK_PRIMAL) {
-        if constexpr (FORM == 3) run_tile<TN>(P.AT.csr, mt.tile, static_cast<const float*>(P.dy), epi_primal32_h(P, P.sc, it), lds32, red);
-        else if constexpr (FORM == 2) run_tile<TN>(P.AT.csr, mt.tile, static_cast<const float*>(P.dy), epi_primal32(P, P.sc, it), lds32, red);
-        else if constexpr (FORM == 1) run_tile<TN>(P.AT.csr, mt.tile, static_cast<const double*>(P.y), epi_primal_h(P, P.sc, it), lds, red);
-        else run_tile<TN>(P.AT.csr, mt.tile, static_cast<const double*>(P.y), epi_primal(P, P.sc, it), lds, red);
+        if constexpr (FORM == 3) run_tile<TN, KEEP>(P.AT.csr, mt.tile, static_cast<const float*>(P.dy), epi_primal32_h(P, P.sc, it), lds32, red);
+        else if constexpr (FORM == 2) run_tile<TN, KEEP>(P.AT.csr, mt.tile, static_cast<const float*>(P.dy), epi_primal32(P, P.sc, it), lds32, red);
+        else if constexpr (FORM == 1) run_tile<TN, KEEP>(P.AT.csr, mt.tile, static_cast<const double*>(P.y), epi_primal_h(P, P.sc, it), lds, red);
+        else run_tile<TN, KEEP>(P.AT.csr, mt.tile, static_cast<const double*>(P.y), epi_primal(P, P.sc, it), lds, red);
     } else if constexpr (KIND == MK_DUAL) {
-        if constexpr (FORM == 3) run_tile<TN>(P.A.csr, mt.tile, static_cast<const float*>(P.dxa), epi_dual32_h(P, P.sc, it), lds32, red);
-        else if constexpr (FORM == 2) run_tile<TN>(P.A.csr, mt.tile, static_cast<const float*>(P.dx), epi_dual32(P, P.sc, it), lds32, red);
-        else if constexpr (FORM == 1) run_tile<TN>(P.A.csr, mt.tile, static_cast<const double*>(P.xa), epi_dual_h(P, P.sc, it), lds, red);
-        else run_tile<TN>(P.A.csr, mt.tile, static_cast<const double*>(P.x), epi_dual(P, P.sc, it), lds, red);
+        if constexpr (FORM == 3) run_tile<TN, KEEP>(P.A.csr, mt.tile, static_cast<const float*>(P.dxa), epi_dual32_h(P, P.sc, it), lds32, red);
+        else if constexpr (FORM == 2) run_tile<TN, KEEP>(P.A.csr, mt.tile, static_cast<const float*>(P.dx), epi_dual32(P, P.sc, it), lds32, red);
+        else if constexpr (FORM == 1) run_tile<TN, KEEP>(P.A.csr, mt.tile, static_cast<const double*>(P.xa), epi_dual_h(P, P.sc, it), lds, red);
+        else run_tile<TN, KEEP>(P.A.csr, mt.tile, static_cast<const double*>(P.x), epi_dual(P, P.sc, it), lds, red);
     } else {
         if (P.sc->status != kRunning) return;
         if (KIND == MK_AX_FP32 && (!P.fp32 || P.method)) return;
@@ -2482,7 +2484,7 @@ __global__ __launch_bounds__(kBlock) void multi_tiles_kernel(const BatchJob* job
         const bool onA = KIND == MK_AX_ALL || KIND == MK_AX_FP32 || KIND == MK_AXA;
         const double* xin = KIND == MK_ATY ? P.y : KIND == MK_ATYA ? P.ya : KIND == MK_AXA ? P.xa : P.x;
         double* out = KIND == MK_ATY ? P.aty : KIND == MK_ATYA ? P.atya : KIND == MK_AXA ? P.axa : P.ax;
-        tile_body<TN, true>(onA ? P.A.csr : P.AT.csr, mt.tile, xin, EpiStore{out, nullptr}, lds, red);
+        tile_body<TN, KEEP>(onA ? P.A.csr : P.AT.csr, mt.tile, xin, EpiStore{out, nullptr}, lds, red);
     }
 }
 
@@ -2751,15 +2753,21 @@ void launch_apply_restart(const DevLP& P, hipStream_t s) {
 
 // Tile launches of one kind: one per group of the maps (form v = 2 * fp32 + method and
 // row-tile shape h, group g = 3 v + h), each with the kernel instance of its form and shape.
+template <int KIND, int FORM, int TN>
+void multi_tiles_launch(const MultiMaps& M, int n, const MapTile* map, int it_or_mode, hipStream_t s) {
+    if (M.keep) hipLaunchKernelGGL((multi_tiles_kernel<KIND, FORM, TN, true>), dim3(n), dim3(kBlock), 0, s, M.jobs, map, it_or_mode);
+    else hipLaunchKernelGGL((multi_tiles_kernel<KIND, FORM, TN, false>), dim3(n), dim3(kBlock), 0, s, M.jobs, map, it_or_mode);
+}
+
 template <int KIND, int FORM>
 void multi_tiles_group(const MultiMaps& M, int g, bool on_a, int it_or_mode, hipStream_t s) {
     const int n = on_a ? M.cnt_a[g] : M.cnt_at[g];
     if (n <= 0) return;
     const MapTile* map = on_a ? M.map_a + M.off_a[g] : M.map_at + M.off_at[g];
     switch (g % kTileShapes) {
-        case 0: hipLaunchKernelGGL((multi_tiles_kernel<KIND, FORM, tile_nnz_of(0)>), dim3(n), dim3(kBlock), 0, s, M.jobs, map, it_or_mode); break;
-        case 1: hipLaunchKernelGGL((multi_tiles_kernel<KIND, FORM, tile_nnz_of(1)>), dim3(n), dim3(kBlock), 0, s, M.jobs, map, it_or_mode); break;
-        default: hipLaunchKernelGGL((multi_tiles_kernel<KIND, FORM, tile_nnz_of(2)>), dim3(n), dim3(kBlock), 0, s, M.jobs, map, it_or_mode); break;
+        case 0: multi_tiles_launch<KIND, FORM, tile_nnz_of(0)>(M, n, map, it_or_mode, s); break;
+        case 1: multi_tiles_launch<KIND, FORM, tile_nnz_of(1)>(M, n, map, it_or_mode, s); break;
+        default: multi_tiles_launch<KIND, FORM, tile_nnz_of(2)>(M, n, map, it_or_mode, s); break;
     }
 }
 
