@@ -199,14 +199,17 @@ __device__ void row_tree_body(const Csr& M, int r, const T* __restrict__ xin, co
     if (tid == 0) epi.finish(r, s, pre);
 }
 
-// Sum of prod[q, qe) in order, eight values read together and the next eight while these are
-// added: in a tile of long rows few threads sum while the others wait, and read four at a
-// time with the adds in between every group pays the LDS latency (~130 cycles).
-template <class T>
+// Sum of prod[q, qe) in order. AHEAD: eight values read together and the next eight while these
+// are added: in a tile of long rows few threads sum while the others wait, and read four at a
+// time with the adds in between every group pays the LDS latency (~130 cycles). Not in the FP64
+// block-diagonal launches, where its registers cost a wave per SIMD (us per iteration, four at
+// a time / ahead: 110 LPs of 230k entries 362 / 389, 30 LPs of dense rows 202 / 207; in FP32
+// 160 LPs 342 / 335, 40 of dense rows 157 / 156).
+template <bool AHEAD, class T>
 __device__ inline T row_sum(const T* prod, int q, int qe) {
     constexpr int U = 8;
     T s = 0;
-    if (qe - q >= 2 * U) {
+    if (AHEAD && qe - q >= 2 * U) {
         T a[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) a[k] = prod[q + k];
@@ -243,7 +246,7 @@ __device__ __forceinline__ T stream_load(const T* p) {
 // KEEP: plain loads of the matrix (see kKeepTiles and keep_multi). A single FP32 launch keeps the
 // non-temporal loads: its smaller matrix then competes with the gathered vectors for the L2
 // (1.7M entries, us per iteration non-temporal / plain: 29.3 / 30.2).
-template <int TN, bool KEEP, class T, class Epi>
+template <int TN, bool KEEP, bool AHEAD, class T, class Epi>
 __device__ void tile_body(const Csr& M, const TileRec& tile, const T* __restrict__ xin, const Epi& epi, T* prod, double* red) {
     constexpr int kPerThread = TN / kBlock;
     constexpr int kRowsPerThread = TN / 4 / kBlock;
@@ -285,7 +288,7 @@ __device__ void tile_body(const Csr& M, const TileRec& tile, const T* __restrict
         for (int j = 0; j < kRowsPerThread; ++j) {
             const int r = r0 + tid + j * kBlock;
             if (r < r1) {
-                epi.finish(r, row_sum(prod, q0[j], q1[j]), pre[j]);
+                epi.finish(r, row_sum<AHEAD>(prod, q0[j], q1[j]), pre[j]);
             }
         }
     } else {
@@ -299,9 +302,9 @@ __device__ inline void tile_body_any(const Csr& M, int b, const T* __restrict__ 
                                      double* red) {
     const int r0 = M.tiles[b], r1 = M.tiles[b + 1];
     const TileRec tile{r0, r1, M.rp[r0], M.rp[r1]};
-    if (M.shape == 0) tile_body<tile_nnz_of(0), false>(M, tile, xin, epi, prod, red);
-    else if (M.shape == 1) tile_body<tile_nnz_of(1), false>(M, tile, xin, epi, prod, red);
-    else tile_body<tile_nnz_of(2), false>(M, tile, xin, epi, prod, red);
+    if (M.shape == 0) tile_body<tile_nnz_of(0), false, true>(M, tile, xin, epi, prod, red);
+    else if (M.shape == 1) tile_body<tile_nnz_of(1), false, true>(M, tile, xin, epi, prod, red);
+    else tile_body<tile_nnz_of(2), false, true>(M, tile, xin, epi, prod, red);
 }
 
 template <class T, class Epi, int TN, bool KEEP>
@@ -309,7 +312,7 @@ __global__ __launch_bounds__(kBlock) void spmv_tiles_kernel(Csr M, const T* __re
     __shared__ T prod[TN];
     __shared__ double red[kBlock / 64];
     if (!epi.begin()) return;
-    tile_body<TN, KEEP>(M, M.recs[blockIdx.x], xin, epi, prod, red);
+    tile_body<TN, KEEP, true>(M, M.recs[blockIdx.x], xin, epi, prod, red);
 }
 
 // Panel-packed SpMV over wave units of rows. The entries of a unit are walked in packed order,
@@ -2451,7 +2454,7 @@ enum MultiKind { MK_PRIMAL = 0, MK_DUAL, MK_AX_ALL, MK_AX_FP32, MK_ATY, MK_AXA, 
 template <int TN, bool KEEP, class T, class Epi>
 __device__ inline void run_tile(const Csr& M, const TileRec& tile, const T* xin, Epi e, T* prod, double* red) {
     if (!e.begin()) return;
-    tile_body<TN, KEEP>(M, tile, xin, e, prod, red);
+    tile_body<TN, KEEP, sizeof(T) == 4>(M, tile, xin, e, prod, red);
 }
 
 // FORM = 2 * fp32 + method for the iteration kinds (one instance per form: the four fused
@@ -2484,7 +2487,7 @@ __global__ __launch_bounds__(kBlock) void multi_tiles_kernel(const BatchJob* job
         const bool onA = KIND == MK_AX_ALL || KIND == MK_AX_FP32 || KIND == MK_AXA;
         const double* xin = KIND == MK_ATY ? P.y : KIND == MK_ATYA ? P.ya : KIND == MK_AXA ? P.xa : P.x;
         double* out = KIND == MK_ATY ? P.aty : KIND == MK_ATYA ? P.atya : KIND == MK_AXA ? P.axa : P.ax;
-        tile_body<TN, KEEP>(onA ? P.A.csr : P.AT.csr, mt.tile, xin, EpiStore{out, nullptr}, lds, red);
+        tile_body<TN, KEEP, false>(onA ? P.A.csr : P.AT.csr, mt.tile, xin, EpiStore{out, nullptr}, lds, red);
     }
 }
 

@@ -178,12 +178,12 @@ __global__ __launch_bounds__(kTpThreads, 6) void tp_rows_kernel(TwoPhase M, Csr 
 #pragma unroll
     for (int k = 0; k < kRows; ++k) {
         const int r = r0 + tid + k * kTpThreads;
-        if (r < r1 && !(M.is_long && M.is_long[r])) epi.finish(r, row_sum(prod, a[k], b[k]), pre[k]);
+        if (r < r1 && !(M.is_long && M.is_long[r])) epi.finish(r, row_sum<true>(prod, a[k], b[k]), pre[k]);
     }
     for (int r = r0 + tid + kRows * kTpThreads; r < r1; r += kTpThreads) {
         if (M.is_long && M.is_long[r]) continue;
         const typename Epi::Pre p = epi.load(r);
-        epi.finish(r, row_sum(prod, trp[r] - p0, trp[r + 1] - p0), p);
+        epi.finish(r, row_sum<true>(prod, trp[r] - p0, trp[r + 1] - p0), p);
     }
 }
 
