@@ -41,30 +41,45 @@ public:
         std::lock_guard<std::mutex> lk(mu_);
         admitted_ -= static_cast<int64_t>(need);
     }
-    // Memory for an admitted request: a free block (*held bytes of it) or a new one.
+    // Memory for an admitted request: a free block (*held bytes of it) or a new one. Nothing is
+    // allocated or released under the lock: a release waits for the whole device, and admit() is
+    // called with the server's own lock held.
     Error take(size_t need, char** out, size_t* held) {
-        std::lock_guard<std::mutex> lk(mu_);
-        size_t best = free_.size();
-        for (size_t i = 0; i < free_.size(); ++i)
-            if (free_[i].second >= need && (best == free_.size() || free_[i].second < free_[best].second)) best = i;
-        if (best < free_.size() && admitted_ + over_ + static_cast<int64_t>(free_[best].second - need) <= budget_) {
-            *out = free_[best].first;
-            *held = free_[best].second;
-            free_bytes_ -= static_cast<int64_t>(*held);
-            taken_ += static_cast<int64_t>(*held);
-            over_ += static_cast<int64_t>(*held - need);
-            free_.erase(free_.begin() + static_cast<std::ptrdiff_t>(best));
-            return Memory::ok();
+        std::vector<char*> drop;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            size_t best = free_.size();
+            for (size_t i = 0; i < free_.size(); ++i)
+                if (free_[i].second >= need && (best == free_.size() || free_[i].second < free_[best].second)) best = i;
+            if (best < free_.size() && admitted_ + over_ + static_cast<int64_t>(free_[best].second - need) <= budget_) {
+                *out = free_[best].first;
+                *held = free_[best].second;
+                free_bytes_ -= static_cast<int64_t>(*held);
+                taken_ += static_cast<int64_t>(*held);
+                over_ += static_cast<int64_t>(*held - need);
+                free_.erase(free_.begin() + static_cast<std::ptrdiff_t>(best));
+                return Memory::ok();
+            }
+            while (!free_.empty() && taken_ + free_bytes_ + static_cast<int64_t>(need) > budget_) drop.push_back(detach());
+            taken_ += static_cast<int64_t>(need);
         }
-        while (!free_.empty() && taken_ + free_bytes_ + static_cast<int64_t>(need) > budget_) drop_one();
+        for (char* p : drop) memory_.release(p);
         Error e = memory_.allocate(out, need);
-        while (Memory::out_of_memory(e) && !free_.empty()) {
-            drop_one();
+        while (Memory::out_of_memory(e)) {
+            char* p = nullptr;
+            {
+                std::lock_guard<std::mutex> lk(mu_);
+                if (!free_.empty()) p = detach();
+            }
+            if (!p) break;
+            memory_.release(p);
             e = memory_.allocate(out, need);
         }
         if (e == Memory::ok()) {
             *held = need;
-            taken_ += static_cast<int64_t>(need);
+        } else {
+            std::lock_guard<std::mutex> lk(mu_);
+            taken_ -= static_cast<int64_t>(need);
         }
         return e;
     }
@@ -91,11 +106,13 @@ public:
         return false;
     }
     Error take_pinned(Pinned** out) {
-        std::lock_guard<std::mutex> lk(mu_);
-        if (!pinned_.empty()) {
-            *out = pinned_.back();
-            pinned_.pop_back();
-            return Memory::ok();
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (!pinned_.empty()) {
+                *out = pinned_.back();
+                pinned_.pop_back();
+                return Memory::ok();
+            }
         }
         return memory_.allocate_pinned(out);
     }
@@ -109,10 +126,12 @@ private:
         taken_ -= static_cast<int64_t>(held);
         over_ -= static_cast<int64_t>(held - need);
     }
-    void drop_one() {
-        memory_.release(free_.back().first);
+    // A free block that no longer counts, to be released without the lock.
+    char* detach() {
+        char* p = free_.back().first;
         free_bytes_ -= static_cast<int64_t>(free_.back().second);
         free_.pop_back();
+        return p;
     }
     Memory memory_;
     std::mutex mu_;

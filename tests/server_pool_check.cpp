@@ -1,7 +1,9 @@
 // Host check of lp_server_pool.h with a memory that records what it is asked for: no GPU code.
-#include <cassert>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
+#include <future>
 #include <string>
 #include <vector>
 
@@ -13,6 +15,7 @@ struct Log {
     std::vector<std::string> calls;
     int next_wait = 0;  // result of the next wait
     size_t limit = ~size_t(0), in_use = 0;
+    std::function<void()> during;  // run inside every allocation and release
 };
 
 struct FakeMemory {
@@ -24,12 +27,14 @@ struct FakeMemory {
     static bool out_of_memory(int e) { return e == 2; }
     int allocate(char** out, size_t bytes) {
         if (log->in_use + bytes > log->limit) return 2;
+        if (log->during) log->during();
         log->in_use += bytes;
         *out = static_cast<char*>(std::malloc(bytes));
         log->calls.push_back("allocate " + std::to_string(bytes));
         return 0;
     }
     void release(char* p) {
+        if (log->during) log->during();
         std::free(p);
         log->calls.push_back("release");
     }
@@ -75,10 +80,61 @@ void failed_setup() {
     CHECK(log.calls.back() == "release");
 }
 
+// While a block is allocated, and while others are released for it, the pool answers other threads.
+void no_memory_call_under_the_lock() {
+    Log log;
+    lpgpu::ServerPool<FakeMemory> pool(1000, FakeMemory{&log});
+    int calls = 0;
+    log.during = [&] {
+        ++calls;
+        auto other = std::async(std::launch::async, [&] {
+            const bool in = pool.admit(1);
+            if (in) pool.retire(1);
+        });
+        if (other.wait_for(std::chrono::seconds(5)) != std::future_status::ready) {
+            std::puts("the pool is locked during a memory call");
+            std::_Exit(1);
+        }
+    };
+    char* p[3];
+    size_t held = 0;
+    for (char*& q : p) CHECK(pool.admit(300) && pool.take(300, &q, &held) == 0);
+    for (char* q : p) pool.give(q, 300, 300), pool.retire(300);
+    CHECK(calls == 3);
+    // 900 free bytes of 1000: two blocks go before 600 new ones come
+    char* big = nullptr;
+    CHECK(pool.admit(600) && pool.take(600, &big, &held) == 0 && held == 600);
+    CHECK(calls == 6);
+    log.during = nullptr;
+    pool.give(big, held, 600);
+    pool.retire(600);
+}
+
+// An allocation that fails counts nothing; free blocks go first when the device is out of memory.
+void out_of_memory() {
+    Log log;
+    lpgpu::ServerPool<FakeMemory> pool(1000, FakeMemory{&log});
+    char *a = nullptr, *b = nullptr;
+    size_t held = 0;
+    CHECK(pool.admit(300) && pool.take(300, &a, &held) == 0);
+    pool.give(a, held, 300);
+    pool.retire(300);
+    log.limit = 0;
+    CHECK(pool.admit(400) && pool.take(400, &b, &held) == 2);
+    CHECK(log.calls.back() == "release");
+    pool.retire(400);
+    log.limit = ~size_t(0);
+    CHECK(pool.admit(1000) && pool.take(1000, &b, &held) == 0);
+    pool.give(b, held, 1000);
+    pool.retire(1000);
+}
+
 }  // namespace
 
 int main() {
     failed_setup();
+    no_memory_call_under_the_lock();
+    out_of_memory();
     std::puts("ok");
     return 0;
 }
