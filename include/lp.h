@@ -394,15 +394,18 @@ int32_t lp_solve_batch_static(lp_handle *const *hs, int32_t count, const lp_opti
  * period (eval_every iterations, evaluation, restart decision) per round of shared
  * block-diagonal launches (replayed as a hipGraph while the set is unchanged). Between
  * rounds it retires the LPs that stopped (their result is copied to the host and their
- * device memory released) and takes in the requests that are ready. A second (set-up)
- * thread admits queued requests in arrival order while a slot is free and the request's
- * device footprint fits the HBM budget, and sets each up on the device (upload, scaling,
- * norm estimate) on its own stream while the rounds run. Every LP starts at its own iteration 0 and keeps its own step sizes, restarts and
+ * device memory given back to the server's pool) and takes in the requests that are ready.
+ * Three set-up threads admit queued requests in arrival order while a slot is free and the
+ * request's device footprint fits the HBM budget, and set each up on the device (upload,
+ * scaling, norm estimate) on streams of their own while the rounds run. The pool keeps memory
+ * of completed requests for the next ones, within the budget; when no request is left it keeps
+ * an eighth of the budget and 256 MB at most, and lp_server_destroy gives that back. Every LP
+ * starts at its own iteration 0 and keeps its own step sizes, restarts and
  * counters, so its result is the same as when it is solved alone.
  * A submitted handle is a template: it must be created with opt->deferred = 1, it is not
  * modified, and it may be submitted any number of times, also while earlier submissions of
  * it are queued or running; every submission is a request of its own, with device memory
- * allocated at admission and released at completion. The result of a request is fetched
+ * taken from the pool at admission and given back at completion. The result of a request is fetched
  * once with lp_server_result. */
 typedef struct lp_server lp_server;
 

@@ -2027,14 +2027,22 @@ void server_loop(lp_server* S) {
     DevMaps run_maps, new_maps;
     bool dirty = true;
     for (;;) {
+        bool idle;
         {
             std::unique_lock<std::mutex> lk(S->mu);
             if (S->stop) break;
-            if (S->ready.empty() && S->running.empty()) {
-                S->cv_idle.notify_all();
-                S->cv_work.wait_for(lk, std::chrono::milliseconds(5));
-                continue;
+            idle = S->ready.empty() && S->running.empty();
+        }
+        if (idle) {
+            std::unique_lock<std::mutex> lk(S->mu);
+            if (S->live == 0 && S->queue.empty()) {
+                lk.unlock();
+                S->pool->trim(S->pool->kept());
+                lk.lock();
             }
+            S->cv_idle.notify_all();
+            if (!S->stop && S->ready.empty()) S->cv_work.wait_for(lk, std::chrono::milliseconds(5));
+            continue;
         }
         server_round(S, run_maps, new_maps, dirty);
     }

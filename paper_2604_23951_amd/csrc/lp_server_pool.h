@@ -4,6 +4,7 @@
 // and waits (HipMemory in the library, a recording one in its host check).
 #pragma once
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <mutex>
@@ -14,8 +15,8 @@ namespace lpgpu {
 
 // Memory is returned only after its last work was waited for, so any stream may take it next.
 // Requests are admitted here: the footprints admitted, what reused blocks exceed theirs by and
-// the free blocks stay within the budget. Everything is given back when the server and its
-// requests are gone.
+// the free blocks stay within the budget. A server without requests trims the free blocks to kept(); everything is given back
+// when the server and its requests are gone.
 template <class Memory>
 class ServerPool {
 public:
@@ -30,6 +31,10 @@ public:
     }
     ServerPool(const ServerPool&) = delete;
     ServerPool& operator=(const ServerPool&) = delete;
+
+    // What a server without requests keeps for the next ones: the footprints of some hundred LPs of
+    // a few thousand rows, little beside the device's memory or the budget.
+    int64_t kept() const { return std::min<int64_t>(budget_ / 8, int64_t(256) << 20); }
 
     bool admit(size_t need) {
         std::lock_guard<std::mutex> lk(mu_);
@@ -82,6 +87,17 @@ public:
             taken_ -= static_cast<int64_t>(need);
         }
         return e;
+    }
+    // Releases free blocks, the largest first, until they hold at most `bytes`.
+    void trim(int64_t bytes) {
+        std::vector<char*> drop;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (free_bytes_ <= bytes) return;
+            std::sort(free_.begin(), free_.end(), [](const auto& a, const auto& b) { return a.second < b.second; });
+            while (free_bytes_ > bytes) drop.push_back(detach());
+        }
+        for (char* p : drop) memory_.release(p);
     }
     // The last work on p was waited for.
     void give(char* p, size_t held, size_t need) {

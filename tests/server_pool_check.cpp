@@ -129,12 +129,34 @@ void out_of_memory() {
     pool.retire(1000);
 }
 
+// A server without requests keeps at most kept(): an eighth of its budget, 256 MB at most.
+void idle() {
+    Log log;
+    lpgpu::ServerPool<FakeMemory> pool(1000, FakeMemory{&log});
+    CHECK(pool.kept() == 125);
+    CHECK(lpgpu::ServerPool<FakeMemory>(int64_t(1) << 40, FakeMemory{&log}).kept() == 256 << 20);
+    char* p[4];
+    const size_t sizes[4] = {90, 400, 30, 200};
+    size_t held = 0;
+    for (int i = 0; i < 4; ++i) CHECK(pool.admit(sizes[i]) && pool.take(sizes[i], &p[i], &held) == 0);
+    for (int i = 0; i < 4; ++i) pool.give(p[i], sizes[i], sizes[i]), pool.retire(sizes[i]);
+    log.calls.clear();
+    pool.trim(pool.kept());
+    CHECK(log.calls.size() == 2);  // 400 and 200; 90 + 30 stay
+    pool.trim(pool.kept());
+    CHECK(log.calls.size() == 2);
+    char* q = nullptr;
+    CHECK(pool.admit(30) && pool.take(30, &q, &held) == 0 && q == p[2]);
+    CHECK(pool.admit(85) && pool.take(85, &q, &held) == 0 && q == p[0] && held == 90);
+}
+
 }  // namespace
 
 int main() {
     failed_setup();
     no_memory_call_under_the_lock();
     out_of_memory();
+    idle();
     std::puts("ok");
     return 0;
 }
