@@ -15,7 +15,9 @@ namespace lpgpu {
 
 // Memory is returned only after its last work was waited for, so any stream may take it next.
 // Requests are admitted here: the footprints admitted, what reused blocks exceed theirs by and
-// the free blocks stay within the budget. A server without requests trims the free blocks to kept(); everything is given back
+// the free blocks stay within the budget. A block is reused for a request that needs at least
+// 8/9 of it: a small request in a large block would keep the next large one from being
+// admitted. A server without requests trims the free blocks to kept(); everything is given back
 // when the server and its requests are gone.
 template <class Memory>
 class ServerPool {
@@ -55,7 +57,7 @@ public:
             std::lock_guard<std::mutex> lk(mu_);
             size_t best = free_.size();
             for (size_t i = 0; i < free_.size(); ++i)
-                if (free_[i].second >= need && (best == free_.size() || free_[i].second < free_[best].second)) best = i;
+                if (free_[i].second >= need && free_[i].second - need <= need / 8 && (best == free_.size() || free_[i].second < free_[best].second)) best = i;
             if (best < free_.size() && admitted_ + over_ + static_cast<int64_t>(free_[best].second - need) <= budget_) {
                 *out = free_[best].first;
                 *held = free_[best].second;

@@ -150,6 +150,20 @@ void idle() {
     CHECK(pool.admit(85) && pool.take(85, &q, &held) == 0 && q == p[0] && held == 90);
 }
 
+// A small request does not take a large block, which would keep a large request out.
+void no_small_request_in_a_large_block() {
+    Log log;
+    lpgpu::ServerPool<FakeMemory> pool(1000, FakeMemory{&log});
+    char *a = nullptr, *b = nullptr;
+    size_t held = 0;
+    CHECK(pool.admit(600) && pool.take(600, &a, &held) == 0);
+    pool.give(a, held, 600);
+    pool.retire(600);
+    CHECK(pool.admit(100) && pool.take(100, &b, &held) == 0 && held == 100);
+    CHECK(pool.admit(900));
+    CHECK(pool.take(900, &a, &held) == 0 && held == 900);
+}
+
 }  // namespace
 
 int main() {
@@ -157,6 +171,7 @@ int main() {
     no_memory_call_under_the_lock();
     out_of_memory();
     idle();
+    no_small_request_in_a_large_block();
     std::puts("ok");
     return 0;
 }
