@@ -365,6 +365,26 @@ struct HipMemory {
 };
 using RequestPool = ServerPool<HipMemory>;
 
+// Device memory of one of a server's set-up threads for what only a set-up needs, the sliced
+// matrices of the norm estimate, of the largest LP that has one. Every set-up ends with a wait for
+// its stream, so the next one may use it.
+struct SetupScratch {
+    // columns and values of at most that many slots; slice offsets and rows; alignment
+    static constexpr size_t kBytes = (4 + 16) * (4 * kSoloPowerNnz + 16384) + 2 * 8 * (kSoloMaxDim + 128) + 4096;
+    char* p = nullptr;
+    char* need(size_t n) {
+        if (!p && hipMalloc(reinterpret_cast<void**>(&p), kBytes) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+        }
+        return n <= kBytes ? p : nullptr;
+    }
+    void release() {
+        if (p) (void)hipFree(p);
+        p = nullptr;
+    }
+};
+
 }  // namespace
 
 struct lp_handle {
@@ -384,6 +404,7 @@ struct lp_handle {
     size_t arena_bytes = 0;
     size_t arena_held = 0;                // bytes of the allocation behind arena
     std::shared_ptr<RequestPool> pool;     // a server's request: where its memory comes from and goes
+    SetupScratch* scratch = nullptr;       // of the server's thread that sets the request up
     DevLP P{};
     int* d_perm = nullptr;
     double* d_x0 = nullptr;
@@ -1209,6 +1230,21 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
     return LP_OK;
 }
 
+// The sliced matrices' place, with FP32 values where the solves read them.
+void add_sell(const Prep& Q, bool fp32, Offsets* O, Arena* L) {
+    if (Q.sA.ptr.empty()) return;
+    auto add = [&](const SellHost& S, size_t* off) {
+        const size_t slots = static_cast<size_t>(S.slots());
+        off[0] = L->add(sizeof(int32_t) * S.ptr.size());
+        off[1] = L->add(sizeof(int32_t) * S.row.size());
+        off[2] = L->add(sizeof(uint32_t) * slots);
+        off[3] = L->add(2 * sizeof(double) * slots);
+        off[4] = fp32 ? L->add(2 * sizeof(float) * slots) : 0;
+    };
+    add(Q.sA, O->sA);
+    add(Q.sAT, O->sAT);
+}
+
 // Device layout of one handle: every array at a 256-byte aligned offset of one allocation.
 size_t arena_layout(const lp_handle* h, Offsets* O) {
     const int32_t m = h->m, n = h->n;
@@ -1282,12 +1318,23 @@ size_t arena_layout(const lp_handle* h, Offsets* O) {
             O->pAT32 = L.add(sizeof(float) * Q.LAT.packed.size());
         }
     }
-    for (int l = 0; l < 2; ++l) {
-        O->fA[l] = L.add(sizeof(TileRec) * Q.fA[l].recs.size());
-        O->fAT[l] = L.add(sizeof(TileRec) * Q.fAT[l].recs.size());
-    }
-    O->rA = L.add(sizeof(TileRec) * Q.rA.size());
-    O->rAT = L.add(sizeof(TileRec) * Q.rAT.size());
+    auto add_recs = [&](Arena& R) {
+        for (int l = 0; l < 2; ++l) {
+            O->fA[l] = R.add(sizeof(TileRec) * Q.fA[l].recs.size());
+            O->fAT[l] = R.add(sizeof(TileRec) * Q.fAT[l].recs.size());
+        }
+        O->rA = R.add(sizeof(TileRec) * Q.rA.size());
+        O->rAT = R.add(sizeof(TileRec) * Q.rAT.size());
+        return R.off;
+    };
+    // A server's request is counted against the budget, so it holds nothing that its set-up alone
+    // needs (the sliced matrices, in the set-up thread's scratch) or that only lp_solve does (the
+    // job); its tile records, which a solve's own launches read until the point is extracted, lie
+    // where that goes, if they fit.
+    const bool request = h->pool != nullptr;
+    Arena in_output;
+    in_output.off = O->ox;
+    if (!request || add_recs(in_output) > O->y) add_recs(L);
     size_t tp_slots = 0;
     auto add_tp = [&](const TwoPhaseHost& H, size_t* off) {
         if (!H.tiles()) return;
@@ -1300,21 +1347,10 @@ size_t arena_layout(const lp_handle* h, Offsets* O) {
     add_tp(Q.tpA, O->tpA);
     add_tp(Q.tpAT, O->tpAT);
     O->tpbuf = L.add((fp32 ? 4 : 8) * tp_slots);
-    auto add_sell = [&](const SellHost& S, size_t* off) {
-        const size_t slots = static_cast<size_t>(S.slots());
-        off[0] = L.add(sizeof(int32_t) * S.ptr.size());
-        off[1] = L.add(sizeof(int32_t) * S.row.size());
-        off[2] = L.add(sizeof(uint32_t) * slots);
-        off[3] = L.add(2 * sizeof(double) * slots);
-        off[4] = fp32 ? L.add(2 * sizeof(float) * slots) : 0;
-    };
-    if (!Q.sA.ptr.empty()) {
-        add_sell(Q.sA, O->sA);
-        add_sell(Q.sAT, O->sAT);
-    }
+    if (!request) add_sell(Q, fp32, O, &L);
     O->part = L.add(sizeof(double) * kNT * kMaxRedBlocks);
     O->sc = L.add(sizeof(Scalars));
-    O->job = L.add(kSoloJobBytes);
+    O->job = request ? 0 : L.add(kSoloJobBytes);
     O->tr = L.add(sizeof(double) * kTraceW * static_cast<size_t>(o.trace_cap > 0 ? o.trace_cap : 1));
     return L.off;
 }
@@ -1561,11 +1597,26 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     };
     bind_tp(Q.tpA, O.tpA, P.A);
     bind_tp(Q.tpAT, O.tpAT, P.AT);
-    const bool sell = !Q.sA.ptr.empty();
+    // An LP with the one-workgroup form runs the norm estimate in one launch, up to the size where
+    // its matrices come mostly from the L2 and one CU's bandwidth costs more than the launches
+    // (lp_create, four launches per step / one launch: 200 x 400 2.6 / 0.83 ms, 11,646 entries 3.6 /
+    // 1.4, 34,511 11.1 / 8.6, 56,839 8.2 / 9.1). It is all that a server's request needs the form for.
+    const bool request = h->pool != nullptr;
+    const SoloPlan power = !(o.step_size > 0.0) && nnz <= kSoloPowerNnz ? solo_stage_plan(h, kSoloLdsMax, false) : SoloPlan{};
+    char* sb = b;  // where the sliced matrices lie
+    if (request) {
+        sb = nullptr;
+        Arena in_scratch;
+        add_sell(Q, false, &O, &in_scratch);
+        if (power.lds > 0 && h->scratch) sb = h->scratch->need(in_scratch.off);
+    }
+    const bool sell = !Q.sA.ptr.empty() && sb, sell32 = fp32 && !request;
     auto bind_sell = [&](const SellHost& H, const size_t* off, Sell& S) {
-        S = Sell{static_cast<int>(H.ptr.size()) - 1, static_cast<int>(H.slots()), I(off[0]), I(off[1]),
-                 reinterpret_cast<const unsigned*>(b + off[2]), D(off[3]), fp32 ? F(off[4]) : nullptr};
+        S = Sell{static_cast<int>(H.ptr.size()) - 1, static_cast<int>(H.slots()), reinterpret_cast<int*>(sb + off[0]),
+                 reinterpret_cast<int*>(sb + off[1]), reinterpret_cast<const unsigned*>(sb + off[2]),
+                 reinterpret_cast<double*>(sb + off[3]), sell32 ? reinterpret_cast<float*>(sb + off[4]) : nullptr};
     };
+    P.sA = P.sAT = Sell{};
     if (sell) {
         bind_sell(Q.sA, O.sA, P.sA);
         bind_sell(Q.sAT, O.sAT, P.sAT);
@@ -1653,10 +1704,10 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     HIP_TRY(h, H2D(b + O.rA, Q.rA.data(), sizeof(TileRec) * Q.rA.size()));
     HIP_TRY(h, H2D(b + O.rAT, Q.rAT.data(), sizeof(TileRec) * Q.rAT.size()));
     if (sell) {
-        HIP_TRY(h, H2D(I(O.sA[0]), Q.sA.ptr.data(), sizeof(int32_t) * Q.sA.ptr.size()));
-        HIP_TRY(h, H2D(I(O.sA[1]), Q.sA.row.data(), sizeof(int32_t) * Q.sA.row.size()));
-        HIP_TRY(h, H2D(I(O.sAT[0]), Q.sAT.ptr.data(), sizeof(int32_t) * Q.sAT.ptr.size()));
-        HIP_TRY(h, H2D(I(O.sAT[1]), Q.sAT.row.data(), sizeof(int32_t) * Q.sAT.row.size()));
+        HIP_TRY(h, H2D(sb + O.sA[0], Q.sA.ptr.data(), sizeof(int32_t) * Q.sA.ptr.size()));
+        HIP_TRY(h, H2D(sb + O.sA[1], Q.sA.row.data(), sizeof(int32_t) * Q.sA.row.size()));
+        HIP_TRY(h, H2D(sb + O.sAT[0], Q.sAT.ptr.data(), sizeof(int32_t) * Q.sAT.ptr.size()));
+        HIP_TRY(h, H2D(sb + O.sAT[1], Q.sAT.row.data(), sizeof(int32_t) * Q.sAT.row.size()));
     }
     if (h->has_x0) HIP_TRY(h, H2D(h->d_x0, x0, sn));
     if (h->has_y0 && m > 0) HIP_TRY(h, H2D(h->d_y0, y0, sm));
@@ -1686,10 +1737,10 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     if (int32_t rc = setup_two_phase(h, Q.tpA, P.A, b, O.tpA, s)) return rc;
     if (int32_t rc = setup_two_phase(h, Q.tpAT, P.AT, b, O.tpAT, s)) return rc;
     if (sell) {
-        launch_fill_sell(P.A.csr, P.sA, reinterpret_cast<unsigned*>(b + O.sA[2]), D(O.sA[3]),
-                         fp32 ? F(O.sA[4]) : nullptr, s);
-        launch_fill_sell(P.AT.csr, P.sAT, reinterpret_cast<unsigned*>(b + O.sAT[2]), D(O.sAT[3]),
-                         fp32 ? F(O.sAT[4]) : nullptr, s);
+        launch_fill_sell(P.A.csr, P.sA, reinterpret_cast<unsigned*>(sb + O.sA[2]), reinterpret_cast<double*>(sb + O.sA[3]),
+                         sell32 ? reinterpret_cast<float*>(sb + O.sA[4]) : nullptr, s);
+        launch_fill_sell(P.AT.csr, P.sAT, reinterpret_cast<unsigned*>(sb + O.sAT[2]), reinterpret_cast<double*>(sb + O.sAT[3]),
+                         sell32 ? reinterpret_cast<float*>(sb + O.sAT[4]) : nullptr, s);
     }
     launch_prepare(P, D(O.c), D(O.bl), D(O.bu), D(O.xl), D(O.xu), D(O.R), D(O.C), D(O.Ri), D(O.Ci), h->d_x0,
                    h->d_y0, s);
@@ -1706,13 +1757,10 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     // chunks of pow_iters steps until a chunk's last step raises the estimate by at most
     // 1e-8 of it (it approaches ||A~||_2 from below and eta = 0.998 / estimate must keep
     // eta ||A~||_2 < 1), at most 25 chunks
-    // An LP with the one-workgroup form whose rows the product layout sums in order runs the same
-    // iteration in one launch, up to the size where its matrices come mostly from the L2 and
-    // one CU's bandwidth costs more than the launches (lp_create, four launches per step / one
-    // launch: 200 x 400 2.6 / 0.83 ms, 11,646 entries 3.6 / 1.4, 34,511 11.1 / 8.6, 56,839 8.2 / 9.1).
-    const SoloPlan power = sell && nnz <= kSoloPowerNnz ? solo_stage_plan(h, kSoloLdsMax, false) : SoloPlan{};
+    // (in one launch where the sliced matrices are there and the product layout sums every row in
+    // order, as it does)
     const bool ordered = P.A.layout == 1 || P.A.nlong + P.AT.nlong == 0;
-    if (!(o.step_size > 0.0) && ordered && power.lds > 0 && power.lds <= kSoloLdsMax) {
+    if (sell && ordered && power.lds > 0) {
         launch_solo_power(P, SoloStage{power.a_slices, power.a_slots, power.at_slices, power.at_slots}, power.lds, o.seed,
                           o.pow_iters, 25, s);
     } else if (!(o.step_size > 0.0)) {
@@ -1730,7 +1778,8 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     if (int32_t rc = check_launch(h, "setup kernels")) return rc;
     HIP_TRY(h, hipMemcpyAsync(h->h_sc, P.sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
     HIP_TRY(h, hipStreamSynchronize(s));
-    if (!h->pool) (void)static_batch_streams(h->device, true, nullptr);
+    if (request) P.sA = P.sAT = Sell{};  // the scratch goes to the next set-up
+    else (void)static_batch_streams(h->device, true, nullptr);
     h->on_device = true;
     return LP_OK;
 }
@@ -1764,7 +1813,6 @@ lp_handle* clone_for_request(const lp_handle* t) {
     h->units_at = t->units_at;
     h->panels_a = t->panels_a;
     h->panels_at = t->panels_at;
-    h->arena_bytes = t->arena_bytes;
     h->prep = t->prep;
     h->raw = t->raw;
     h->recs_a = t->recs_a;
@@ -1804,6 +1852,7 @@ struct lp_server {
     static constexpr int kSetups = 3;
     std::thread setup_worker[kSetups];
     hipStream_t setup_stream[kSetups] = {nullptr, nullptr, nullptr};
+    SetupScratch setup_scratch[kSetups];
     std::shared_ptr<RequestPool> pool;
     std::mutex mu;
     std::condition_variable cv_work, cv_idle, cv_setup;
@@ -2014,7 +2063,9 @@ void setup_loop(lp_server* S, int which) {
         }
         t.h->stream = S->setup_stream[which];
         t.h->own_stream = false;
+        t.h->scratch = &S->setup_scratch[which];
         t.setup_rc = materialize(t.h);
+        t.h->scratch = nullptr;
         if (t.setup_rc != LP_OK) abandon_setup(t.h);  // while its stream is at hand
         std::unique_lock<std::mutex> lk(S->mu);
         S->ready.push_back(t);
@@ -2097,14 +2148,18 @@ int32_t lp_server_submit(lp_server* S, lp_handle* h, uint64_t* ticket) {
     if (!S || !h || !ticket) return fail(nullptr, LP_ERR_INVALID_ARG, "bad submit arguments");
     if (!h->deferred || !h->raw || !h->prep) return fail(h, LP_ERR_INVALID_ARG, "a served handle must be deferred");
     if (h->device != S->device) return fail(h, LP_ERR_INVALID_ARG, "handle and server on different devices");
-    if (static_cast<int64_t>(h->arena_bytes) > S->budget)
-        return fail(h, LP_ERR_INVALID_ARG, "footprint exceeds the server's HBM budget");
     lp_handle* r = nullptr;
     try {
         r = clone_for_request(h);
-        r->pool = S->pool;
     } catch (...) {
         return fail(h, LP_ERR_OUT_OF_MEMORY, "host allocation failed");
+    }
+    r->pool = S->pool;
+    Offsets O;
+    r->arena_bytes = arena_layout(r, &O);  // a request holds less than a handle of its own
+    if (static_cast<int64_t>(r->arena_bytes) > S->budget) {
+        delete r;
+        return fail(h, LP_ERR_INVALID_ARG, "footprint exceeds the server's HBM budget");
     }
     std::unique_lock<std::mutex> lk(S->mu);
     Ticket t{S->next_ticket++, r, S->now(), 0.0, 0.0, 0, LP_OK};
@@ -2226,6 +2281,7 @@ void lp_server_destroy(lp_server* S) {
     for (auto& kv : S->finished) lp_destroy(kv.second.h);
     (void)hipStreamDestroy(S->stream);
     for (hipStream_t st : S->setup_stream) (void)hipStreamDestroy(st);
+    for (SetupScratch& c : S->setup_scratch) c.release();
     delete S;
 }
 
