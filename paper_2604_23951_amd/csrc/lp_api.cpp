@@ -1400,12 +1400,18 @@ int32_t tune_layout(lp_handle* h, hipStream_t s, LayoutTrial* out) {
 
 // Fills the two-phase layout of M on the device from its (scaled) CSR: entries per cell, the
 // cells' places (on the host), then the entries.
-int32_t setup_two_phase(lp_handle* h, const TwoPhaseHost& H, const Mat& M, char* base, const size_t* off, hipStream_t s) {
+int32_t setup_two_phase(lp_handle* h, const TwoPhaseHost& H, Mat& M, char* base, const size_t* off, hipStream_t s) {
     if (!H.tiles()) return LP_OK;
     const TwoPhase& T = M.tp;
     const size_t tiles = static_cast<size_t>(H.tiles()), blocks = static_cast<size_t>(H.blocks), cells = H.cells();
     char* tmp = nullptr;  // the cells' counts, then their first places; and their places inside the tiles
-    HIP_TRY(h, hipMalloc(reinterpret_cast<void**>(&tmp), 8 * cells));
+    const hipError_t device_memory = hipMalloc(reinterpret_cast<void**>(&tmp), 8 * cells);
+    if (device_memory == hipErrorOutOfMemory) {  // no room to build it: the products keep the panels
+        (void)hipGetLastError();
+        M.tp.tiles = 0;
+        return LP_OK;
+    }
+    HIP_TRY(h, device_memory);
     struct Free {
         char* p;
         ~Free() { (void)hipFree(p); }
@@ -1486,7 +1492,16 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     if (h->pool) {
         HIP_TRY(h, h->pool->take(h->arena_bytes, &h->arena, &h->arena_held));
     } else {
-        HIP_TRY(h, hipMalloc(reinterpret_cast<void**>(&h->arena), h->arena_bytes));
+        hipError_t device_memory = hipMalloc(reinterpret_cast<void**>(&h->arena), h->arena_bytes);
+        if (device_memory == hipErrorOutOfMemory && (Q.tpA.tiles() || Q.tpAT.tiles())) {
+            // a nearly full device: the products keep the panels
+            (void)hipGetLastError();
+            h->prep->tpA = h->prep->tpAT = TwoPhaseHost{};
+            O = Offsets{};
+            h->arena_bytes = arena_layout(h, &O);
+            device_memory = hipMalloc(reinterpret_cast<void**>(&h->arena), h->arena_bytes);
+        }
+        HIP_TRY(h, device_memory);
         h->arena_held = h->arena_bytes;
     }
     if (h->pool && !h->h_sc) {
