@@ -1509,8 +1509,16 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
         std::memset(h->h_sc, 0, sizeof(Scalars));
     } else if (!h->h_sc) {
         const size_t res = sizeof(double) * (2 * static_cast<size_t>(n) + static_cast<size_t>(m));
-        const bool pinned = res <= kPinnedResult;
-        HIP_TRY(h, hipHostMalloc(reinterpret_cast<void**>(&h->h_sc), kPinnedScalars + (pinned ? res : 0), hipHostMallocDefault));
+        bool pinned = res <= kPinnedResult;
+        void* host = nullptr;
+        hipError_t host_memory = hipHostMalloc(&host, kPinnedScalars + (pinned ? res : 0), hipHostMallocDefault);
+        if (host_memory != hipSuccess && pinned) {  // without room for the point: it is copied from the device
+            (void)hipGetLastError();
+            pinned = false;
+            host_memory = hipHostMalloc(&host, kPinnedScalars, hipHostMallocDefault);
+        }
+        HIP_TRY(h, host_memory);
+        h->h_sc = static_cast<Scalars*>(host);
         std::memset(h->h_sc, 0, sizeof(Scalars));
         h->h_res = pinned ? reinterpret_cast<double*>(reinterpret_cast<char*>(h->h_sc) + kPinnedScalars) : nullptr;
     }

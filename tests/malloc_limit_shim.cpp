@@ -1,4 +1,4 @@
-// hipMalloc that reports out of memory above a size or at one call, for a process that loads this library before
+// hipMalloc that reports out of memory above a size or at one call, and hipHostMalloc above a size, for a process that loads this library before
 // the solver's (its symbols are found first). No GPU code.
 #include <dlfcn.h>
 
@@ -18,4 +18,17 @@ extern "C" int hipMalloc(void** p, size_t bytes) {
         return 2;  // hipErrorOutOfMemory
     }
     return real(p, bytes);
+}
+
+static size_t host_limit = ~size_t(0);
+
+extern "C" void shim_host_limit(size_t bytes) { host_limit = bytes; }
+
+extern "C" int hipHostMalloc(void** p, size_t bytes, unsigned flags) {
+    static auto real = reinterpret_cast<int (*)(void**, size_t, unsigned)>(dlsym(dlopen("libamdhip64.so.7", RTLD_LAZY), "hipHostMalloc"));
+    if (bytes > host_limit) {
+        ++refused;
+        return 2;
+    }
+    return real(p, bytes, flags);
 }
