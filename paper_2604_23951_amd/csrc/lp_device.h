@@ -360,7 +360,11 @@ constexpr bool solo_sorted(int m, int n) { return n <= 2048 && m <= 1024; }
 constexpr int solo_threads(int variant) { return variant == SOLO_256 ? 256 : variant == SOLO_512 ? 512 : 1024; }
 constexpr int kSoloMaxDim = 14000;          // rows and columns: the gathered FP64 vector stays within LDS
 constexpr long long kSoloMaxNnz = 65536;
-constexpr int kSoloMaxRow = 128;            // entries of a row, summed by one thread
+// Entries of a row, summed by one thread while the others wait. us per iteration of a batch's LP
+// with one long row, one thread / row tiles: 200 x 400 (tiles in LDS) 136 entries 4.1 / 6.8, 168
+// 5.0 / 7.2, 264 9.1 / 8.0, 400 13.4 / 9.3; 800 x 1600 (tiles in global memory) 136 entries 5.3 / 20.9,
+// 408 14.3 / 23.8, 1600 50 / 37. The limit lies on the safe side of the first crossover.
+constexpr int kSoloMaxRow = 128;
 constexpr int kSoloLdsMax = 152 * 1024;     // dynamic LDS of a workgroup at most
 // Set-up of a two-phase layout: entries per cell, then the entries placed (cell_base: a cell's
 // first place in block order, [block * tiles + tile]; cell_k: in its tile, [tile * blocks + block]).
