@@ -2011,7 +2011,8 @@ __device__ inline void materialize_at(const DevLP& P, int g) {
 
 __global__ void materialize_kernel(DevLP P) { materialize_at(P, blockIdx.x * blockDim.x + threadIdx.x); }
 
-// Refinement (FP32 form): after the initial evaluation (mode 1) or a restart decided by
+// Refinement (FP32 form): after the initial evaluation (mode 1; also one that stops the solve, whose
+// iterates are then the initial point and corrections of 0) or a restart decided by
 // the evaluation (mode 0: last_restart 1 current, 2 average), the chosen point becomes the
 // FP64 master and the anchor, and the correction data are recomputed in FP64 from the
 // products A~x, A~^T y that the evaluation just formed.
@@ -2047,7 +2048,6 @@ __device__ inline void rebase_at(const DevLP& P, int lr, int g) {
 __global__ void rebase_kernel(DevLP P, int mode) {
     const int lr = mode == 1 ? 1 : P.sc->last_restart;
     if (lr == 0) return;
-    if (mode == 1 && P.sc->status != kRunning) return;
     rebase_at(P, lr, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
@@ -2234,7 +2234,7 @@ __device__ void wg_solve(const DevLP& P, const BatchJob& J, Scalars* ssc, double
         for (int g = tid; g < mx; g += kBlock) save_prev_at(P, 0, true, g);
         __syncthreads();
     }
-    if (P.fp32 && ssc->status == kRunning) {
+    if (P.fp32) {
         for (int g = tid; g < mx; g += kBlock) rebase_at(P, 1, g);
         __syncthreads();
     }
@@ -2513,8 +2513,7 @@ __global__ __launch_bounds__(kBlock) void multi_elem_kernel(const BatchJob* jobs
     if (OP == EO_INIT) {
         init_state_at(P, g, J.x0, J.y0);
     } else if (OP == EO_REBASE_INIT) {
-        if (sc->status != kRunning) return;
-        save_prev_at(P, 0, true, g);
+        if (sc->status == kRunning) save_prev_at(P, 0, true, g);
         if (P.fp32) rebase_at(P, 1, g);
     } else if (OP == EO_MATERIALIZE) {
         if (P.fp32 && sc->status == kRunning) materialize_at(P, g);

@@ -522,7 +522,7 @@ __device__ __noinline__ void solo_evaluate(const BatchJob& J, int mode) {
         for (int g = tid; g < mx; g += NT) save_prev_at(P, mode == 1 ? 0 : lr, mode == 1, g);
         __syncthreads();
     }
-    if ((mode == 1 && running && FP32) || (mode == 0 && lr)) {
+    if ((mode == 1 && FP32) || (mode == 0 && lr)) {
         for (int g = tid; g < mx; g += NT) {
             if (FP32) rebase_at(P, lr, g);
             else apply_restart_at(P, lr, g);
