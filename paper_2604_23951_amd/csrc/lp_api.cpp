@@ -83,23 +83,28 @@ std::vector<TileRec> tile_recs(const std::vector<int32_t>& tiles, const int32_t*
     return out;
 }
 
-// Row tiles of one LP's own launches (the shape the tuned table gives is for many LPs per
-// launch): a launch of few tiles is bound by one tile's chain of loads, row sums and
-// stores, which grows with the tile, and a launch of many by their number, so the largest
-// shape that still gives nearly every CU a tile (us per iteration with tiles of 1024 / 2048 /
-// 4096, FP64: 32k entries 7.9 / 9.6 / 13.0, 231k 9.2 / 11.1 / 15.2, 993k 23.3 / 20.7 / 19.3). tree_len: rows longer than this are the ones
-// the layout reduces by a workgroup; all others must fit a tile to be summed in order.
+// Row tiles of one LP's own launches. The tuned table's shape was measured on many LPs per launch. A
+// launch of few tiles is bound by one tile's chain of loads, row sums and stores, which grows with
+// the tile, so the shape is the largest, up to the tuned one, that still gives nearly every CU a
+// tile (us per iteration with tiles of 1024 / 2048 / 4096, FP64: 32k entries 7.9 / 9.6 / 13.0, 231k
+// 10.1 / 12.0 / 16.3). A larger tile than the tuned one pays only where that holds fewer than 16
+// rows, whose serial sums it would wait for (4999 rows of 200 entries 19.6 / 17.9 / 17.3, of 490
+// 41.8 / 37.2 / 37.5); with short rows it does not, least of all where its tiles are a few more
+// than the CUs (1.2M entries in rows of 12, tuned 1024: 34.2 / 43.8 / 65.5 and 26.9 / 30.0 / 34.1;
+// 2.3M 41.8 / 45.5 / 51.1, in FP32, tuned 2048, 42.8 / 40.1 / 44.7). tree_len: rows longer than this
+// are the ones the layout reduces by a workgroup; all others must fit a tile to be summed in order.
 struct FlatTiles {
     std::vector<TileRec> recs;
     int shape = 0, tree_len = 0;
 };
 
-FlatTiles flat_tiles(int32_t rows, const int32_t* rp, int32_t tree_len, int cus) {
+FlatTiles flat_tiles(int32_t rows, const int32_t* rp, int32_t tree_len, int tuned, int cus) {
     FlatTiles F;
     int32_t longest = 0;
     for (int32_t r = 0; r < rows; ++r)
         if (rp[r + 1] - rp[r] <= tree_len) longest = std::max(longest, rp[r + 1] - rp[r]);
-    F.shape = kTileShapes - 1;
+    F.shape = 16LL * rp[rows] > static_cast<int64_t>(tile_nnz_of(tuned)) * rows ? kTileShapes - 1 : tuned;
+    while (F.shape < kTileShapes - 1 && longest > tile_nnz_of(F.shape)) ++F.shape;
     while (F.shape > 0 && longest <= tile_nnz_of(F.shape - 1) &&
            static_cast<int64_t>(rp[rows]) < static_cast<int64_t>(cus) * tile_nnz_of(F.shape) * 7 / 8)
         --F.shape;
@@ -126,8 +131,8 @@ struct TwoPhaseHost {
 // Where two launches per product with streams and runs beat one with a gather per entry: a
 // gathered vector that does not fit an XCD's L2, or one of 1.5 MB and more (the gathers miss
 // L1 and queue for the L2) with enough entries to pay for the second launch. us per iteration,
-// Halpern form, row tiles or panels / two phases: 2.4M entries, x of 3.2 MB, FP64 63 / 70, FP32
-// 50 / 51; 4.8M 110 / 86, 82 / 61; 7.2M 150 / 138, 121 / 80; 1.2e7 232 / 207, 190 / 137; 1.7M
+// Halpern form, row tiles or panels / two phases: 2.4M entries, x of 3.2 MB, FP64 53 / 70, FP32
+// 47 / 51; 4.8M 110 / 86, 82 / 61; 7.2M 150 / 138, 121 / 80; 1.2e7 232 / 207, 190 / 137; 1.7M
 // with vectors below 1.8 MB 38 / 57, 29 / 41.
 // Not beyond 2^29 entries: the 32 (FP32 storage: 20) bytes per entry that the two matrices'
 // layouts and the products take more could be what no longer fits.
@@ -1209,8 +1214,10 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
         h->panels_at = Q.LAT.panels;
         const int64_t sv = o.precision == LP_PREC_FP32_REFINED ? 4 : 8;
         const bool any_width = slice == (int64_t(1) << 19);
-        if ((Q.LA.panels == 1 || any_width) && sv * n <= kFlatBytes) Q.fA[0] = flat_tiles(m, rp, long_len, cus);
-        if ((Q.LAT.panels == 1 || any_width) && sv * m <= kFlatBytes) Q.fAT[0] = flat_tiles(n, Q.rpT.data(), long_len, cus);
+        const int tuned = tuned_tile_shape(sv == 4, m, n, nnz);
+        if ((Q.LA.panels == 1 || any_width) && sv * n <= kFlatBytes) Q.fA[0] = flat_tiles(m, rp, long_len, tuned, cus);
+        if ((Q.LAT.panels == 1 || any_width) && sv * m <= kFlatBytes)
+            Q.fAT[0] = flat_tiles(n, Q.rpT.data(), long_len, tuned, cus);
         // not for deferred handles: servers and batches iterate with row tiles, and the layout
         // would count against a server's budget
         const bool two = any_width && !h->deferred;
@@ -1221,8 +1228,8 @@ int32_t host_prep(lp_handle* h, const int32_t* rp, const int32_t* ci) {
             Q.tpAT = {};
     }
     if (o.spmv_layout != LP_LAYOUT_PANELS && o.tile_nnz == 0) {  // (a shape that was asked for is kept)
-        Q.fA[1] = flat_tiles(m, rp, tn, cus);
-        Q.fAT[1] = flat_tiles(n, Q.rpT.data(), tn, cus);
+        Q.fA[1] = flat_tiles(m, rp, tn, Q.shape, cus);
+        Q.fAT[1] = flat_tiles(n, Q.rpT.data(), tn, Q.shape, cus);
     }
     const int mx = m > n ? m : n;
     Q.nred = (mx + 1023) / 1024;

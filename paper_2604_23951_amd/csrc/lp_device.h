@@ -118,8 +118,8 @@ struct Panels {
 // unless a panel width was asked for. The gathers hit the L2 in any order then, and the panel
 // units (a few hundred entries per wave and step, a barrier after each, ~20 us however small
 // the matrix) only cost latency. us per iteration, Halpern form, panels / row tiles: 32k
-// entries 11.8 / 7.8, dense rows with 993k (FP64) 57 / 16, power-law columns with 1.2M 48 / 38
-// (FP32 39 / 29), 2.4M 72 / 57 (62 / 50); beyond, x at 6.4 MB: 111 / 114, y at 6.4 MB: 190 / 219.
+// entries 11.8 / 7.8, dense rows with 993k (FP64) 57 / 16, power-law columns with 1.2M 51 / 32
+// (FP32 44 / 27), 2.4M 77 / 53 (66 / 47); beyond, x at 6.4 MB: 111 / 114, y at 6.4 MB: 190 / 219.
 // The FP64 products of the FP32 storage form gather twice the bytes and keep the panels where
 // those exceed it (y at 8 MB, 1.2e7 entries: panels 107, row tiles 159).
 constexpr long long kFlatBytes = 4LL << 20;
