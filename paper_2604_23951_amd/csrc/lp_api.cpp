@@ -92,7 +92,8 @@ std::vector<TileRec> tile_recs(const std::vector<int32_t>& tiles, const int32_t*
 // 41.8 / 37.2 / 37.5); with short rows it does not, least of all where its tiles are a few more
 // than the CUs (1.2M entries in rows of 12, tuned 1024: 34.2 / 43.8 / 65.5 and 26.9 / 30.0 / 34.1;
 // 2.3M 41.8 / 45.5 / 51.1, in FP32, tuned 2048, 42.8 / 40.1 / 44.7). tree_len: rows longer than this
-// are the ones the layout reduces by a workgroup; all others must fit a tile to be summed in order.
+// are the ones the layout reduces by a workgroup, each in a tile of its own, and do not count for
+// the shape; all others must fit a tile to be summed in order.
 struct FlatTiles {
     std::vector<TileRec> recs;
     int shape = 0, tree_len = 0;
@@ -100,13 +101,19 @@ struct FlatTiles {
 
 FlatTiles flat_tiles(int32_t rows, const int32_t* rp, int32_t tree_len, int tuned, int cus) {
     FlatTiles F;
-    int32_t longest = 0;
-    for (int32_t r = 0; r < rows; ++r)
-        if (rp[r + 1] - rp[r] <= tree_len) longest = std::max(longest, rp[r + 1] - rp[r]);
-    F.shape = 16LL * rp[rows] > static_cast<int64_t>(tile_nnz_of(tuned)) * rows ? kTileShapes - 1 : tuned;
+    int32_t longest = 0, short_rows = 0;
+    int64_t entries = 0;  // of the rows that are summed in order
+    for (int32_t r = 0; r < rows; ++r) {
+        const int32_t len = rp[r + 1] - rp[r];
+        if (len > tree_len) continue;
+        longest = std::max(longest, len);
+        entries += len;
+        ++short_rows;
+    }
+    F.shape = 16 * entries > static_cast<int64_t>(tile_nnz_of(tuned)) * short_rows ? kTileShapes - 1 : tuned;
     while (F.shape < kTileShapes - 1 && longest > tile_nnz_of(F.shape)) ++F.shape;
     while (F.shape > 0 && longest <= tile_nnz_of(F.shape - 1) &&
-           static_cast<int64_t>(rp[rows]) < static_cast<int64_t>(cus) * tile_nnz_of(F.shape) * 7 / 8)
+           entries < static_cast<int64_t>(cus) * tile_nnz_of(F.shape) * 7 / 8)
         --F.shape;
     F.tree_len = std::min(tree_len, tile_nnz_of(F.shape));
     if (longest > F.tree_len) return F;

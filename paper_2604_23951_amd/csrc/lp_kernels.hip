@@ -292,7 +292,10 @@ __device__ void tile_body(const Csr& M, const TileRec& tile, const T* __restrict
             }
         }
     } else {
-        row_tree_body<TN, T>(M, r0, xin, epi, red);
+        // (a row's loads past its end are repeats of its last entries: few per thread for short rows)
+        constexpr int kShort = tile_nnz_of(0);
+        if (TN > kShort && p1 - p0 <= kShort) row_tree_body<kShort, T>(M, r0, xin, epi, red);
+        else row_tree_body<TN, T>(M, r0, xin, epi, red);
     }
 }
 

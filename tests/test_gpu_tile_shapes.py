@@ -46,3 +46,15 @@ def test_few_tiles_and_few_rows_in_a_tile(precision):
     _, want = _run(long_rows, spmv_layout=1, precision=precision, tile_nnz=lay["tile_nnz"])
     for a, b in zip(got, want):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("row", [400, 1300])
+def test_rows_that_a_workgroup_reduces(row, precision):
+    """All rows longer than long_row_len, in the panel layout: as in the panels themselves."""
+    lp = _lp(900, 6000, row)
+    lay, got = _run(lp, precision=precision)
+    assert lay["long_rows_a"] == 900 and lay["flat_a"] == 900
+    _, want = _run(lp, precision=precision, panel_slice_bytes=8 * 3001)
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a, b)
