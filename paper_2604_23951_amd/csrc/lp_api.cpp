@@ -817,8 +817,8 @@ struct DevMaps {
         M.map_elem = reinterpret_cast<const int2*>(buf + oel);
         M.n_elem = static_cast<int>(melem.size());
         M.active = reinterpret_cast<int*>(buf + ost);
-        long long bytes[2] = {0, 0};  // entries of A and A^T: value and column
-        for (const lp_handle* h : hs) bytes[h->P.fp32 ? 1 : 0] += 2LL * h->nnz * (h->P.fp32 ? 8 : 12);
+        long long bytes[2] = {0, 0};
+        for (const lp_handle* h : hs) bytes[h->P.fp32 ? 1 : 0] += iteration_bytes(h->m, h->n, h->nnz, h->P.fp32 ? 4 : 8);
         M.keep = keep_multi(bytes[0], bytes[1]) ? 1 : 0;
         auto H2D = [&](size_t off, const void* src, size_t bytes) {
             return bytes ? hipMemcpyAsync(buf + off, src, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
@@ -1553,7 +1553,7 @@ int32_t device_setup(lp_handle* h, const int32_t* rp, const int32_t* ci, const d
     P.nnz = nnz;
     P.nred = Q.nred;
     P.A.csr = Csr{m, ntA, static_cast<int>(nnz), Q.shape, I(O.arp), I(O.aci), D(O.av), I(O.at), nullptr, nullptr, n,
-                  tile_nnz_of(Q.shape), reinterpret_cast<const TileRec*>(b + O.rA), nnz * 24 <= kKeepTiles ? 1 : 0};
+                  tile_nnz_of(Q.shape), reinterpret_cast<const TileRec*>(b + O.rA), iteration_bytes(m, n, nnz, 8) <= kKeepTiles ? 1 : 0};
     P.AT.csr = Csr{n, ntAT, static_cast<int>(nnz), Q.shape, I(O.trp), I(O.tci), D(O.tv), I(O.tt), nullptr, nullptr, m,
                    tile_nnz_of(Q.shape), reinterpret_cast<const TileRec*>(b + O.rAT), P.A.csr.keep};
     P.A.layout = P.AT.layout = panels ? 0 : 1;

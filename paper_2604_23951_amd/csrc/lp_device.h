@@ -53,21 +53,25 @@ struct Scalars {
     int ray_src;       // candidate ray of a certificate: 1 displacement since the previous evaluation, 2 anchored average
 };
 
-// What an iteration streams of its matrices up to which plain loads, which may stay in the 256 MB
+// What an iteration streams up to which plain loads of the matrices, which may stay in the 256 MB
 // Infinity Cache from one iteration to the next, beat non-temporal ones. us per iteration, plain /
 // non-temporal:
 // - two phases (entries of both matrices and the products): 144 MB 80 / 91, 154 MB 86 / 99, 230 MB
 //   144 / 138, 240 MB 140 / 137, 384 MB 209 / 207;
-// - FP64 row tiles of one LP (entries of both): power-law columns 69 MB 67 / 73, 115 MB 117 / 121,
-//   137 MB 144 / 147, 165 MB 184 / 180, 184 MB 213 / 207, 275 MB 361 / 354; uniform columns 92 MB
-//   76 / 83, 137 MB 126 / 128, 184 MB 195 / 191;
-// - block-diagonal launches (all their LPs), FP64: 137 MB 86 / 94, 179 MB 117 / 119, 211 MB 139 /
-//   136, 579 MB 367 / 362; FP32: 140 MB 86 / 93, 211 MB 129 / 133, 281 MB 172 / 173, 421 MB 256 /
-//   252.
-constexpr long long kKeepTwoPhase = 192LL << 20, kKeepTiles = 144LL << 20;
+// - FP64 row tiles of one LP (iteration_bytes): uniform columns 215 MB 71 / 79, 307 MB 123 / 125, 414 MB
+//   198 / 189; power-law columns 335 MB 139 / 140, 402 MB 181 / 176, 670 MB 360 / 351; rows of 40
+//   entries 235 MB 96 / 119; dense 237 MB 110 / 135, 358 MB 191 / 197;
+// - block-diagonal launches (the same, of all their LPs), FP64: 308 MB 86 / 94, 402 MB 117 / 119, 473 MB
+//   139 / 136, dense rows 263 MB 112 / 126, 478 MB 209 / 202; FP32: 407 MB 129 / 133, 542 MB 172 / 173,
+//   813 MB 256 / 252, dense rows 427 MB 152 / 156.
+constexpr long long kKeepTwoPhase = 192LL << 20, kKeepTiles = 370LL << 20;
+// Entries of both matrices, and the vectors twice: most are read and written. value: bytes of one.
+constexpr long long iteration_bytes(long long m, long long n, long long nnz, int value) {
+    return 2 * nnz * (value + 4) + 2 * value * (9 * n + 8 * m);
+}
 // Of the block-diagonal launches' LPs: `bytes64` in the FP64 form, `bytes32` in the FP32 form.
 constexpr bool keep_multi(long long bytes64, long long bytes32) {
-    return 5 * bytes64 + 3 * bytes32 <= 5 * (192LL << 20);
+    return 4 * bytes64 + 3 * bytes32 <= 4 * (430LL << 20);
 }
 
 // A row tile: rows [r0, r1), entries [p0, p1).
