@@ -246,7 +246,7 @@ __device__ __forceinline__ T stream_load(const T* p) {
 // KEEP: plain loads of the matrix (see kKeepTiles and keep_multi). A single FP32 launch keeps the
 // non-temporal loads: its smaller matrix then competes with the gathered vectors for the L2
 // (1.7M entries, us per iteration non-temporal / plain: 29.3 / 30.2).
-template <int TN, bool KEEP, bool AHEAD, class T, class Epi>
+template <int TN, bool KEEP, bool AHEAD, bool SHORT = false, class T, class Epi>
 __device__ void tile_body(const Csr& M, const TileRec& tile, const T* __restrict__ xin, const Epi& epi, T* prod, double* red) {
     constexpr int kPerThread = TN / kBlock;
     constexpr int kRowsPerThread = TN / 4 / kBlock;
@@ -292,9 +292,11 @@ __device__ void tile_body(const Csr& M, const TileRec& tile, const T* __restrict
             }
         }
     } else {
-        // (a row's loads past its end are repeats of its last entries: few per thread for short rows)
+        // A row's loads past its end are repeats: few per thread for short rows. SHORT: in a solve's own
+        // launches, where a panel layout's long rows come this way; block-diagonal launches see few of
+        // them and the code costs ~1% (160 FP32 LPs 335 / 338 us per iteration without / with it).
         constexpr int kShort = tile_nnz_of(0);
-        if (TN > kShort && p1 - p0 <= kShort) row_tree_body<kShort, T>(M, r0, xin, epi, red);
+        if (SHORT && TN > kShort && p1 - p0 <= kShort) row_tree_body<kShort, T>(M, r0, xin, epi, red);
         else row_tree_body<TN, T>(M, r0, xin, epi, red);
     }
 }
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(kBlock) void spmv_tiles_kernel(Csr M, const T* __re
     __shared__ T prod[TN];
     __shared__ double red[kBlock / 64];
     if (!epi.begin()) return;
-    tile_body<TN, KEEP, true>(M, M.recs[blockIdx.x], xin, epi, prod, red);
+    tile_body<TN, KEEP, true, true>(M, M.recs[blockIdx.x], xin, epi, prod, red);
 }
 
 // Panel-packed SpMV over wave units of rows. The entries of a unit are walked in packed order,
