@@ -189,7 +189,10 @@ typedef struct lp_options {
                               gives this LP's precision, mean row length and size (the table is
                               written by paper_2604_23951_amd/tune_tiles.py on the device). A row
                               longer than the tile is reduced by a workgroup of its own, so the
-                              shape decides which rows are summed by a tree */
+                              shape decides which rows are summed by a tree. With 0, lp_solve's own
+                              launches may cut the rows into smaller or larger tiles (a launch per
+                              LP fills the device otherwise than one for many); the rows summed by
+                              a tree stay those of this shape */
     int32_t pad5;
 } lp_options;
 
@@ -229,8 +232,9 @@ typedef struct lp_info {
                               evaluation, 2 the averaged point (the PDHG output in the Halpern
                               form) minus the restart anchor; 0 otherwise */
     int32_t solve_path;    /* how lp_solve ran: 0 one kernel per phase (the spmv_layout products,
-                              hipGraph periods), 1 one workgroup from LDS (an LP whose iteration
-                              arrays fit small_lp_lds, see there); batched and served LPs: 0 */
+                              hipGraph periods), 1 one workgroup from LDS (an LP that small_lp_lds
+                              admits, see there); batched and served LPs: 0 (lp_get_layout tells
+                              what ran those) */
 } lp_info;
 
 /* Fill *opt with the defaults listed above. */
