@@ -817,9 +817,9 @@ struct DevMaps {
         M.map_elem = reinterpret_cast<const int2*>(buf + oel);
         M.n_elem = static_cast<int>(melem.size());
         M.active = reinterpret_cast<int*>(buf + ost);
-        long long bytes[2] = {0, 0};
-        for (const lp_handle* h : hs) bytes[h->P.fp32 ? 1 : 0] += iteration_bytes(h->m, h->n, h->nnz, h->P.fp32 ? 4 : 8);
-        M.keep = keep_multi(bytes[0], bytes[1]) ? 1 : 0;
+        long long bytes = 0;  // of the LPs in the FP64 form
+        for (const lp_handle* h : hs) bytes += h->P.fp32 ? 0 : iteration_bytes(h->m, h->n, h->nnz, 8);
+        M.keep = bytes <= kKeepMulti ? 1 : 0;
         auto H2D = [&](size_t off, const void* src, size_t bytes) {
             return bytes ? hipMemcpyAsync(buf + off, src, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
         };

@@ -61,17 +61,14 @@ struct Scalars {
 // - FP64 row tiles of one LP (iteration_bytes): uniform columns 215 MB 71 / 79, 307 MB 123 / 125, 414 MB
 //   198 / 189; power-law columns 335 MB 139 / 140, 402 MB 181 / 176, 670 MB 360 / 351; rows of 40
 //   entries 235 MB 96 / 119; dense 237 MB 110 / 135, 358 MB 191 / 197;
-// - block-diagonal launches (the same, of all their LPs), FP64: 308 MB 86 / 94, 402 MB 117 / 119, 473 MB
-//   139 / 136, dense rows 263 MB 112 / 126, 478 MB 209 / 202; FP32: 407 MB 129 / 133, 542 MB 172 / 173,
-//   813 MB 256 / 252, dense rows 427 MB 152 / 156.
-constexpr long long kKeepTwoPhase = 192LL << 20, kKeepTiles = 370LL << 20;
+// - block-diagonal launches (the same, of all their LPs in the FP64 form): 308 MB 86 / 94, 402 MB 117 /
+//   119, 473 MB 139 / 136, dense rows 263 MB 112 / 126, 478 MB 209 / 202, 980 MB of both 406 / 398. In the
+//   FP32 form they are faster with plain loads, or as fast, whatever they stream: 407 MB 129 / 133,
+//   637 MB 226 / 230, 813 MB 256 / 252, 2526 MB 847 / 879, 4096 LPs to 1e-4 2.07 / 2.16 s.
+constexpr long long kKeepTwoPhase = 192LL << 20, kKeepTiles = 370LL << 20, kKeepMulti = 430LL << 20;
 // Entries of both matrices, and the vectors twice: most are read and written. value: bytes of one.
 constexpr long long iteration_bytes(long long m, long long n, long long nnz, int value) {
     return 2 * nnz * (value + 4) + 2 * value * (9 * n + 8 * m);
-}
-// Of the block-diagonal launches' LPs: `bytes64` in the FP64 form, `bytes32` in the FP32 form.
-constexpr bool keep_multi(long long bytes64, long long bytes32) {
-    return 4 * bytes64 + 3 * bytes32 <= 4 * (430LL << 20);
 }
 
 // A row tile: rows [r0, r1), entries [p0, p1).
@@ -290,7 +287,7 @@ struct MultiMaps {
     // [off_a[g], off_a[g] + cnt_a[g]) of map_a (and likewise of map_at), so every launch runs
     // one kernel specialised per form and shape present.
     int off_a[12], cnt_a[12], off_at[12], cnt_at[12];
-    int keep;  // plain loads of the matrices (see keep_multi)
+    int keep;  // plain loads of the matrices (see kKeepMulti)
 };
 
 constexpr int kMapGroups = 4 * kTileShapes;

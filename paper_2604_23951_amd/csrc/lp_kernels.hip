@@ -243,7 +243,7 @@ __device__ __forceinline__ T stream_load(const T* p) {
     else return __builtin_nontemporal_load(p);
 }
 
-// KEEP: plain loads of the matrix (see kKeepTiles and keep_multi). A single FP32 launch keeps the
+// KEEP: plain loads of the matrix (see kKeepTiles and kKeepMulti). A single FP32 launch keeps the
 // non-temporal loads: its smaller matrix then competes with the gathered vectors for the L2
 // (1.7M entries, us per iteration non-temporal / plain: 29.3 / 30.2).
 template <int TN, bool KEEP, bool AHEAD, bool SHORT = false, class T, class Epi>
